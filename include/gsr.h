@@ -288,14 +288,17 @@ int64_t gsr_required_pairs(const gsr_ctx *ctx);
 /* Synchronise `stream` and return the number of (tile, Gaussian) pairs the
  * last forward on `workspace` produced: one per tile of each visible
  * Gaussian's 3-sigma rectangle, including the pairs whose tile lies outside
- * the Gaussian's alpha support (those are dropped by the pair sort and not
+ * the Gaussian's alpha support (those are left out of the lists and not
  * rendered). */
 int64_t gsr_pair_count(gsr_ctx *ctx, void *workspace, gsr_stream stream);
 
 /* DEVICE pointers into the workspace, for inspection after a forward:
  * tile_ranges [total_tiles][2] int32 (start, end) into the sorted lists,
  * sorted_ids [pairs] uint32 = view * n + gaussian index.  Tiles are numbered
- * view after view, row-major within a view. */
+ * view after view, row-major within a view, and their lists follow each other
+ * in that order without gaps: a forward places them in the order they are
+ * finished, and this call (synchronous) moves them within the workspace,
+ * which a later backward of that forward may still use. */
 gsr_status gsr_debug_tiles(gsr_ctx *ctx, void *workspace, const int32_t **tile_ranges,
                            const uint32_t **sorted_ids, int64_t *total_tiles);
 
@@ -443,11 +446,11 @@ gsr_status gsr_pose_qt_grad(gsr_ctx *ctx, int n_views, const float *q, const flo
 /* Per-stage timing of calls on this context (HIP events recorded on the
  * call's stream around each stage; HIP-graph launches are not split). */
 enum {
-  GSR_STAGE_PREPROCESS = 0, /* projection, binning data, depth keys */
-  GSR_STAGE_DEPTH_SORT,     /* radix sort of the projected Gaussians by depth */
-  GSR_STAGE_EMIT,           /* scan of tile counts and pair emission */
-  GSR_STAGE_PAIR_SORT,      /* radix sort of the pairs by tile */
-  GSR_STAGE_RANGES,         /* per-tile ranges and work order */
+  GSR_STAGE_PREPROCESS = 0, /* projection and the entries of the bins of tiles */
+  GSR_STAGE_DEPTH_SORT,     /* (no separate stage: the tile lists' kernel sorts by depth) */
+  GSR_STAGE_EMIT,           /* (no separate stage: the projection writes the entries) */
+  GSR_STAGE_PAIR_SORT,      /* tile lists: per-bin depth sort, lists and ranges; work order */
+  GSR_STAGE_RANGES,         /* (no separate stage) */
   GSR_STAGE_RASTER,         /* forward compositing, or the fused forward + L1 + backward */
   GSR_STAGE_RASTER_BWD,     /* backward compositing (unfused backward only) */
   GSR_STAGE_PREGRAD,        /* chain to parameters and pose */

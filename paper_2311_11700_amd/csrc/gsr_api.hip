@@ -18,7 +18,7 @@ struct gsr_ctx {
   bool planned = false;
   std::vector<ViewInfo> views_host;
   ViewInfo *views_dev = nullptr;
-  int32_t *tile_view_dev = nullptr;
+  int32_t *tile_view_dev = nullptr;  // [total_tiles] view of each tile, then [total_bins] view of each bin
   unsigned long long *pinned = nullptr;  // 8 pinned host words
   std::string last_error;
   int64_t required = 0;
@@ -28,7 +28,6 @@ struct gsr_ctx {
   const void *last_forward_ws = nullptr;
   int64_t fwd_generation = 0;  // successful gsr_render_forward calls on this context
   void *scratch = nullptr;     // device address of this device's static scratch (gsr_render_l1_fused_noalloc)
-  int sort_grid = 2048;
   // stage timing
   bool profiling = false;
   std::vector<hipEvent_t> ev_pool;   // (GSR_NSTAGES + 1) events per timed call
@@ -71,7 +70,23 @@ gsr_status last_launch(gsr_ctx *ctx, const char *what) {
   return hip_check(ctx, hipGetLastError(), what);
 }
 
-int passes_for(int bits) { return (bits + RADIX_BITS - 1) / RADIX_BITS; }
+// Bins that the projection's blocks count in LDS at a time.
+constexpr int LDS_BINS_MAX = 4096;
+
+// Edge (log2, in tiles) of a view's bins: the largest that leaves a view at
+// least MIN_BINS bins.  A Gaussian reaches five tiles each way in a room, so
+// halving the edge doubles to triples the entries and hardly shortens a bin's
+// list; but a view of few bins leaves the chip idle in the lists kernel.
+// Measured (edges 4, 2, 1 tiles; us per pass): 1200x680 324, 387, 595; 16
+// keyframes 3514, 3859, 7114; 640x480 (80, 300, 1200 bins) 520, 533, 588;
+// 160x120 (6, 20, 80 bins) 227, 188, 180.
+constexpr int MIN_BINS = 48;
+int bin_shift_for(int TX, int TY) {
+  static_assert(BIN_MAX == 4, "largest edge");
+  for (int s = 2; s > 0; --s)
+    if ((int64_t)((TX + (1 << s) - 1) >> s) * ((TY + (1 << s) - 1) >> s) >= MIN_BINS) return s;
+  return 0;
+}
 
 Workspace make_ws(const Plan &p, void *base_v) {
   char *base = static_cast<char *>(base_v);
@@ -80,23 +95,12 @@ Workspace make_ws(const Plan &p, void *base_v) {
   w.recA = reinterpret_cast<float4 *>(base + p.off_recA);
   w.recB = reinterpret_cast<float4 *>(base + p.off_recB);
   w.recC = reinterpret_cast<float4 *>(base + p.off_recC);
-  w.tinfo = reinterpret_cast<uint4 *>(base + p.off_rect);
-  w.support = reinterpret_cast<Support *>(base + p.off_support);
   w.count = reinterpret_cast<uint32_t *>(base + p.off_count);
-  w.tile_visible = reinterpret_cast<uint32_t *>(base + p.off_tile_visible);
-  for (int k = 0; k < 2; ++k) {
-    w.dkeys[k] = reinterpret_cast<uint32_t *>(base + p.off_dkeys[k]);
-    w.dvals[k] = reinterpret_cast<uint32_t *>(base + p.off_dvals[k]);
-    w.pkeys[k] = reinterpret_cast<uint32_t *>(base + p.off_pkeys[k]);
-    w.pvals[k] = reinterpret_cast<uint32_t *>(base + p.off_pvals[k]);
-  }
-  w.hist = reinterpret_cast<uint32_t *>(base + p.off_hist);
-  w.hoff = reinterpret_cast<uint32_t *>(base + p.off_hoff);
-  w.bucket_rec = reinterpret_cast<uint32_t *>(base + p.off_bucket);
-  w.digit_total = reinterpret_cast<uint32_t *>(base + p.off_digit);
-  w.whist = reinterpret_cast<unsigned long long *>(base + p.off_whist);
-  w.whoff = reinterpret_cast<unsigned long long *>(base + p.off_whoff);
-  w.wdigit = reinterpret_cast<unsigned long long *>(base + p.off_wdigit);
+  w.entries = reinterpret_cast<Entry *>(base + p.off_entries);
+  w.group_off = reinterpret_cast<uint32_t *>(base + p.off_group);
+  w.block_base = reinterpret_cast<uint32_t *>(base + p.off_base);
+  w.block_pairs = reinterpret_cast<unsigned long long *>(base + p.off_pairs);
+  w.ids = reinterpret_cast<uint32_t *>(base + p.off_ids);
   w.ranges = reinterpret_cast<int2 *>(base + p.off_ranges);
   w.T_final = reinterpret_cast<float *>(base + p.off_T);
   w.last = reinterpret_cast<int32_t *>(base + p.off_last);
@@ -108,11 +112,8 @@ Workspace make_ws(const Plan &p, void *base_v) {
   w.tile_cost = reinterpret_cast<uint32_t *>(base + p.off_tile_cost);
   w.expand_bits = reinterpret_cast<unsigned long long *>(base + p.off_expand_bits);
   w.expand_cnt = reinterpret_cast<uint32_t *>(base + p.off_expand_cnt);
-  w.loss_part = reinterpret_cast<float *>(base + p.off_loss);
-  w.dsorted = passes_for(32) & 1;
-  w.psorted = passes_for(p.tile_bits) & 1;
-  w.pack_shift = p.pack_shift;
-  w.id_mask = p.pack_shift ? (1u << p.pack_shift) - 1u : 0xFFFFFFFFu;
+  // (the fused step stores no per-pixel transmittance)
+  w.tile_loss = reinterpret_cast<float *>(base + p.off_T);
   return w;
 }
 
@@ -147,7 +148,6 @@ RenderConsts consts(const gsr_config &c, const gsr_gaussians &g) {
   // parameters, except that spherical-harmonic colour depends on the
   // viewing direction and so on the pose; a pose-only backward skips the rest.
   rc.grad_fields = (c.flags & GSR_GAUSS_GRAD) ? 0x3FFu : (g.sh ? 0x3FFu & ~0x020u : 0x3FFu & ~0x1E0u);
-  rc.id_mask = 0xFFFFFFFFu;
   return rc;
 }
 
@@ -193,23 +193,19 @@ void prof_end(gsr_ctx *ctx, hipStream_t s, int first_unmarked) {
   ctx->cur_events = nullptr;
 }
 
-// Projection, depth sort, pair emission, tile sort and ranges.  The
-// projection also resets the header, clears grad2d for a fused step, zeroes
-// the fused step's loss when the gradients are overwritten and, with
-// order_queue, writes the rasteriser's longest-first work order.
+// Projection and tile lists.  The projection also clears grad2d for a fused
+// step; with order_queue the lists kernel writes the rasteriser's
+// longest-first work order.
 void enqueue_lists(gsr_ctx *ctx, const gsr_gaussians &g, const gsr_camera *cams, const gsr_config &cfg,
-                   Workspace &ws, bool clear_grad2d, float *loss_zero, bool order_queue, hipStream_t s) {
+                   Workspace &ws, bool clear_grad2d, bool order_queue, hipStream_t s) {
   const Plan &p = ctx->plan;
-  launch_preprocess(g, cams, ctx->views_dev, p.n_views, cfg, ws, clear_grad2d, loss_zero, p.max_sort_tiles,
-                    order_queue ? p.total_tiles : 0, s);
+  launch_lists_begin(ws, s);
+  launch_preprocess(p, g, cams, ctx->views_dev, cfg, ws, clear_grad2d, s);
   prof_mark(ctx, s, GSR_STAGE_PREPROCESS);
-  launch_depth_sort(p, ws, s, ctx->sort_grid);
   prof_mark(ctx, s, GSR_STAGE_DEPTH_SORT);
-  launch_emit_pairs(p, ws, ctx->views_dev, s);
   prof_mark(ctx, s, GSR_STAGE_EMIT);
-  launch_pair_sort(p, ws, s, ctx->sort_grid);
+  launch_bin_lists(p, ws, ctx->views_dev, ctx->tile_view_dev + p.total_tiles, order_queue ? p.total_tiles : 0, s);
   prof_mark(ctx, s, GSR_STAGE_PAIR_SORT);
-  launch_tile_ranges(p, ws, s);
 }
 
 void enqueue_fused(gsr_ctx *ctx, const gsr_gaussians &g, const gsr_camera *cams, const gsr_config &cfg,
@@ -218,14 +214,13 @@ void enqueue_fused(gsr_ctx *ctx, const gsr_gaussians &g, const gsr_camera *cams,
                    Workspace &ws, const gsr_images *out, const gsr_grads &gr, float *loss, hipStream_t s) {
   const Plan &p = ctx->plan;
   prof_begin(ctx, s);
-  enqueue_lists(ctx, g, cams, cfg, ws, true, (cfg.flags & GSR_GRAD_OVERWRITE) ? loss : nullptr,
-                ctx->tuning.lpt_order != 0, s);
+  enqueue_lists(ctx, g, cams, cfg, ws, true, ctx->tuning.lpt_order != 0, s);
   prof_mark(ctx, s, GSR_STAGE_RANGES);
   launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, g, consts(cfg, g), t_rgb, t_depth, pmask, w_rgb,
-                      w_depth, loss_cap, out, loss, ctx->tuning, ctx->num_cus, s);
+                      w_depth, loss_cap, out, ctx->tuning, ctx->num_cus, s);
   prof_mark(ctx, s, GSR_STAGE_RASTER);
   prof_mark(ctx, s, GSR_STAGE_RASTER_BWD);
-  launch_preprocess_backward(p, g, cams, cfg, ws, gr, s);
+  launch_preprocess_backward(p, g, cams, cfg, ws, gr, loss, s);
   prof_end(ctx, s, GSR_STAGE_PREGRAD);
 }
 
@@ -316,7 +311,10 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   p.n_rec = n * n_views;
   p.capacity = pair_capacity;
   std::vector<ViewInfo> views(n_views);
-  int64_t tiles = 0, pixels = 0;
+  const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(PRE_ROUNDS_MAX, n * n_views / (PRE_BLOCK * 256)));
+  const int64_t bpv = (n + PRE_BLOCK * rounds - 1) / (PRE_BLOCK * rounds);
+  int64_t tiles = 0, pixels = 0, bins = 0, mat = 0, most = 0;
+  int max_bins = 1;
   for (int v = 0; v < n_views; ++v) {
     const int W = wh_host[2 * v], H = wh_host[2 * v + 1];
     if (W < 1 || H < 1) return fail(ctx, GSR_E_INVALID, "gsr_plan: view size must be positive");
@@ -329,23 +327,26 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
     vi.tile_off = (int32_t)tiles;
     vi._pad = 0;
     vi.pix_off = pixels;
+    vi.bin_shift = bin_shift_for(vi.TX, vi.TY);
+    vi.BX = (vi.TX + (1 << vi.bin_shift) - 1) >> vi.bin_shift;
+    vi.BY = (vi.TY + (1 << vi.bin_shift) - 1) >> vi.bin_shift;
+    vi.bin_off = (int32_t)bins;
+    vi.mat_off = mat;
+    mat += bpv * rounds * ((int64_t)vi.BX * vi.BY + 1);
+    most = std::max<int64_t>(most, n / ((int64_t)vi.BX * vi.BY));
+    bins += (int64_t)vi.BX * vi.BY;
+    max_bins = (int)std::max<int64_t>(max_bins, (int64_t)vi.BX * vi.BY);
     tiles += (int64_t)vi.TX * vi.TY;
     pixels += (int64_t)W * H;
   }
   if (tiles >= (1ll << 31)) return fail(ctx, GSR_E_UNSUPPORTED, "gsr_plan: too many tiles");
   p.total_tiles = (int)tiles;
   p.total_pixels = pixels;
-  // Tile keys 0..tiles-1 plus one key past the last tile for the pairs
-  // outside a Gaussian's alpha support.
-  int bits = 0;
-  while ((1ll << bits) < tiles + 1) ++bits;
-  p.tile_bits = bits;
-  int rbits = 1;
-  while ((1ll << rbits) < p.n_rec) ++rbits;
-  p.pack_shift = bits + rbits <= 32 ? rbits : 0;
-  const int64_t dtile = (int64_t)BLOCK * SORT_ITEMS_DEPTH, ptile = (int64_t)BLOCK * SORT_ITEMS_PAIR;
-  p.max_sort_tiles = (int)std::max<int64_t>((p.n_rec + dtile - 1) / dtile, (p.capacity + ptile - 1) / ptile);
-  p.depth_tiles = (int)std::max<int64_t>(1, (p.n_rec + dtile - 1) / dtile);
+  p.total_bins = (int)bins;
+  p.lds_bins = std::min(max_bins, LDS_BINS_MAX);
+  p.lists_cap = (int)std::min<int64_t>(LISTS_CAP_MAX, std::max<int64_t>(LISTS_CAP_MIN, (3 * most + 1023) / 1024 * 1024));
+  p.blocks_per_view = (int)bpv;
+  p.pre_rounds = rounds;
   p.n_pose_blocks = (int)std::max<int64_t>(1, (n + BLOCK - 1) / BLOCK);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -358,31 +359,24 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   p.off_recA = take(16 * nr);
   p.off_recB = take(16 * nr);
   p.off_recC = take(16 * nr);
-  p.off_rect = take(16 * nr);
-  p.off_support = take(sizeof(Support) * nr);
   p.off_count = take(4 * nr);
-  p.off_tile_visible = take(4 * (size_t)((nr + (size_t)BLOCK * SORT_ITEMS_DEPTH - 1) / ((size_t)BLOCK * SORT_ITEMS_DEPTH)));
-  for (int k = 0; k < 2; ++k) p.off_dkeys[k] = take(4 * nr);
-  for (int k = 0; k < 2; ++k) p.off_dvals[k] = take(4 * nr);
-  for (int k = 0; k < 2; ++k) p.off_pkeys[k] = take(4 * cap);
-  for (int k = 0; k < 2; ++k) p.off_pvals[k] = take(4 * cap);
-  p.off_hist = take(4 * (size_t)RADIX * p.max_sort_tiles);
-  p.off_hoff = take(4 * (size_t)RADIX * p.max_sort_tiles);
-  p.off_bucket = take(4 * (cap / EMIT_BUCKET + 2));
-  p.off_digit = take(4 * RADIX);
-  p.off_whist = take(8 * (size_t)RADIX * p.depth_tiles);
-  p.off_whoff = take(8 * (size_t)RADIX * p.depth_tiles);
-  p.off_wdigit = take(8 * RADIX);
+  const size_t pre_blocks = (size_t)p.blocks_per_view * n_views;
+  p.off_entries = take(sizeof(Entry) * cap);
+  p.off_base = take(4 * pre_blocks * rounds);
+  p.off_pairs = take(8 * pre_blocks);
+  p.off_ids = take(4 * cap);
   p.off_ranges = take(8 * (size_t)p.total_tiles);
   p.off_T = take(4 * (size_t)pixels);
   p.off_last = take(4 * (size_t)pixels);
   p.off_zr = take(4 * (size_t)pixels);
+  // The group offsets are read for the last time before the forward stores
+  // the per-pixel state, and take its place where they fit.
+  p.off_group = 4 * (size_t)mat <= off - p.off_T ? p.off_T : take(4 * (size_t)mat);
   p.off_counts = take(64);
   p.off_grad2d = take(8 * NGRAD2D * nr);
   p.off_pose = take(8 * 6 * (size_t)n_views * p.n_pose_blocks);
   p.off_queue = take(4 * (size_t)p.total_tiles);
   p.off_tile_cost = take(4 * (size_t)p.total_tiles);
-  p.off_loss = take(4);
   {
     const size_t chunks = (size_t)((pixels + EXPAND_CHUNK - 1) / EXPAND_CHUNK);
     p.off_expand_bits = take(8 * chunks * (EXPAND_CHUNK / 64));
@@ -397,13 +391,15 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   ctx->views_dev = nullptr;
   ctx->tile_view_dev = nullptr;
   ctx->planned = false;
-  std::vector<int32_t> tv(tiles);
-  for (int v = 0; v < n_views; ++v)
+  std::vector<int32_t> tv(tiles + bins);
+  for (int v = 0; v < n_views; ++v) {
     for (int64_t t = 0; t < (int64_t)views[v].TX * views[v].TY; ++t) tv[views[v].tile_off + t] = v;
+    for (int64_t b = 0; b < (int64_t)views[v].BX * views[v].BY; ++b) tv[tiles + views[v].bin_off + b] = v;
+  }
   st = hip_check(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->views_dev), sizeof(ViewInfo) * n_views), "hipMalloc(views)");
-  if (st == GSR_OK) st = hip_check(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->tile_view_dev), sizeof(int32_t) * tiles), "hipMalloc(tile_view)");
+  if (st == GSR_OK) st = hip_check(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->tile_view_dev), sizeof(int32_t) * tv.size()), "hipMalloc(tile_view)");
   if (st == GSR_OK) st = hip_check(ctx, hipMemcpy(ctx->views_dev, views.data(), sizeof(ViewInfo) * n_views, hipMemcpyHostToDevice), "hipMemcpy(views)");
-  if (st == GSR_OK) st = hip_check(ctx, hipMemcpy(ctx->tile_view_dev, tv.data(), sizeof(int32_t) * tiles, hipMemcpyHostToDevice), "hipMemcpy(tile_view)");
+  if (st == GSR_OK) st = hip_check(ctx, hipMemcpy(ctx->tile_view_dev, tv.data(), sizeof(int32_t) * tv.size(), hipMemcpyHostToDevice), "hipMemcpy(tile_view)");
   if (st != GSR_OK) return st;
   ctx->plan = p;
   ctx->views_host = views;
@@ -421,7 +417,7 @@ gsr_status gsr_render_forward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_ca
   hipStream_t s = static_cast<hipStream_t>(stream);
   Workspace ws = make_ws(ctx->plan, workspace);
   prof_begin(ctx, s);
-  enqueue_lists(ctx, *g, cams, *cfg, ws, false, nullptr, false, s);
+  enqueue_lists(ctx, *g, cams, *cfg, ws, false, false, s);
   prof_mark(ctx, s, GSR_STAGE_RANGES);
   launch_render_forward(ctx->plan, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), out, s);
   prof_end(ctx, s, GSR_STAGE_RASTER);
@@ -463,7 +459,7 @@ gsr_status gsr_render_backward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_c
   for (int j = 0; j <= GSR_STAGE_RASTER; ++j) prof_mark(ctx, s, j);
   launch_render_backward(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), g_rgb, g_depth, g_T, s);
   prof_mark(ctx, s, GSR_STAGE_RASTER_BWD);
-  launch_preprocess_backward(p, *g, cams, *cfg, ws, *grads, s);
+  launch_preprocess_backward(p, *g, cams, *cfg, ws, *grads, nullptr, s);
   prof_end(ctx, s, GSR_STAGE_PREGRAD);
   return last_launch(ctx, "gsr_render_backward launch");
 }
@@ -629,18 +625,14 @@ gsr_status gsr_debug_tiles(gsr_ctx *ctx, void *workspace, const int32_t **tile_r
   if (!ctx) return GSR_E_INVALID;
   if (!ctx->planned || !workspace) return fail(ctx, GSR_E_STATE, "gsr_debug_tiles: no plan or workspace");
   Workspace ws = make_ws(ctx->plan, workspace);
+  // The lists as one sequence in tile order.
+  gsr_status st = hip_check(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
+  if (st != GSR_OK) return st;
+  launch_lists_in_tile_order(ctx->plan, ws, nullptr);
+  st = hip_check(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
+  if (st != GSR_OK) return st;
   if (tile_ranges) *tile_ranges = reinterpret_cast<const int32_t *>(ws.ranges);
-  if (sorted_ids) {
-    if (ws.pack_shift) {
-      // Packed words: write the record ids into the (unused) value buffer.
-      gsr_status st = hip_check(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
-      if (st != GSR_OK) return st;
-      launch_unpack_ids(ctx->plan, ws, nullptr);
-      st = hip_check(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
-      if (st != GSR_OK) return st;
-    }
-    *sorted_ids = ws.pvals[ws.psorted];
-  }
+  if (sorted_ids) *sorted_ids = ws.ids;
   if (total_tiles) *total_tiles = ctx->plan.total_tiles;
   return GSR_OK;
 }
@@ -679,7 +671,7 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
   hipStream_t s = static_cast<hipStream_t>(stream);
   Workspace ws = make_ws(ctx->plan, workspace);
   const Plan &p = ctx->plan;
-  enqueue_lists(ctx, *g, cams, *cfg, ws, false, nullptr, false, s);
+  enqueue_lists(ctx, *g, cams, *cfg, ws, false, false, s);
   hipEvent_t e0, e1;
   if ((st = hip_check(ctx, hipEventCreate(&e0), "hipEventCreate")) != GSR_OK) return st;
   if ((st = hip_check(ctx, hipEventCreate(&e1), "hipEventCreate")) != GSR_OK) {
@@ -699,7 +691,7 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
       launch_fill_f32(reinterpret_cast<float *>(ws.grad2d), 0.f, 2 * p.n_rec * NGRAD2D, s);
       (void)hipEventRecord(e0, s);
       launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), target_rgb, target_depth,
-                          pixel_mask, w_rgb, w_depth, nullptr, nullptr, loss, t, ctx->num_cus, s);
+                          pixel_mask, w_rgb, w_depth, nullptr, nullptr, t, ctx->num_cus, s);
       (void)hipEventRecord(e1, s);
       st = hip_check(ctx, hipEventSynchronize(e1), "hipEventSynchronize");
       float ms = 0.f;

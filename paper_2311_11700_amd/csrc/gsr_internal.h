@@ -13,43 +13,43 @@ namespace gsr {
 constexpr int TILE = 16;          // tile edge in pixels
 constexpr int BLOCK = 256;        // one thread per pixel of a tile
 constexpr int NGRAD2D = 10;       // u, v, conic a, b, c, opacity, r, g, b, depth
-constexpr int SORT_ITEMS_DEPTH = 2;  // keys per thread per sort tile, depth sort of the records
-constexpr int SORT_ITEMS_PAIR = 8;  // keys per thread per sort tile, tile sort of the pairs
-constexpr int RADIX_BITS = 8;
+constexpr int PRE_BLOCK = 512;    // records projected at a time by a projection block
+constexpr int PRE_ROUNDS_MAX = 4; // PRE_BLOCKs of records per block, at most
+constexpr int BIN_MAX = 4;        // largest bin edge S in tiles
+// Entries the lists kernel sorts in LDS at a time (12 bytes each beside 10 KB
+// of counters): chosen by gsr_plan in this range.
+constexpr int LISTS_CAP_MIN = 4096, LISTS_CAP_MAX = 12288, LISTS_ENTRY_BYTES = 12;
+constexpr int RADIX_BITS = 8;     // buckets of the rasteriser's work order
 constexpr int RADIX = 1 << RADIX_BITS;
-constexpr int SCAN_ITEMS = 8;
-constexpr int EMIT_BUCKET = 256;  // pairs per emission bucket (one block-iteration of k_emit_pairs)
 constexpr int EXPAND_CHUNK = 2048;  // pixels per block of the adding step (eight rounds of BLOCK)
 // Real spherical harmonics of degree <= 1: 1/(2 sqrt(pi)) and sqrt(3/(4 pi)).
 constexpr double SH_C0 = 0.28209479177387814;
 constexpr double SH_C1 = 0.48860251190291992;
-
-// Bits per radix pass for keys of key_bits bits: ceil(key_bits / 8) passes
-// with the bits spread evenly (fewer digit values make longer output runs).
-__host__ __device__ constexpr int radix_digit_bits(int key_bits) {
-  return (key_bits + (key_bits + RADIX_BITS - 1) / RADIX_BITS - 1) / ((key_bits + RADIX_BITS - 1) / RADIX_BITS);
-}
 
 // Per-view geometry of the concatenated output (device copy lives in the
 // context, written at plan time).
 struct ViewInfo {
   int32_t W, H, TX, TY;
   int32_t tile_off;   // first global tile id of the view
+  int32_t bin_shift;  // log2 of the bins' edge S in tiles (0, 1 or 2)
+  int32_t BX, BY;     // bins of the view, ceil(TX / S) x ceil(TY / S)
+  int32_t bin_off;    // first global bin id of the view
   int32_t _pad;
+  int64_t mat_off;    // first word of the view's group offsets
   int64_t pix_off;    // first pixel of the view in the concatenated images
 };
 
 // Header words at the start of the workspace.
 enum HeaderWord {
-  HDR_NPAIRS = 0,      // u64 (words 0-1): pairs produced by the last forward
+  HDR_NPAIRS = 0,      // u64 (words 0-1): pairs (rectangle tiles) of the last forward
   HDR_REQUIRED = 2,    // u64 (words 2-3): largest pair count seen that overflowed
   HDR_OVERFLOW = 4,    // u32: set when a forward overflowed the pair buffer
   HDR_QUEUE = 5,       // u32: persistent rasteriser work counter
   HDR_FWD_DONE = 6,    // u32: marker that a forward filled this workspace
   HDR_MAGIC = 8,       // u32 x 2 (words 8-9): set once the header has been initialised
-  HDR_NVISIBLE = 10,   // u64 (words 10-11): records that passed the culling (depth-sorted keys)
-  HDR_NLISTED = 12,    // u64 (words 12-13): pairs inside the alpha support (the sorted tile lists)
+  HDR_NLISTED = 12,    // u64 (words 12-13): pairs inside the alpha support (the tile lists)
   HDR_COSTS = 14,      // u32: a fused step has recorded every tile's duration (sticky)
+  HDR_ENTRIES = 16,    // u64 (words 16-17): bin entries reserved
   HDR_WORDS = 64
 };
 // Header magic: a workspace whose words 8-9 do not hold it has never been
@@ -74,17 +74,19 @@ struct Support {
   double U, V, t, hy, dys, ra;  // centre, level, half-height, dy of the rightmost point, 1 / a
 };
 
-__device__ inline bool support_of(float4 A, float4 B, float alpha_min, Support &s) {
+__device__ inline bool support_of(float4 A, float4 B, double inv_alpha_min, Support &s) {
 #pragma clang fp contract(off)
   s.U = (double)A.x + (double)A.y;
   s.V = (double)A.z + (double)A.w;
   const double a = (double)B.x, b = (double)B.y, c = (double)B.z;
   const double det = a * c - b * b;
-  s.t = 2.0 * log((double)B.w / (double)alpha_min) + 1e-4;
+  s.t = 2.0 * log((double)B.w * inv_alpha_min) + 1e-4;
   if (!(det > 0.0) || !(s.t > 0.0)) return false;
-  const double SA = c / det, SB = -b / det, SC = a / det;  // covariance
-  s.hy = sqrt(s.t * SC);
-  s.dys = SB * sqrt(s.t / SA);
+  // Half-height sqrt(t a / det); the rightmost point lies at
+  // dy = (-b / det) sqrt(t det / c).
+  const double r = 1.0 / det, k = s.t * r;
+  s.hy = sqrt(k * a);
+  s.dys = -b * sqrt(k / c);
   s.ra = 1.0 / a;
   return true;
 }
@@ -109,26 +111,26 @@ __device__ inline int support_row(const Support &s, double a, double b, double c
   return (int)(chi - clo) + 1;
 }
 
+// A record in a bin of tiles: its depth key (float32 bits), its id and the
+// tiles of the bin it reaches (bit row S + column).
+struct Entry {
+  uint32_t key, id, mask;
+};
+constexpr uint32_t NO_BASE = 0xFFFFFFFFu;
+
 struct Workspace {
   uint32_t *hdr;
   float4 *recA;            // [n_rec] (u_hi, u_lo, v_hi, v_lo)
   float4 *recB;            // [n_rec] (conic a, b, c, opacity)
   float4 *recC;            // [n_rec] (r, g, b, camera-frame depth)
-  uint4 *tinfo;            // [n_rec] (view tile offset, view TX | cull << 31, tx0 | tx1 << 16, ty0 | ty1 << 16)
-  Support *support;        // [n_rec] alpha-support parameters (records with the cull bit)
   uint32_t *count;         // [n_rec] tiles touched (0 = culled)
-  uint32_t *tile_visible;  // [depth-sort tiles] visible records of each projection block
-  uint32_t *dkeys[2];      // [n_rec] depth keys (float32 bits), ping-pong
-  uint32_t *dvals[2];      // [n_rec] record ids, ping-pong
-  uint32_t *pkeys[2];      // [capacity] global tile ids, ping-pong
-  uint32_t *pvals[2];      // [capacity] record ids, ping-pong
-  uint32_t *hist;          // [RADIX][max_sort_tiles] digit counts per sort tile
-  uint32_t *hoff;          // [RADIX][max_sort_tiles] exclusive scan of hist (digit-major)
-  uint32_t *bucket_rec;    // [capacity / EMIT_BUCKET + 2] depth-order record holding pair EMIT_BUCKET * b
-  uint32_t *digit_total;   // [RADIX]
-  unsigned long long *whist;   // [RADIX][depth_tiles] pair counts per digit and tile (depth sort's last pass)
-  unsigned long long *whoff;   // [RADIX][depth_tiles] exclusive scan of whist over the tiles
-  unsigned long long *wdigit;  // [RADIX] pair counts per digit
+  // Bin entries: each projection batch's, grouped by bin, from block_base on;
+  // group_off[view][batch][bin] .. [bin + 1] is the bin's group among them.
+  Entry *entries;          // [capacity]
+  uint32_t *group_off;
+  uint32_t *block_base;    // [projection batches] (NO_BASE: none, or past the capacity)
+  unsigned long long *block_pairs;  // [projection blocks] pairs (rectangle tiles) of the block's records
+  uint32_t *ids;           // [capacity] record ids of the tile lists
   int2 *ranges;            // [total_tiles]
   float *T_final;          // [total_pixels]
   int32_t *last;           // [total_pixels]
@@ -140,14 +142,7 @@ struct Workspace {
   unsigned long long *expand_bits;  // [chunks][8][4] adding step: one bit per pixel (ballot words)
   uint32_t *expand_cnt;    // [chunks] adding step: unreliable pixels per chunk, then their exclusive scan
   uint32_t *tile_cost;     // [total_tiles] duration of each tile in the last fused step (10 ns ticks)
-  float *loss_part;        // [1] (unused slot kept for alignment)
-  int dsorted;             // which depth buffer holds the sorted result
-  int psorted;             // which pair buffer holds the sorted result
-  // Packed pairs (when tile and record bits fit 32): one word per pair,
-  // tile << pack_shift | record id, sorted without a value array; else
-  // pack_shift = 0, keys hold tiles and pvals the record ids.
-  int pack_shift;
-  uint32_t id_mask;        // record id of a sorted word: word & id_mask
+  float *tile_loss;        // [total_tiles] loss of each tile in the fused step
 };
 
 struct Plan {
@@ -157,17 +152,17 @@ struct Plan {
   int total_tiles = 0;
   int64_t total_pixels = 0;
   int64_t capacity = 0;
-  int tile_bits = 0;
-  int pack_shift = 0;      // record-id bits below the tile in a packed pair word (0: unpacked)
-  int max_sort_tiles = 0;
-  int depth_tiles = 0;     // sort tiles of the depth sort
+  int blocks_per_view = 0; // projection blocks of each view
+  int pre_rounds = 1;      // PRE_BLOCKs of records (and batches of entries) per projection block
+  int total_bins = 0;
+  int lds_bins = 0;        // bins that a projection block counts in LDS at a time
+  int lists_cap = 0;       // bin entries that the lists kernel sorts at a time
   int n_pose_blocks = 0;
   size_t bytes = 0;
   // byte offsets inside the workspace
-  size_t off_hdr, off_recA, off_recB, off_recC, off_rect, off_count, off_dkeys[2], off_dvals[2],
-      off_pkeys[2], off_pvals[2], off_hist, off_digit, off_ranges, off_T, off_last, off_zr,
-      off_grad2d, off_pose, off_queue, off_loss, off_counts, off_hoff, off_bucket, off_whist, off_whoff, off_wdigit,
-      off_support, off_tile_visible, off_tile_cost, off_expand_bits, off_expand_cnt;
+  size_t off_hdr, off_recA, off_recB, off_recC, off_count, off_entries, off_group, off_base, off_pairs, off_ids, off_ranges,
+      off_T, off_last, off_zr, off_grad2d, off_pose, off_queue, off_counts, off_tile_cost, off_expand_bits,
+      off_expand_cnt;
 };
 
 struct Tuning {
@@ -182,7 +177,6 @@ struct RenderConsts {
   float alpha_min, alpha_max, T_min;
   float bg[3];
   uint32_t grad_fields;  // bit f set: the backward accumulates grad2d field f
-  uint32_t id_mask;      // record id of a sorted pair word (set by the launchers)
 };
 
 // ---------------------------------------------------------------- device helpers
@@ -212,10 +206,10 @@ __device__ __forceinline__ void reset_header_words(uint32_t *hdr) {
   }
   hdr[HDR_NPAIRS] = 0u;
   hdr[HDR_NPAIRS + 1] = 0u;
-  hdr[HDR_NVISIBLE] = 0u;
-  hdr[HDR_NVISIBLE + 1] = 0u;
   hdr[HDR_NLISTED] = 0u;
   hdr[HDR_NLISTED + 1] = 0u;
+  hdr[HDR_ENTRIES] = 0u;
+  hdr[HDR_ENTRIES + 1] = 0u;
   hdr[HDR_QUEUE] = 0u;
   hdr[HDR_FWD_DONE] = 1u;
 }
@@ -234,6 +228,31 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, int nbits, uint64_t 
     m &= bit ? bb : ~bb;
   }
   return m;
+}
+
+// Exclusive scan of one value per thread over a block of NT threads; s_w
+// holds NT / 64 words.
+template <int NT>
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s_w, uint32_t &total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) s_w[wave] = x;
+  __syncthreads();
+  uint32_t pre = 0u, tot = 0u;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    const uint32_t c = s_w[w];
+    pre += w < wave ? c : 0u;
+    tot += c;
+  }
+  total = tot;
+  __syncthreads();
+  return pre + x - v;
 }
 
 // --------------------------------------------------------------- tile order
@@ -308,30 +327,26 @@ __device__ __forceinline__ void order_tiles(const uint32_t *__restrict__ tile_co
 
 // --------------------------------------------------------------- launchers (host)
 
-// Preprocess (projection, binning data, depth keys) for every (view, Gaussian).
-// Also resets the per-call header words, clears grad2d when clear_grad2d,
-// zeroes *loss_zero when it is not null (start of a fused step), and writes
-// the depth sort's first-pass digit counts into hist.
-// With order_total > 0 it also writes the rasteriser's longest-first work
-// order of that many tiles (from the durations the last fused step recorded).
-void launch_preprocess(const gsr_gaussians &g, const gsr_camera *cams, const ViewInfo *views,
-                       int n_views, const gsr_config &cfg, const Workspace &ws, bool clear_grad2d,
-                       float *loss_zero, int max_sort_tiles, int order_total, hipStream_t s);
+// Preprocess (projection and bin entries) for every (view, Gaussian).  Also
+// clears grad2d when clear_grad2d (start of a fused step).
+void launch_preprocess(const Plan &p, const gsr_gaussians &g, const gsr_camera *cams, const ViewInfo *views,
+                       const gsr_config &cfg, const Workspace &ws, bool clear_grad2d, hipStream_t s);
 
 // Reliable-Gaussian selection (fine tracking stage).
 void launch_select_reliable(const gsr_gaussians &g, const gsr_camera *cam, const float *depth, int W, int H,
                             float eps, float z_near, uint8_t *out, hipStream_t s);
 
-// Sorting and list construction.
-int launch_depth_sort(const Plan &p, Workspace &ws, hipStream_t s, int sort_grid);
-void launch_emit_pairs(const Plan &p, const Workspace &ws, const ViewInfo *views, hipStream_t s);
-int launch_pair_sort(const Plan &p, Workspace &ws, hipStream_t s, int sort_grid);
-void launch_tile_ranges(const Plan &p, const Workspace &ws, hipStream_t s);
-// Packed pairs: record ids of the sorted words into pvals[psorted].
-void launch_unpack_ids(const Plan &p, const Workspace &ws, hipStream_t s);
+// Start of a call (before the projection), and the tile lists from the bin
+// entries.  With order_total > 0 the lists kernel also writes the rasteriser's
+// longest-first work order of that many tiles (from the durations the last
+// fused step recorded).
+void launch_lists_begin(const Workspace &ws, hipStream_t s);
+void launch_bin_lists(const Plan &p, const Workspace &ws, const ViewInfo *views, const int32_t *bin_view,
+                      int order_total, hipStream_t s);
+// The lists moved into tile order without gaps (inspection).
+void launch_lists_in_tile_order(const Plan &p, const Workspace &ws, hipStream_t s);
 void launch_fill_u32(uint32_t *ptr, uint32_t value, int64_t count, hipStream_t s);
 void launch_fill_f32(float *ptr, float value, int64_t count, hipStream_t s);
-void launch_reset_header(const Workspace &ws, hipStream_t s);
 // The rasteriser's work order (order_tiles) as a one-block kernel.
 void launch_queue_order(const Workspace &ws, int total_tiles, hipStream_t s);
 
@@ -346,8 +361,7 @@ void launch_render_backward(const Plan &p, const Workspace &ws, const ViewInfo *
 void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *views,
                          const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
                          const float *t_rgb, const float *t_depth, const uint8_t *pmask,
-                         float w_rgb, float w_depth, const float *loss_cap, const gsr_images *out, float *loss,
-                         const Tuning &tun, int num_cus, hipStream_t s);
+                         float w_rgb, float w_depth, const float *loss_cap, const gsr_images *out, const Tuning &tun, int num_cus, hipStream_t s);
 // Work totals of the last forward (re-walks its lists; needs the Gaussians'
 // colours and the constants of that call).
 void launch_work_counts(const Plan &p, const Workspace &ws, const ViewInfo *views, const int32_t *tile_view,
@@ -375,9 +389,10 @@ void launch_expand_add(const Plan &p, const ViewInfo *views, const gsr_camera *c
 void launch_expand_delete(const gsr_gaussians &g, const gsr_camera *cam, const float *depth_obs, int W, int H,
                           float gamma, float eta, float z_near, float *logit_out, uint8_t *decayed, hipStream_t s);
 
-// Backward preprocess (chain to parameters and pose).
+// Backward preprocess (chain to parameters and pose; with loss, also the fused
+// step's tile losses summed into *loss).
 void launch_preprocess_backward(const Plan &p, const gsr_gaussians &g, const gsr_camera *cams,
-                                const gsr_config &cfg, const Workspace &ws, const gsr_grads &gr,
+                                const gsr_config &cfg, const Workspace &ws, const gsr_grads &gr, float *loss,
                                 hipStream_t s);
 
 }  // namespace gsr

@@ -355,38 +355,49 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 }
 
 // Deterministic reduction of the per-block pose partials: one block per
-// (view, component), fixed summation order.
-__global__ __launch_bounds__(BLOCK) void k_pose_reduce(const double *__restrict__ part, int n_blocks,
-                                                       int n_views, int overwrite, float *__restrict__ d_pose) {
+// (view, component), fixed summation order; with tile_loss a last block sums
+// the tiles' losses the same way (in FP64: a float sum over the tiles in the
+// order they finish differs between two runs in its sixth digit).
+__global__ __launch_bounds__(BLOCK) void k_step_reduce(const double *__restrict__ part, int n_blocks, int n_views,
+                                                       int n_pose, int overwrite, float *__restrict__ d_pose,
+                                                       const float *__restrict__ tile_loss, int n_tiles,
+                                                       float *__restrict__ loss) {
   __shared__ double red[BLOCK];
   const int vc = blockIdx.x;  // view * 6 + component
   double acc = 0.0;
-  for (int b = threadIdx.x; b < n_blocks; b += BLOCK) acc += part[(int64_t)b * n_views * 6 + vc];
+  if (vc < n_pose) {
+    for (int b = threadIdx.x; b < n_blocks; b += BLOCK) acc += part[(int64_t)b * n_views * 6 + vc];
+  } else {
+#pragma unroll 8
+    for (int t = threadIdx.x; t < n_tiles; t += BLOCK) acc += (double)tile_loss[t];
+  }
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int w = BLOCK / 2; w > 0; w >>= 1) {
     if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) put(d_pose[vc], red[0], overwrite != 0);
+  if (threadIdx.x == 0) put(vc < n_pose ? d_pose[vc] : *loss, red[0], overwrite != 0);
 }
 
 void launch_preprocess_backward(const Plan &p, const gsr_gaussians &g, const gsr_camera *cams,
-                                const gsr_config &cfg, const Workspace &ws, const gsr_grads &gr,
+                                const gsr_config &cfg, const Workspace &ws, const gsr_grads &gr, float *loss,
                                 hipStream_t s) {
   const bool want_pose = (cfg.flags & GSR_POSE_GRAD) && gr.d_pose;
-  if (g.n == 0) {
+  const int overwrite = (cfg.flags & GSR_GRAD_OVERWRITE) ? 1 : 0;
+  if (g.n > 0) {
+    PreConstsB pc{cfg.z_near, cfg.lowpass, cfg.cutoff_sigma, cfg.flags, cfg.fov_guard};
+    const size_t lds = want_pose ? (size_t)4 * p.n_views * 6 * sizeof(double) : 0;
+    hipLaunchKernelGGL(g.sh ? k_preprocess_bwd<true> : k_preprocess_bwd<false>, dim3(p.n_pose_blocks), dim3(BLOCK), lds, s, g, cams,
+                       p.n_views, pc, ws, gr);
+  } else if (want_pose && overwrite) {
     // No Gaussian, no gradient: an overwritten pose gradient is zero.
-    if (want_pose && (cfg.flags & GSR_GRAD_OVERWRITE)) launch_fill_f32(gr.d_pose, 0.f, (int64_t)p.n_views * 6, s);
-    return;
+    launch_fill_f32(gr.d_pose, 0.f, (int64_t)p.n_views * 6, s);
   }
-  PreConstsB pc{cfg.z_near, cfg.lowpass, cfg.cutoff_sigma, cfg.flags, cfg.fov_guard};
-  const size_t lds = want_pose ? (size_t)4 * p.n_views * 6 * sizeof(double) : 0;
-  hipLaunchKernelGGL(g.sh ? k_preprocess_bwd<true> : k_preprocess_bwd<false>, dim3(p.n_pose_blocks), dim3(BLOCK), lds, s, g, cams,
-                     p.n_views, pc, ws, gr);
-  if (want_pose)
-    hipLaunchKernelGGL(k_pose_reduce, dim3(p.n_views * 6), dim3(BLOCK), 0, s, ws.pose_part, p.n_pose_blocks,
-                       p.n_views, (cfg.flags & GSR_GRAD_OVERWRITE) ? 1 : 0, gr.d_pose);
+  const int n_pose = g.n > 0 && want_pose ? p.n_views * 6 : 0;
+  if (n_pose > 0 || loss)
+    hipLaunchKernelGGL(k_step_reduce, dim3((unsigned)(n_pose + (loss ? 1 : 0))), dim3(BLOCK), 0, s, ws.pose_part,
+                       p.n_pose_blocks, p.n_views, n_pose, overwrite, gr.d_pose, ws.tile_loss, p.total_tiles, loss);
 }
 
 }  // namespace gsr

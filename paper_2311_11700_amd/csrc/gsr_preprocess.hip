@@ -20,9 +20,8 @@ struct PreConsts {
   uint32_t flags;
   float fov_guard;
   float alpha_min;
+  double inv_alpha_min;
   int clear_grad2d;  // zero each record's grad2d row (start of a fused step)
-  float *loss_zero;  // zeroed by one thread when not null
-  int order_total;   // > 0: block 0 writes the rasteriser's work order of this many tiles
 };
 
 // Rotation matrix of a unit quaternion (w, x, y, z) (GS-SLAM supplement,
@@ -40,15 +39,70 @@ __device__ __forceinline__ void quat_rot(T w, T x, T y, T z, T R[9]) {
   R[8] = T(1) - T(2) * (x * x + y * y);
 }
 
-// Project record rec = view * n + i; returns its depth sort key (float32
-// depth bits, 0xFFFFFFFF when culled).  SH: spherical-harmonic colour.
-template <bool SH>
-__device__ __forceinline__ uint32_t project_record(const gsr_gaussians &g, const gsr_camera *__restrict__ cams,
-                                                   const ViewInfo *__restrict__ views, const PreConsts &pc,
-                                                   const Workspace &ws, int view, int64_t i, int64_t rec) {
-  const ViewInfo vi = views[view];
-  const gsr_camera &cam = cams[view];
+// Whether record i of the view is certainly culled: masked, not beyond the near
+// plane, or its tile rectangle empty.  The rectangle's half-width is
+// cutoff sqrt(A) with A <= |J_0|^2 max(scale)^2 + lowpass; the bound is
+// evaluated in float32 with margins far above its rounding, and any
+// comparison with a NaN keeps the record for the exact tests.
+__device__ __forceinline__ bool surely_culled(const gsr_gaussians &g, const gsr_camera &cam, const ViewInfo &vi,
+                                              const PreConsts &pc, int64_t i) {
+  if (g.mask && g.mask[i] == 0) return true;
+  const double mx = g.mean[3 * i], my = g.mean[3 * i + 1], mz = g.mean[3 * i + 2];
+  const double x = (((double)cam.R[0] * mx + (double)cam.R[1] * my) + (double)cam.R[2] * mz) + (double)cam.t[0];
+  const double y = (((double)cam.R[3] * mx + (double)cam.R[4] * my) + (double)cam.R[5] * mz) + (double)cam.t[1];
+  const double z = (((double)cam.R[6] * mx + (double)cam.R[7] * my) + (double)cam.R[8] * mz) + (double)cam.t[2];
+  if (z <= (double)pc.z_near) return true;
+  if ((pc.flags & GSR_FULL_RECT) || !(cam.fx > 0.f) || !(cam.fy > 0.f)) return false;
+  const float ls = fmaxf(fmaxf(g.log_scale[3 * i], g.log_scale[3 * i + 1]), g.log_scale[3 * i + 2]);
+  const float smax = __expf(ls) * 1.001f;
+  const float rz = 1.f / (float)z, xz = (float)x * rz, yz = (float)y * rz;
+  float tx = fabsf(xz), ty = fabsf(yz);
+  if (pc.fov_guard > 0.f) {
+    tx = fminf(tx, pc.fov_guard * (0.5f * (float)vi.W) / cam.fx * 1.001f);
+    ty = fminf(ty, pc.fov_guard * (0.5f * (float)vi.H) / cam.fy * 1.001f);
+  }
+  const float jx = cam.fx * rz, jy = cam.fy * rz;
+  const float rx = pc.cutoff * sqrtf(jx * jx * (1.f + tx * tx) * smax * smax + fabsf(pc.lowpass));
+  const float ry = pc.cutoff * sqrtf(jy * jy * (1.f + ty * ty) * smax * smax + fabsf(pc.lowpass));
+  const float u = cam.fx * xz + cam.cx, v = cam.fy * yz + cam.cy;
+  const float mu = rx * 1.001f + 1e-4f * (fabsf(u) + fabsf(cam.cx)) + 0.5f;
+  const float mv = ry * 1.001f + 1e-4f * (fabsf(v) + fabsf(cam.cy)) + 0.5f;
+  return u + mu < 0.f || u - mu > (float)(vi.TX * TILE) || v + mv < 0.f || v - mv > (float)(vi.TY * TILE);
+}
 
+// What the binning needs of a visible record: its tile rectangle, depth key,
+// conic and alpha support.
+struct Staged {
+  Support sp;
+  float a, b, c;
+  uint32_t key, rec;
+  uint16_t tx0, tx1, ty0, ty1;
+};
+
+// The projection's arguments, in LDS.
+struct ProjArgs {
+  gsr_gaussians g;
+  ViewInfo vi;
+  PreConsts pc;
+  float4 *recA, *recB, *recC;
+  uint32_t *count;
+  double *grad2d;
+  int cull;
+};
+
+// Project record rec = view * n + i; returns whether it is visible (`out` is
+// then filled in).  SH: spherical-harmonic colour.  Out of line, with its
+// arguments in LDS: inside the loop over the batches the compiler keeps the
+// camera's FP64 values and the coefficients of exp and log in registers
+// (170 instead of 90, and one block per CU less).
+template <bool SH>
+__device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, const gsr_camera *camp, int64_t i,
+                                                         int64_t rec, Staged *out) {
+  const gsr_gaussians &g = args->g;
+  const ViewInfo &vi = args->vi;
+  const PreConsts &pc = args->pc;
+  const ProjArgs &ws = *args;
+  const gsr_camera &cam = *camp;
   const float fm0 = g.mean[3 * i], fm1 = g.mean[3 * i + 1], fm2 = g.mean[3 * i + 2];
   const float fl0 = g.log_scale[3 * i], fl1 = g.log_scale[3 * i + 1], fl2 = g.log_scale[3 * i + 2];
   const float4 fq = reinterpret_cast<const float4 *>(g.quat)[i];
@@ -79,57 +133,51 @@ __device__ __forceinline__ uint32_t project_record(const gsr_gaussians &g, const
   const double z = ((W6 * mx + W7 * my) + W8 * mz) + (double)cam.t[2];
   ok = ok && (z > (double)pc.z_near);
 
-  // Covariance (Eq. 2).
+  // Rotation of Eq. 2.
   double qw = fq.x, qx = fq.y, qy = fq.z, qz = fq.w;
   const double qn = sqrt(((qw * qw + qx * qx) + qy * qy) + qz * qz);
   ok = ok && (qn > 0.0);
   double Rq[9];
   {
-    const double inv = ok ? qn : 1.0;
-    qw /= inv; qx /= inv; qy /= inv; qz /= inv;
+    const double inv = 1.0 / (ok ? qn : 1.0);
+    qw *= inv; qx *= inv; qy *= inv; qz *= inv;
     quat_rot<double>(qw, qx, qy, qz, Rq);
   }
   const double s0 = exp((double)fl0), s1 = exp((double)fl1), s2 = exp((double)fl2);
-  const double q0 = s0 * s0, q1 = s1 * s1, q2 = s2 * s2;
-  double S[9];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c)
-      S[3 * r + c] = (Rq[3 * r] * q0 * Rq[3 * c] + Rq[3 * r + 1] * q1 * Rq[3 * c + 1]) +
-                     Rq[3 * r + 2] * q2 * Rq[3 * c + 2];
-  // Camera-frame covariance W S W^T.
-  const double Wm[9] = {W0, W1, W2, W3, W4, W5, W6, W7, W8};
-  double M[9], Sc[9];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c)
-      M[3 * r + c] = (Wm[3 * r] * S[c] + Wm[3 * r + 1] * S[3 + c]) + Wm[3 * r + 2] * S[6 + c];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c)
-      Sc[3 * r + c] = (M[3 * r] * Wm[3 * c] + M[3 * r + 1] * Wm[3 * c + 1]) + M[3 * r + 2] * Wm[3 * c + 2];
   // EWA projection (Eq. 3): J = [[fx/z, 0, -fx (x/z)/z], [0, fy/z, -fy (y/z)/z]],
   // with x/z and y/z limited to +-g W/(2 fx), +-g H/(2 fy) when the guard g
-  // is on (the projected centre below is not limited).
+  // is on (the projected centre below is not limited).  With T = J W R_q S
+  // the projected covariance is T T^T: no 3x3 covariance is formed.
   const double fx = cam.fx, fy = cam.fy;
-  const double zz = ok ? z : 1.0;
-  double rx_ = x / zz, ry_ = y / zz;
+  const double iz = 1.0 / (ok ? z : 1.0);
+  const double px = (fx * x) * iz, py = (fy * y) * iz;
+  double gx = px, gy = py;
   if (pc.fov_guard > 0.f) {
-    const double lx = (double)pc.fov_guard * (0.5 * (double)vi.W) / fx;
-    const double ly = (double)pc.fov_guard * (0.5 * (double)vi.H) / fy;
-    rx_ = fmin(lx, fmax(-lx, rx_));
-    ry_ = fmin(ly, fmax(-ly, ry_));
+    const double lx = (double)pc.fov_guard * (0.5 * (double)vi.W), ly = (double)pc.fov_guard * (0.5 * (double)vi.H);
+    gx = fx >= 0.0 ? fmin(lx, fmax(-lx, px)) : lx;
+    gy = fy >= 0.0 ? fmin(ly, fmax(-ly, py)) : ly;
   }
-  const double J00 = fx / zz, J02 = -(fx * rx_) / zz;
-  const double J11 = fy / zz, J12 = -(fy * ry_) / zz;
-  const double T00 = J00 * Sc[0] + J02 * Sc[6], T01 = J00 * Sc[1] + J02 * Sc[7],
-               T02 = J00 * Sc[2] + J02 * Sc[8];
-  const double T11 = J11 * Sc[4] + J12 * Sc[7], T12 = J11 * Sc[5] + J12 * Sc[8];
-  const double A = (T00 * J00 + T02 * J02) + (double)pc.lowpass;
-  const double B = T01 * J11 + T02 * J12;
-  const double C = (T11 * J11 + T12 * J12) + (double)pc.lowpass;
+  const double J00 = fx * iz, J02 = -gx * iz;
+  const double J11 = fy * iz, J12 = -gy * iz;
+  double T0[3], T1[3];
+  {
+    const double P0[3] = {fma(J00, W0, J02 * W6), fma(J00, W1, J02 * W7), fma(J00, W2, J02 * W8)};
+    const double P1[3] = {fma(J11, W3, J12 * W6), fma(J11, W4, J12 * W7), fma(J11, W5, J12 * W8)};
+    const double sc[3] = {s0, s1, s2};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      T0[k] = fma(P0[0], Rq[k], fma(P0[1], Rq[3 + k], P0[2] * Rq[6 + k])) * sc[k];
+      T1[k] = fma(P1[0], Rq[k], fma(P1[1], Rq[3 + k], P1[2] * Rq[6 + k])) * sc[k];
+    }
+  }
+  const double A = fma(T0[0], T0[0], fma(T0[1], T0[1], T0[2] * T0[2])) + (double)pc.lowpass;
+  const double B = fma(T0[0], T1[0], fma(T0[1], T1[1], T0[2] * T1[2]));
+  const double C = fma(T1[0], T1[0], fma(T1[1], T1[1], T1[2] * T1[2])) + (double)pc.lowpass;
   const double det = A * C - B * B;
   ok = ok && (det > 0.0);
 
-  const double u = (fx * x) / zz + (double)cam.cx;
-  const double v = (fy * y) / zz + (double)cam.cy;
+  const double u = px + (double)cam.cx;
+  const double v = py + (double)cam.cy;
 
   int tx0 = 0, tx1 = vi.TX - 1, ty0 = 0, ty1 = vi.TY - 1;
   if (!(pc.flags & GSR_FULL_RECT) && ok) {
@@ -146,7 +194,7 @@ __device__ __forceinline__ uint32_t project_record(const gsr_gaussians &g, const
 
   if (!ok) {
     ws.count[rec] = 0u;
-    return 0xFFFFFFFFu;
+    return false;
   }
   // Only records that enter tile lists receive or give back 2D gradients.
   if (pc.clear_grad2d) {
@@ -158,7 +206,8 @@ __device__ __forceinline__ uint32_t project_record(const gsr_gaussians &g, const
   const float uh = (float)u, vh = (float)v;
   const float op = (float)(1.0 / (1.0 + exp(-(double)fop)));
   const float4 fa = make_float4(uh, (float)(u - (double)uh), vh, (float)(v - (double)vh));
-  const float4 fb = make_float4((float)(C / det), (float)(-B / det), (float)(A / det), op);
+  const double idet = 1.0 / det;
+  const float4 fb = make_float4((float)(C * idet), (float)(-B * idet), (float)(A * idet), op);
   ws.recA[rec] = fa;
   ws.recB[rec] = fb;
   float fc0 = col[0], fc1 = col[1], fc2 = col[2];
@@ -181,97 +230,242 @@ __device__ __forceinline__ uint32_t project_record(const gsr_gaussians &g, const
     fc2 = (float)c[2];
   }
   ws.recC[rec] = make_float4(fc0, fc1, fc2, zf);
-  // Every tile of the rectangle gets a pair; the emission marks the ones the
-  // alpha support does not reach (none in the full-rectangle mode or
-  // without an alpha threshold).
-  const bool cull = !(pc.flags & GSR_FULL_RECT) && pc.alpha_min > 0.f;
-  if (cull) {
+  if (args->cull) {
     Support sp;
-    if (!support_of(fa, fb, pc.alpha_min, sp)) {
+    if (!support_of(fa, fb, pc.inv_alpha_min, sp)) {
       sp.U = sp.V = sp.t = sp.dys = sp.ra = 0.0;
-      sp.hy = -1.0;  // no row reaches it: every pair is dropped
+      sp.hy = -1.0;  // no row reaches it
     }
-    ws.support[rec] = sp;
+    out->sp = sp;
   }
-  ws.tinfo[rec] = make_uint4((uint32_t)vi.tile_off, (uint32_t)vi.TX | (cull ? 0x80000000u : 0u),
-                             (uint32_t)tx0 | ((uint32_t)tx1 << 16), (uint32_t)ty0 | ((uint32_t)ty1 << 16));
   ws.count[rec] = (uint32_t)(tx1 - tx0 + 1) * (uint32_t)(ty1 - ty0 + 1);
-  return __float_as_uint(zf);
+  out->a = fb.x;
+  out->b = fb.y;
+  out->c = fb.z;
+  out->key = __float_as_uint(zf);
+  out->rec = (uint32_t)rec;
+  out->tx0 = (uint16_t)tx0;
+  out->tx1 = (uint16_t)tx1;
+  out->ty0 = (uint16_t)ty0;
+  out->ty1 = (uint16_t)ty1;
+  return true;
 }
 
-// One block per sort tile of the depth sort: project its records, write the
-// depth keys and record ids of the visible ones to the front of the tile's
-// slots in record order (the depth sort reads only those, so culled records
-// never enter the sort), and count the keys' first radix digit (bits 0-7)
-// for the sort's first pass.  Block 0 also resets the per-call header words
-// (and the fused step's loss when it is overwritten).
-constexpr int PRE_BLOCK = BLOCK * SORT_ITEMS_DEPTH;
-template <bool SH>
-__global__ __launch_bounds__(PRE_BLOCK) void k_preprocess(gsr_gaussians g, const gsr_camera *__restrict__ cams,
-                                                          const ViewInfo *__restrict__ views, PreConsts pc,
-                                                          Workspace ws, int n_views, int max_tiles) {
-  constexpr int NW = PRE_BLOCK / 64;
-  __shared__ uint32_t cnt[RADIX];
-  __shared__ uint32_t s_wv[NW];
-  __shared__ uint32_t s_qcnt[RADIX], s_qcur[RADIX], s_qw[NW], s_timed;
-  const int64_t rec = (int64_t)blockIdx.x * PRE_BLOCK + threadIdx.x;
-  const int wave = threadIdx.x >> 6;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    reset_header_words(ws.hdr);
-    s_timed = ws.hdr[HDR_COSTS];  // read by the thread that reset the header
-    if (pc.loss_zero) *pc.loss_zero = 0.f;
+// One block per `rounds` x PRE_BLOCK Gaussians of one view: an early test
+// drops most of the records outside the view (a third to four fifths of a room
+// seen from inside), and the rest, packed into full wavefronts, go through the
+// projection in batches of PRE_BLOCK.  Then the block writes an entry of every
+// visible one for every bin of tiles it reaches, in three steps spread evenly
+// over the block whatever the records' sizes: the column range inside the alpha
+// support of every tile row of every record (FP64, once; ROW_CACHE rows are
+// kept in LDS, the rest found again where they are used); then, per bin row of
+// every record, the entries per bin are counted (lds_bins bins at a time) and
+// one global add reserves the batch's place; then they are written grouped by
+// bin.
+constexpr int ROW_CACHE = 3072;
+
+// Column range of one tile row of a record: first column | length << 16 (length
+// 0 where the alpha support does not reach the row).
+__device__ __forceinline__ uint32_t row_range(const Staged &t, bool cull, int ty) {
+  int c0 = t.tx0, len = (int)t.tx1 - (int)t.tx0 + 1;
+  if (cull) {
+    c0 = 0;
+    len = support_row(t.sp, (double)t.a, (double)t.b, (double)t.c, ty, t.tx0, t.tx1, c0);
   }
-  if (blockIdx.x == 0 && pc.order_total > 0) {
-    // The rasteriser's work order for this step, from the tile durations
-    // the last fused step recorded (the other blocks cover its time).
-    __syncthreads();
-    order_tiles<PRE_BLOCK>(ws.tile_cost, s_timed != 0u, pc.order_total, ws.queue, s_qcnt, s_qcur, s_qw);
+  return (uint32_t)c0 | (uint32_t)len << 16;
+}
+
+// Last of the n ascending values first[] that is <= i.
+__device__ __forceinline__ int owner_of(const uint32_t *first, int n, uint32_t i) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= i) lo = mid;
+    else hi = mid - 1;
   }
-  if (threadIdx.x < RADIX) cnt[threadIdx.x] = 0u;
-  uint32_t key = 0xFFFFFFFFu;
-  if (rec < g.n * (int64_t)n_views) {
-    const int view = (int)(rec / g.n);
-    key = project_record<SH>(g, cams, views, pc, ws, view, rec - (int64_t)view * g.n, rec);
-  }
-  // Culled records have the key 0xFFFFFFFF (a visible depth is a positive
-  // finite float, whose bits are below it).
-  const bool vis = key != 0xFFFFFFFFu;
-  const uint64_t vmask = __ballot(vis);
-  if ((threadIdx.x & 63) == 0) s_wv[wave] = (uint32_t)__popcll(vmask);
-  __syncthreads();
-  uint32_t before = 0u, total = 0u;
+  return lo;
+}
+
+// Mask of the tiles of bin column bx that the rows cover (bit r S + column).
+__device__ __forceinline__ uint32_t unit_mask(const uint32_t rows[BIN_MAX], int bx, int shift) {
+  const int S = 1 << shift;
+  uint32_t m = 0u;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    before += w < wave ? s_wv[w] : 0u;
-    total += s_wv[w];
+  for (int r = 0; r < BIN_MAX; ++r) {
+    const int c0 = (int)(rows[r] & 0xFFFFu), len = (int)(rows[r] >> 16);
+    const int a = max(c0 - (bx << shift), 0), b = min(c0 + len - (bx << shift), S);
+    if (b > a) m |= ((1u << b) - (1u << a)) << (r * S);
   }
-  if (vis) {
-    const int64_t pos = (int64_t)blockIdx.x * PRE_BLOCK + before + (uint32_t)__popcll(vmask & lanemask_lt());
-    ws.dkeys[0][pos] = key;
-    ws.dvals[0][pos] = (uint32_t)rec;
-  }
-  const uint32_t d = key & (RADIX - 1u);
-  const uint64_t peers = match_digit(d, RADIX_BITS, vmask);
-  if (vis && (peers & lanemask_lt()) == 0ull) atomicAdd(&cnt[d], (uint32_t)__popcll(peers));
-  __syncthreads();
-  if (threadIdx.x < RADIX) ws.hist[(size_t)threadIdx.x * max_tiles + blockIdx.x] = cnt[threadIdx.x];
-  if (threadIdx.x == 0) ws.tile_visible[blockIdx.x] = total;
+  return m;
 }
 
-void launch_preprocess(const gsr_gaussians &g, const gsr_camera *cams, const ViewInfo *views,
-                       int n_views, const gsr_config &cfg, const Workspace &ws, bool clear_grad2d,
-                       float *loss_zero, int max_sort_tiles, int order_total, hipStream_t s) {
-  PreConsts pc{cfg.z_near, cfg.lowpass, cfg.cutoff_sigma, cfg.flags, cfg.fov_guard, cfg.alpha_min,
-               clear_grad2d ? 1 : 0, loss_zero, order_total};
-  const int64_t n_rec = g.n * (int64_t)n_views;
-  if (g.n > 0) {
-    hipLaunchKernelGGL(g.sh ? k_preprocess<true> : k_preprocess<false>, dim3((unsigned)((n_rec + PRE_BLOCK - 1) / PRE_BLOCK)), dim3(PRE_BLOCK), 0, s,
-                       g, cams, views, pc, ws, n_views, max_sort_tiles);
-  } else {
-    launch_reset_header(ws, s);
-    if (loss_zero) launch_fill_f32(loss_zero, 0.f, 1, s);
-    launch_queue_order(ws, order_total, s);
+template <bool SH>
+__global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_preprocess(gsr_gaussians g, const gsr_camera *__restrict__ cams,
+                                                          const ViewInfo *__restrict__ views, PreConsts pc,
+                                                          Workspace ws, int bpv, int rounds, int lds_bins,
+                                                          unsigned long long cap) {
+  constexpr int NW = PRE_BLOCK / 64;
+  extern __shared__ uint32_t s_cur[];  // [lds_bins]
+  __shared__ ProjArgs s_args;
+  __shared__ Staged s_rec[PRE_BLOCK];  // the records of a batch (the visible ones filled in)
+  __shared__ uint32_t s_first[PRE_BLOCK];
+  __shared__ uint32_t s_rowat[PRE_BLOCK];  // first tile row of each record
+  __shared__ uint32_t s_rows[ROW_CACHE];
+  __shared__ uint16_t s_left[PRE_BLOCK * PRE_ROUNDS_MAX];  // records the early test leaves
+  __shared__ uint32_t s_w[NW];
+  __shared__ unsigned long long s_pairs[NW];
+  __shared__ uint32_t s_base, s_nleft;
+  const int view = blockIdx.x / bpv, blk = blockIdx.x - view * bpv;
+  const ViewInfo vi = views[view];
+  const gsr_camera &cam = cams[view];
+  const int wave = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blk * PRE_BLOCK * rounds;
+  const int64_t rec0 = (int64_t)view * g.n;
+  // Every tile of a record's rectangle is a pair; the lists leave out the
+  // tiles its alpha support does not reach (none in the full-rectangle mode
+  // or without an alpha threshold).
+  const bool cull = !(pc.flags & GSR_FULL_RECT) && pc.alpha_min > 0.f;
+  if (threadIdx.x == 0) {
+    s_nleft = 0u;
+    s_args = ProjArgs{g, vi, pc, ws.recA, ws.recB, ws.recC, ws.count, ws.grad2d, cull ? 1 : 0};
   }
+  __syncthreads();
+  for (int r = 0; r < rounds; ++r) {
+    const int64_t i = i0 + r * PRE_BLOCK + threadIdx.x;
+    bool left = false;
+    if (i < g.n) {
+      left = !surely_culled(g, cam, vi, pc, i);
+      if (!left) ws.count[rec0 + i] = 0u;
+    }
+    const uint64_t m = __ballot(left);
+    uint32_t at = 0u;
+    if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&s_nleft, (uint32_t)__popcll(m));
+    at = __shfl(at, 0);
+    if (left) s_left[at + (uint32_t)__popcll(m & lanemask_lt())] = (uint16_t)(r * PRE_BLOCK + threadIdx.x);
+  }
+  __syncthreads();
+  const int nleft = (int)s_nleft;
+  const int shift = vi.bin_shift, S = 1 << shift, nb = vi.BX * vi.BY;
+  unsigned long long pairs = 0ull;
+  for (int batch = 0; batch < rounds; ++batch) {
+    const int group = blockIdx.x * rounds + batch;
+    if (batch * PRE_BLOCK >= nleft) {
+      if (threadIdx.x == 0) ws.block_base[group] = NO_BASE;
+      continue;
+    }
+    const int k = batch * PRE_BLOCK + (int)threadIdx.x;
+    const int nrec = min(nleft - batch * PRE_BLOCK, PRE_BLOCK);
+    bool vis = false;
+    if (k < nleft) {
+      const int64_t i = i0 + (int)s_left[k];
+      vis = project_record<SH>(&s_args, &cam, i, rec0 + i, &s_rec[threadIdx.x]);
+    }
+    uint32_t units, tile_rows;
+    {
+      // (records without rows share the next one's first row and unit)
+      uint32_t nu = 0u, nr = 0u;
+      if (vis) {
+        const Staged &t = s_rec[threadIdx.x];
+        nr = (uint32_t)(t.ty1 - t.ty0 + 1);
+        nu = (uint32_t)((t.ty1 >> shift) - (t.ty0 >> shift) + 1);
+        pairs += (unsigned long long)(t.tx1 - t.tx0 + 1) * nr;
+      }
+      s_first[threadIdx.x] = block_exclusive_scan<PRE_BLOCK>(nu, s_w, units);
+      s_rowat[threadIdx.x] = block_exclusive_scan<PRE_BLOCK>(nr, s_w, tile_rows);
+    }
+    __syncthreads();
+    for (uint32_t u = threadIdx.x; u < min(tile_rows, (uint32_t)ROW_CACHE); u += PRE_BLOCK) {
+      const int o = owner_of(s_rowat, nrec, u);
+      s_rows[u] = row_range(s_rec[o], cull, s_rec[o].ty0 + (int)(u - s_rowat[o]));
+    }
+    __syncthreads();
+    uint32_t *row = ws.group_off + vi.mat_off + ((int64_t)blk * rounds + batch) * (nb + 1);
+    uint32_t carry = 0u;
+    // Sweep 0 over all bins (counts and offsets), then sweep 1 (entries).
+    for (int sweep = 0; sweep < 2; ++sweep) {
+      for (int c0 = 0; c0 < nb; c0 += lds_bins) {
+        const int cn = min(lds_bins, nb - c0);  // bins of this turn
+        if (sweep == 0) {
+          for (int b = threadIdx.x; b < cn; b += PRE_BLOCK) s_cur[b] = 0u;
+          __syncthreads();
+        } else if (nb > lds_bins) {
+          for (int b = threadIdx.x; b < cn; b += PRE_BLOCK) s_cur[b] = row[c0 + b];
+          __syncthreads();
+        }
+        for (uint32_t u = threadIdx.x; u < units; u += PRE_BLOCK) {
+          const int o = owner_of(s_first, nrec, u);
+          const Staged &t = s_rec[o];
+          const int by = (t.ty0 >> shift) + (int)(u - s_first[o]);
+          uint32_t rows[BIN_MAX];
+#pragma unroll
+          for (int r = 0; r < BIN_MAX; ++r) {
+            const int ty = (by << shift) + r;
+            rows[r] = 0u;
+            if (r < S && ty >= (int)t.ty0 && ty <= (int)t.ty1) {
+              const uint32_t at = s_rowat[o] + (uint32_t)(ty - (int)t.ty0);
+              rows[r] = at < (uint32_t)ROW_CACHE ? s_rows[at] : row_range(t, cull, ty);
+            }
+          }
+          for (int bx = t.tx0 >> shift; bx <= t.tx1 >> shift; ++bx) {
+            const int b = by * vi.BX + bx - c0;
+            if (b < 0 || b >= cn) continue;
+            const uint32_t m = unit_mask(rows, bx, shift);
+            if (m == 0u) continue;
+            const uint32_t p = atomicAdd(&s_cur[b], 1u);
+            if (sweep == 1) ws.entries[s_base + p] = Entry{t.key, t.rec, m};
+          }
+        }
+        __syncthreads();
+        if (sweep == 0) {
+          for (int b0 = 0; b0 < cn; b0 += PRE_BLOCK) {
+            const int b = b0 + (int)threadIdx.x;
+            uint32_t total;
+            const uint32_t pre = block_exclusive_scan<PRE_BLOCK>(b < cn ? s_cur[b] : 0u, s_w, total) + carry;
+            if (b < cn) {
+              s_cur[b] = pre;
+              row[c0 + b] = pre;
+            }
+            carry += total;
+          }
+          __syncthreads();
+        }
+      }
+      if (sweep == 0) {
+        if (threadIdx.x == 0) {
+          row[nb] = carry;
+          uint32_t base = NO_BASE;
+          if (carry > 0u) {
+            const unsigned long long at =
+                atomicAdd(reinterpret_cast<unsigned long long *>(ws.hdr + HDR_ENTRIES), (unsigned long long)carry);
+            if (at + carry <= cap) base = (uint32_t)at;
+          }
+          ws.block_base[group] = base;
+          s_base = base;
+        }
+        __syncthreads();
+        if (s_base == NO_BASE) break;
+      }
+    }
+    __syncthreads();  // the next batch takes the staging
+  }
+  for (int o = 32; o > 0; o >>= 1) pairs += __shfl_xor(pairs, o);
+  if ((threadIdx.x & 63) == 0) s_pairs[wave] = pairs;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NW; ++w) pairs += s_pairs[w];
+    ws.block_pairs[blockIdx.x] = pairs;
+  }
+}
+
+void launch_preprocess(const Plan &p, const gsr_gaussians &g, const gsr_camera *cams, const ViewInfo *views,
+                       const gsr_config &cfg, const Workspace &ws, bool clear_grad2d, hipStream_t s) {
+  PreConsts pc{cfg.z_near, cfg.lowpass, cfg.cutoff_sigma, cfg.flags, cfg.fov_guard, cfg.alpha_min,
+               cfg.alpha_min > 0.f ? 1.0 / (double)cfg.alpha_min : 0.0, clear_grad2d ? 1 : 0};
+  if (g.n > 0)
+    hipLaunchKernelGGL(g.sh ? k_preprocess<true> : k_preprocess<false>,
+                       dim3((unsigned)(p.blocks_per_view * p.n_views)), dim3(PRE_BLOCK), (size_t)4 * p.lds_bins, s, g,
+                       cams, views, pc, ws, p.blocks_per_view, p.pre_rounds, p.lds_bins,
+                       (unsigned long long)p.capacity);
 }
 
 // Reliable-Gaussian selection (Eq. 12): compare each centre's camera depth

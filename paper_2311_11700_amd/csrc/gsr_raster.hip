@@ -105,10 +105,9 @@ struct FwdState {
 // Depth of list entry pos of the tile, from the staged batch that starts at
 // entry lo when it holds pos, else from the record.
 __device__ __forceinline__ float entry_depth(int pos, int lo, const Staged *s_rec, const TileInfo &ti,
-                                            const uint32_t *__restrict__ ids, const float4 *__restrict__ recC,
-                                            uint32_t id_mask) {
+                                            const uint32_t *__restrict__ ids, const float4 *__restrict__ recC) {
   if (pos >= lo) return s_rec[pos - lo].geo.w;
-  return recC[ids[ti.range.x + pos] & id_mask].w;
+  return recC[ids[ti.range.x + pos]].w;
 }
 
 // With COUNT, the walk also adds its work to counts (wave totals, once per
@@ -141,7 +140,7 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
     if (__syncthreads_and(amin == A_STOPPED)) break;
     const int pos = base + threadIdx.x;
     if ((int)threadIdx.x < NB && pos < ti.range.y) {
-      const uint32_t id = next_id & rc.id_mask;
+      const uint32_t id = next_id;
       if (s_id) s_id[threadIdx.x] = id;
       s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, recA, recB, recC);
       if (pos + NB < ti.range.y) next_id = ids[pos + NB];
@@ -184,7 +183,7 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
   if (staged_lo) *staged_lo = lo_last;
   // The reference depth: the last blended entry's, read once per pixel (an
   // entry was blended, so a batch was staged).
-  if (st.last > 0) st.zr = entry_depth(st.last - 1, lo_last, s_rec, ti, ids, recC, rc.id_mask);
+  if (st.last > 0) st.zr = entry_depth(st.last - 1, lo_last, s_rec, ti, ids, recC);
   if (COUNT && __lane_id() == 0 && nev_w) {
     atomicAdd(counts + 1, (unsigned long long)nev_w);
     atomicAdd(counts + 2, (unsigned long long)nbl_w);
@@ -413,7 +412,7 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
     } else {
       staged_lo = -1;
       if ((int)threadIdx.x < cnt) {
-        const uint32_t id = (next_lo == lo ? next_id : ids[ti.range.x + lo + threadIdx.x]) & rc.id_mask;
+        const uint32_t id = next_lo == lo ? next_id : ids[ti.range.x + lo + threadIdx.x];
         s_id[threadIdx.x] = id;
         s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, recA, recB, recC);
       }
@@ -546,13 +545,9 @@ struct RasterArgs {
   RenderConsts rc;
 };
 
-// Raster arguments of a workspace: the sorted pair words and the mask that
-// extracts a record id from them.
 static RasterArgs raster_args(const Workspace &ws, const ViewInfo *views, const int32_t *tile_view,
-                              const gsr_gaussians &g, RenderConsts rc) {
-  rc.id_mask = ws.id_mask;
-  const uint32_t *ids = ws.pack_shift ? ws.pkeys[ws.psorted] : ws.pvals[ws.psorted];
-  return RasterArgs{ws.recA, ws.recB, ws.recC, ids, ws.ranges, views, tile_view, g.n, rc};
+                              const gsr_gaussians &g, const RenderConsts &rc) {
+  return RasterArgs{ws.recA, ws.recB, ws.recC, ws.ids, ws.ranges, views, tile_view, g.n, rc};
 }
 
 // Per-pixel forward state that a separate backward reads (the unfused
@@ -625,7 +620,8 @@ __device__ __forceinline__ float sgnf(float x) { return (float)((x > 0.f) - (x <
 // order, or in the longest-first order of `queue`); per tile run the
 // forward blend, the L1 loss gradient of every pixel, and the backward walk
 // without leaving the block (per-pixel state stays in registers).  Each
-// tile's duration goes to tile_cost, the next step's longest-first order.
+// tile's duration goes to tile_cost, the next step's longest-first order, and
+// its loss to tile_loss (summed in tile order at the end of the step).
 template <int NB>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_render_fused(RasterArgs a, uint32_t *__restrict__ hdr,
                                                         const uint32_t *__restrict__ queue, int total_tiles,
@@ -633,7 +629,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                                                         const float *__restrict__ t_depth,
                                                         const uint8_t *__restrict__ pmask, float w_rgb,
                                                         float w_depth, const float *__restrict__ loss_cap,
-                                                        gsr_images out, float *__restrict__ loss,
+                                                        gsr_images out, float *__restrict__ tile_loss,
                                                         double *__restrict__ grad2d, PixelState ps,
                                                         uint32_t *__restrict__ tile_cost) {
   __shared__ Staged s_rec[NB];
@@ -710,8 +706,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       if ((threadIdx.x & 63) == 0) s_loss[threadIdx.x >> 6] = ls;
       tile_backward<false>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id, &s_max,
                            s_mA, staged_lo, w_rgb, w_depth);
-      if (threadIdx.x == 0 && loss) atomicAdd(loss, (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]));
       if (threadIdx.x == 0) {
+        tile_loss[tile] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
         const uint64_t d = wall_clock64() - clk0;
         tile_cost[tile] = d < 0xFFFFFFFFull ? (uint32_t)d : 0xFFFFFFFFu;
         if (blockIdx.x == 0) hdr[HDR_COSTS] = 1u;
@@ -795,7 +791,7 @@ void launch_render_backward(const Plan &p, const Workspace &ws, const ViewInfo *
 void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *views,
                          const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
                          const float *t_rgb, const float *t_depth, const uint8_t *pmask, float w_rgb,
-                         float w_depth, const float *loss_cap, const gsr_images *out, float *loss,
+                         float w_depth, const float *loss_cap, const gsr_images *out,
                          const Tuning &tun, int num_cus, hipStream_t s) {
   const RasterArgs a = raster_args(ws, views, tile_view, g, rc);
   gsr_images o{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -808,7 +804,7 @@ void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *vie
   const uint32_t *queue = tun.lpt_order ? ws.queue : nullptr;
 #define GSR_LAUNCH_FUSED(NB_)                                                                                  \
   hipLaunchKernelGGL(k_render_fused<NB_>, dim3(grid), dim3(BLOCK), 0, s, a, ws.hdr, queue, p.total_tiles,            \
-                     tun.tiles_per_pop, t_rgb, t_depth, pmask, w_rgb, w_depth, loss_cap, o, loss, ws.grad2d, ps,      \
+                     tun.tiles_per_pop, t_rgb, t_depth, pmask, w_rgb, w_depth, loss_cap, o, ws.tile_loss, ws.grad2d, ps,      \
                      ws.tile_cost)
   switch (tun.batch) {
     case 64: GSR_LAUNCH_FUSED(64); break;
