@@ -169,7 +169,8 @@ const char *gsr_status_string(gsr_status s);
 const char *gsr_last_error(const gsr_ctx *ctx);
 
 /* Create a context on HIP device `device` (owns a few KB of device memory for
- * the view table and a pinned host word; no other state).  The first call on
+ * the view table and, after a plan with a view of more than 32768 pixels, 24 KB
+ * per view for gsr_loss_median, and a pinned host word; no other state).  The first call on
  * a device also resolves the address of that device's static scratch (see
  * gsr_render_l1_fused_noalloc). */
 gsr_status gsr_create(int device, gsr_ctx **out);
@@ -326,8 +327,10 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
  * +inf when m = 0.  px_loss (DEVICE float [sum HW], e.g. gsr_images.loss of
  * a fused step) is compared as non-negative floats: negative values and -0
  * count as 0, NaN above +inf.  The selection is exact (radix select on the
- * float bits, one block per view).  cap_out is DEVICE float [n_views], the
- * loss_cap argument of the next step.  Asynchronous. */
+ * float bits).  cap_out is DEVICE float [n_views], the loss_cap argument of
+ * the next step.  Asynchronous; calls on several streams of one context take
+ * turns where a view has more than 32768 pixels (they share counters of the
+ * context, which a captured call does not use). */
 gsr_status gsr_loss_median(gsr_ctx *ctx, const float *px_loss, const uint8_t *pixel_mask, float factor,
                            float *cap_out, gsr_stream stream);
 

@@ -27,6 +27,12 @@ struct gsr_ctx {
   hipGraphExec_t gexec = nullptr;
   const void *last_forward_ws = nullptr;
   int64_t fwd_generation = 0;  // successful gsr_render_forward calls on this context
+  // Counters of gsr_loss_median, allocated by gsr_plan for plans with a large
+  // view.  Every call waits for the event of the one before, so calls on
+  // several streams take turns.
+  uint32_t *median_dev = nullptr;
+  hipEvent_t median_done = nullptr;
+  int64_t largest_view = 0;
   void *scratch = nullptr;     // device address of this device's static scratch (gsr_render_l1_fused_noalloc)
   // stage timing
   bool profiling = false;
@@ -292,6 +298,8 @@ void gsr_destroy(gsr_ctx *ctx) {
   if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
   if (ctx->views_dev) (void)hipFree(ctx->views_dev);
   if (ctx->tile_view_dev) (void)hipFree(ctx->tile_view_dev);
+  if (ctx->median_dev) (void)hipFree(ctx->median_dev);
+  if (ctx->median_done) (void)hipEventDestroy(ctx->median_done);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
   delete ctx;
@@ -388,9 +396,13 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   if (st != GSR_OK) return st;
   if (ctx->views_dev) (void)hipFree(ctx->views_dev);
   if (ctx->tile_view_dev) (void)hipFree(ctx->tile_view_dev);
+  if (ctx->median_dev) (void)hipFree(ctx->median_dev);
   ctx->views_dev = nullptr;
   ctx->tile_view_dev = nullptr;
+  ctx->median_dev = nullptr;
   ctx->planned = false;
+  int64_t largest_view = 0;
+  for (const ViewInfo &vi : views) largest_view = std::max<int64_t>(largest_view, (int64_t)vi.W * vi.H);
   std::vector<int32_t> tv(tiles + bins);
   for (int v = 0; v < n_views; ++v) {
     for (int64_t t = 0; t < (int64_t)views[v].TX * views[v].TY; ++t) tv[views[v].tile_off + t] = v;
@@ -400,7 +412,15 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   if (st == GSR_OK) st = hip_check(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->tile_view_dev), sizeof(int32_t) * tv.size()), "hipMalloc(tile_view)");
   if (st == GSR_OK) st = hip_check(ctx, hipMemcpy(ctx->views_dev, views.data(), sizeof(ViewInfo) * n_views, hipMemcpyHostToDevice), "hipMemcpy(views)");
   if (st == GSR_OK) st = hip_check(ctx, hipMemcpy(ctx->tile_view_dev, tv.data(), sizeof(int32_t) * tv.size(), hipMemcpyHostToDevice), "hipMemcpy(tile_view)");
+  if (st == GSR_OK && median_wants_scratch(largest_view)) {
+    const size_t bytes = median_scratch_bytes(n_views);
+    st = hip_check(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->median_dev), bytes), "hipMalloc(median)");
+    if (st == GSR_OK) st = hip_check(ctx, hipMemset(ctx->median_dev, 0, bytes), "hipMemset(median)");
+    if (st == GSR_OK && !ctx->median_done)
+      st = hip_check(ctx, hipEventCreateWithFlags(&ctx->median_done, hipEventDisableTiming), "hipEventCreate");
+  }
   if (st != GSR_OK) return st;
+  ctx->largest_view = largest_view;
   ctx->plan = p;
   ctx->views_host = views;
   ctx->planned = true;
@@ -483,8 +503,25 @@ gsr_status gsr_loss_median(gsr_ctx *ctx, const float *px_loss, const uint8_t *pi
   if (!ctx->planned) return fail(ctx, GSR_E_STATE, "gsr_plan() has not been called");
   if (!px_loss || !cap_out) return fail(ctx, GSR_E_INVALID, "gsr_loss_median: null argument");
   if (!(factor >= 0.f)) return fail(ctx, GSR_E_INVALID, "gsr_loss_median: factor must be >= 0");
-  launch_loss_median(ctx->plan, ctx->views_dev, px_loss, pixel_mask, factor, cap_out,
-                     static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  // A captured call keeps clear of the shared counters: its replays may run
+  // beside other calls.
+  uint32_t *scratch = ctx->median_dev;
+  if (scratch) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    gsr_status st = hip_check(ctx, hipStreamIsCapturing(s, &capturing), "hipStreamIsCapturing");
+    if (st != GSR_OK) return st;
+    if (capturing != hipStreamCaptureStatusNone) scratch = nullptr;
+  }
+  if (scratch) {
+    gsr_status st = hip_check(ctx, hipStreamWaitEvent(s, ctx->median_done, 0), "hipStreamWaitEvent");
+    if (st != GSR_OK) return st;
+  }
+  launch_loss_median(ctx->plan, ctx->views_dev, ctx->largest_view, px_loss, pixel_mask, factor, cap_out, scratch, s);
+  if (scratch) {
+    gsr_status st = hip_check(ctx, hipEventRecord(ctx->median_done, s), "hipEventRecord");
+    if (st != GSR_OK) return st;
+  }
   return last_launch(ctx, "gsr_loss_median launch");
 }
 

@@ -369,9 +369,13 @@ void launch_work_counts(const Plan &p, const Workspace &ws, const ViewInfo *view
 void launch_l1(const Plan &p, const ViewInfo *views, const float *rgb, const float *depth,
                const float *t_rgb, const float *t_depth, const uint8_t *pmask, float w_rgb,
                float w_depth, const float *loss_cap, float *g_rgb, float *g_depth, float *loss, hipStream_t s);
-// Loss cap: factor x lower median of each view's per-pixel loss.
-void launch_loss_median(const Plan &p, const ViewInfo *views, const float *px_loss, const uint8_t *pmask,
-                        float factor, float *cap_out, hipStream_t s);
+// Loss cap: factor x lower median of each view's per-pixel loss.  With scratch
+// (median_scratch_bytes, zero before the first call; every call leaves it
+// zero) many blocks share a view; without, one block a view.
+size_t median_scratch_bytes(int n_views);
+bool median_wants_scratch(int64_t largest_view);
+void launch_loss_median(const Plan &p, const ViewInfo *views, int64_t largest_view, const float *px_loss,
+                        const uint8_t *pmask, float factor, float *cap_out, uint32_t *scratch, hipStream_t s);
 
 // Pose parameterisations (one thread per view).
 void launch_pose_apply(int n, const float *xi, const gsr_camera *cin, gsr_camera *cout, hipStream_t s);
