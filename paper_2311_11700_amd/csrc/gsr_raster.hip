@@ -19,6 +19,9 @@
 namespace gsr {
 
 constexpr int BATCH = 192;  // staged records per forward round (<= BLOCK; the fused kernel's is tunable)
+constexpr int FGROUP = 4;   // list entries that the forward walk takes at a time
+constexpr int BGROUP = 8;   // and the backward walk (one contraction), in two halves
+constexpr int BHALF = 4;
 constexpr float NEG_HALF_LOG2E = -0.72134752044448170368f;  // -log2(e) / 2
 constexpr float LN2 = 0.69314718055994530942f;
 // Alpha threshold of a pixel that has stopped (or lies outside the image):
@@ -29,7 +32,7 @@ constexpr float A_STOPPED = 2.f;
 struct Staged {
   float4 geo;  // (u_rel, v_rel, opacity, depth)
   float4 con;  // (a'', 2 b'', c'', unused)
-  float4 col;  // (r, g, b, unused)
+  float4 col;  // (r, g, b, depth)
 };
 
 struct TileInfo {
@@ -79,19 +82,69 @@ __device__ __forceinline__ Staged stage_record(uint32_t id, float x0, float y0, 
   // the remaining bits.
   s.geo = make_float4((A.x - x0) + A.y, (A.z - y0) + A.w, Bc.w, C.w);
   s.con = make_float4(NEG_HALF_LOG2E * Bc.x, 2.f * (NEG_HALF_LOG2E * Bc.y), NEG_HALF_LOG2E * Bc.z, 0.f);
-  s.col = make_float4(C.x, C.y, C.z, 0.f);
+  s.col = C;
   return s;
+}
+
+// Staging of list entry t of a batch of cnt: the walks take whole groups, so
+// the slots up to the next multiple of BGROUP hold records of opacity 0.
+__device__ __forceinline__ int padded(int cnt) { return (cnt + BGROUP - 1) & ~(BGROUP - 1); }
+
+__device__ __forceinline__ Staged empty_record() {
+  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+  return Staged{z, z, z};
 }
 
 // alpha of a staged Gaussian at pixel offset (dx, dy) = centre - pixel;
 // oG >= 0, so the clamp to [0, alpha_max] is min(oG, alpha_max).
-__device__ __forceinline__ float splat_alpha(const float4 &geo, const float4 &con, float dx, float dy,
-                                             float alpha_max, float &G, float &oG) {
+__device__ __forceinline__ float splat_alpha(const float4 &geo, const float3 &con, float dx, float dy,
+                                             float alpha_max, float &oG) {
   const float t = __fmaf_rn(con.x, dx, con.y * dy);
   const float P = __fmaf_rn(con.z * dy, dy, dx * t);
-  G = __builtin_amdgcn_exp2f(P);
-  oG = geo.z * G;
+  oG = geo.z * __builtin_amdgcn_exp2f(P);
   return __builtin_amdgcn_fmed3f(oG, 0.f, alpha_max);
+}
+
+// Geometry of GROUP consecutive staged records, read one group ahead of its
+// use: the compiler places the reads next to the use, so a scheduling barrier
+// follows them.
+template <int G>
+struct GroupGeo {
+  float4 geo[G];
+  float3 con[G];
+  __device__ __forceinline__ void load(const Staged *rec) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      geo[u] = rec[u].geo;
+      con[u] = *reinterpret_cast<const float3 *>(&rec[u].con);
+    }
+  }
+};
+
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// v_mfma_f32_4x4x1_16b_f32: lane l = 4 b + j supplies a (row j) and b (column
+// j) of block b; D[i] of the lane is row i, column j: D[i] += a of lane
+// 4 b + i * b of lane l.  (All lanes take part, whatever the EXEC mask.)
+__device__ __forceinline__ float4v outer4(float a, float b, float4v D) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, D, 0, 0, 0);
+}
+
+// Element (j, i) <- (i, j) of the 4x4 matrices that four neighbouring lanes
+// hold (D[i] of lane 4 b + j).
+__device__ __forceinline__ float4v transpose4(float4v D) {
+  const int i = __lane_id() & 3;
+  float4v r;
+#define GSR_ROW(J)                                                                                              \
+  {                                                                                                             \
+    float v[4];                                                                                                 \
+    for (int k = 0; k < 4; ++k)                                                                                 \
+      v[k] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(D[k]), (J) * 0x55, 0xf, 0xf, true));        \
+    r[J] = i == 0 ? v[0] : (i == 1 ? v[1] : (i == 2 ? v[2] : v[3]));                                            \
+  }
+  GSR_ROW(0) GSR_ROW(1) GSR_ROW(2) GSR_ROW(3)
+#undef GSR_ROW
+  return r;
 }
 
 // ------------------------------------------------------------------ forward
@@ -122,7 +175,12 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
                                              Staged *s_rec, FwdState &st, unsigned long long *counts,
                                              uint32_t *s_id = nullptr, int *staged_lo = nullptr) {
   st.T = 1.f;
-  st.C0 = st.C1 = st.C2 = st.D = 0.f;
+  // Colour and depth, transposed among four lanes: lane 4 b + j holds channel
+  // j (r, g, b, depth) of the four pixels 4 b + i (one matrix instruction adds
+  // an entry where four FMAs would).
+  float4v C = {0.f, 0.f, 0.f, 0.f};
+  const float *s_col = reinterpret_cast<const float *>(&s_rec[0].col) + (threadIdx.x & 3);
+  constexpr int COL_STRIDE = sizeof(Staged) / sizeof(float);
   st.last = 0;
   st.zr = 0.f;
   // The pixel's alpha threshold; A_STOPPED once it has stopped (or outside
@@ -139,45 +197,89 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
   for (int base = ti.range.x; base < ti.range.y; base += NB) {
     if (__syncthreads_and(amin == A_STOPPED)) break;
     const int pos = base + threadIdx.x;
-    if ((int)threadIdx.x < NB && pos < ti.range.y) {
+    const int cnt = min(NB, ti.range.y - base);
+    if ((int)threadIdx.x < cnt) {
       const uint32_t id = next_id;
       if (s_id) s_id[threadIdx.x] = id;
       s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, recA, recB, recC);
       if (pos + NB < ti.range.y) next_id = ids[pos + NB];
+    } else if ((int)threadIdx.x < padded(cnt)) {
+      s_rec[threadIdx.x] = empty_record();
     }
-    lo_last = base - ti.range.x;
+    const int first = base - ti.range.x;
+    lo_last = first;
     __syncthreads();
-    // Branch-free walk: every lane evaluates every entry and keeps or drops
-    // the result with selects; the wave leaves the batch once all of its
-    // pixels have stopped.  `live` (wave-uniform) holds the lanes still
-    // blending.
-    const int cnt = min(NB, ti.range.y - base);
+    // Every lane evaluates every entry and keeps or drops the result with
+    // selects.  `live` (wave-uniform) holds the lanes still blending; it
+    // changes only where a pixel stops, and the wave leaves the batch when it
+    // is empty.
     uint64_t live = __builtin_amdgcn_ballot_w64(amin != A_STOPPED);
-    for (int k = 0; k < cnt && live; ++k) {
-      if (COUNT) nev_w += (uint32_t)__popcll(live);
-      const float4 geo = s_rec[k].geo;
-      const float4 con = s_rec[k].con;
-      const float dx = geo.x - lx, dy = geo.y - ly;
-      float G, oG;
-      const float alpha = splat_alpha(geo, con, dx, dy, rc.alpha_max, G, oG);
-      const bool acc = alpha >= amin;
-      // Blend weight alpha T and the transmittance behind, T - alpha T.
-      const float wa = alpha * st.T;
-      const float Tn = st.T - wa;
-      const bool stop = acc && Tn < rc.T_min;
-      const bool blend = acc && !stop;
-      if (COUNT) nbl_w += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(blend));
-      amin = stop ? A_STOPPED : amin;
-      // Nearly every entry blends in some lane: no branch around the update.
-      const float4 col = s_rec[k].col;
-      const float w = blend ? wa : 0.f;
-      st.C0 = __fmaf_rn(w, col.x, st.C0);
-      st.C1 = __fmaf_rn(w, col.y, st.C1);
-      st.C2 = __fmaf_rn(w, col.z, st.C2);
-      st.D = __fmaf_rn(w, geo.w, st.D);
-      st.T = blend ? Tn : st.T;
-      st.last = blend ? base - ti.range.x + k + 1 : st.last;
-      live = __builtin_amdgcn_ballot_w64(amin != A_STOPPED);
+    GroupGeo<FGROUP> g;
+    g.load(s_rec);
+    for (int k = 0; k < cnt && live; k += FGROUP) {
+      float w[FGROUP], T[FGROUP], alpha[FGROUP], col[FGROUP];
+      bool acc[FGROUP];
+#pragma unroll
+      for (int u = 0; u < FGROUP; ++u) col[u] = s_col[(k + u) * COL_STRIDE];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < FGROUP; ++u) {
+        float oG;
+        alpha[u] = splat_alpha(g.geo[u], g.con[u], g.geo[u].x - lx, g.geo[u].y - ly, rc.alpha_max, oG);
+      }
+      g.load(s_rec + min(k + FGROUP, NB - FGROUP));
+      __builtin_amdgcn_sched_barrier(0);
+      float Tc = st.T;
+      int rel = -1;  // last entry of the group that blends
+#pragma unroll
+      for (int u = 0; u < FGROUP; ++u) {
+        acc[u] = alpha[u] >= amin;
+        // Blend weight alpha T and the transmittance behind, T - alpha T.
+        w[u] = (acc[u] ? alpha[u] : 0.f) * Tc;
+        Tc = Tc - w[u];
+        T[u] = Tc;
+        rel = acc[u] ? u : rel;
+      }
+      // T never grows: no pixel stops in the group unless its last value is
+      // below T_min (that of a stopped pixel is not: it keeps the value that
+      // it had in front of the entry that stopped it).
+      const uint64_t stop = __builtin_amdgcn_ballot_w64(Tc < rc.T_min);
+      uint64_t ran[FGROUP], blends[FGROUP];  // (counted only)
+      if (COUNT) {
+#pragma unroll
+        for (int u = 0; u < FGROUP; ++u) {
+          ran[u] = live;
+          blends[u] = __builtin_amdgcn_ballot_w64(acc[u]);
+        }
+      }
+      if (stop) {
+        bool run = true;
+        Tc = st.T;
+        rel = -1;
+#pragma unroll
+        for (int u = 0; u < FGROUP; ++u) {
+          const bool a = alpha[u] >= amin;
+          if (COUNT) ran[u] = __builtin_amdgcn_ballot_w64(run) & live;
+          run = run && !(a && T[u] < rc.T_min);
+          w[u] = run ? w[u] : 0.f;
+          Tc = run ? T[u] : Tc;
+          rel = a && run ? u : rel;
+          if (COUNT) blends[u] = __builtin_amdgcn_ballot_w64(a && run);
+        }
+        amin = run ? amin : A_STOPPED;
+        live = __builtin_amdgcn_ballot_w64(amin != A_STOPPED);
+      }
+      st.T = Tc;
+      // (an entry behind the list's end has alpha 0: an alpha_min of 0 accepts it)
+      st.last = rel >= 0 ? min(first + k + 1 + rel, first + cnt) : st.last;
+#pragma unroll
+      for (int u = 0; u < FGROUP; ++u) {
+        if (COUNT && k + u < cnt) {
+          nev_w += (uint32_t)__popcll(ran[u]);
+          nbl_w += (uint32_t)__popcll(blends[u]);
+        }
+        C = outer4(w[u], col[u], C);
+      }
     }
   }
   if (staged_lo) *staged_lo = lo_last;
@@ -188,9 +290,11 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
     atomicAdd(counts + 1, (unsigned long long)nev_w);
     atomicAdd(counts + 2, (unsigned long long)nbl_w);
   }
-  st.C0 = __fmaf_rn(st.T, rc.bg[0], st.C0);
-  st.C1 = __fmaf_rn(st.T, rc.bg[1], st.C1);
-  st.C2 = __fmaf_rn(st.T, rc.bg[2], st.C2);
+  C = transpose4(C);
+  st.C0 = __fmaf_rn(st.T, rc.bg[0], C[0]);
+  st.C1 = __fmaf_rn(st.T, rc.bg[1], C[1]);
+  st.C2 = __fmaf_rn(st.T, rc.bg[2], C[2]);
+  st.D = C[3];
 }
 
 // ----------------------------------------------------------------- backward
@@ -204,18 +308,15 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
 // per-pixel constants: the matrix [dLdP; w] (entries x pixels) times the
 // matrix [1, xc, yc, xc^2, xc yc, yc^2, gC_r, gC_g, gC_b, gD] (pixels x 10),
 // a dense contraction over the pixels.  Each wavefront collects dLdP and w of
-// 8 entries (16 rows) for its 64 pixels in LDS and contracts them on the
-// bf16 matrix cores (v_mfma_f32_16x16x32_bf16, each value split into two
-// bf16 halves: K = 128 slots in 4 steps); the four
-// wavefronts add their 16x16 products into the block's per-entry sums.
+// BGROUP = 8 entries (16 rows) for its 64 pixels in LDS and contracts them on
+// the bf16 matrix cores (v_mfma_f32_16x16x32_bf16, 4 steps); the four
+// wavefronts' sums are added at the flush.
 
 constexpr int SUB = 64;                   // entries per backward sub-batch
-constexpr int MA_ROWS = 16;               // 8 entries x (dLdP, w)
-constexpr int MA_STRIDE = 64 + 4;         // 32-bit words (bf16 pairs) per row (padding spreads LDS banks)
+constexpr int MA_ROWS = 2 * BGROUP;       // high and low parts of (dLdP, w) of a group's entries
+constexpr int MA_STRIDE = 64 + 4;         // words (pixels, bf16 pairs) per row (padding spreads LDS banks)
 constexpr int MA_WAVE = MA_ROWS * MA_STRIDE;
 constexpr int NMOM = 10;                  // per-entry sums kept in LDS
-
-typedef float float4v __attribute__((ext_vector_type(4)));
 
 struct BwdIn {
   float T;         // final transmittance
@@ -234,71 +335,161 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Contract the wave's collected rows (rows 2q = dLdP, 2q+1 = w of entry q)
-// with the per-pixel constants on the bf16 matrix cores
-// (v_mfma_f32_16x16x32_bf16): every per-pixel value x of the A rows is held
-// as a pair (h, l) of bf16, h = x with the low 16 bits of its float32 cleared
-// and l = x - h rounded to bf16 (h + l carries 16 significant bits, a
-// relative error below 2^-16), and the pair occupies two consecutive K slots
-// whose B entries both hold the pixel's column value (exact in bf16 for the
-// moment polynomials of half-integer coordinates, at most 8 significant
-// bits, and for residual signs).  K = 128 slots (64 pixels x 2) in 4 steps;
-// step j covers the wave's pixel row j.  Lane l supplies A[l % 16][k] and
-// B[k][l % 16] for the 8 slots k of its group l / 16; D[i][l % 16] lands in
-// register i % 4 of lane 16 (i / 4) + l % 16.  The accumulation is FP32.
-// The result is consumed (mfma_consume) only at the next group, so the
-// matrix-core chain runs while the wavefront walks on.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t split_bf16(float x) {
-  const float h = __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
-  const float2v p = {h, x - h};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2));
+// dLdP and w of one entry at this lane's pixel, each as the sum of two bf16
+// (h = x rounded, l = x - h rounded: 16 significant bits, a relative error of
+// at most 2^-17): words (h, h) and (l, l) of the pair.  x - h is exact.
+__device__ __forceinline__ void split_pair(float dLdP, float w, uint32_t &hi, uint32_t &lo) {
+  const float2v x = {dLdP, w};
+  const bf16x2 h = __builtin_convertvector(x, bf16x2);
+  hi = __builtin_bit_cast(uint32_t, h);
+  const float2v r = {dLdP - __uint_as_float(hi << 16), w - __uint_as_float(hi & 0xFFFF0000u)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
 }
 
-// With BLO the B values are not exact in bf16: Bl holds the low halves
-// (B - Bb rounded to bf16) and a second set of steps adds A Bl, so that the
-// products keep about 16 significant bits on both sides.
+// Contract the wave's collected rows (rows 2 e and 2 e + 1: the high and low
+// words of entry e) with the per-pixel constants B.  A pixel's word is two
+// consecutive K slots, dLdP and w: the B entries of the first slot are the
+// moment columns, of the second the upstream columns, 0 in the others.  B is
+// exact in bf16 for the moment polynomials of half-integer coordinates (at
+// most 8 significant bits) and for residual signs; with BLO it is not, and Bl
+// holds the low halves (B - Bb rounded to bf16) for a second set of steps.
+// K = 128 slots (64 pixels x 2) in 4 steps; step j covers the wave's pixel row
+// j.  Lane l supplies A[l % 16][k] and B[k][l % 16] for the 8 slots k of its
+// group l / 16; D[i][l % 16] lands in register i % 4 of lane 16 (i / 4) +
+// l % 16.  The accumulation is FP32.  (In FP32, v_mfma_f32_16x16x4_f32, the
+// 16 steps of a group run on the vector units and cost more than the split.)
 template <bool BLO>
-__device__ __forceinline__ float4v mfma_issue_split(const float *mA, const bf16x8 Bb[4], const bf16x8 *Bl) {
+__device__ __forceinline__ float4v contract(const uint32_t *mA, const bf16x8 Bb[4], const bf16x8 *Bl) {
   const int lane = __lane_id();
-  const int r = lane & 15, g = lane >> 4;
   wave_lds_sync();
   // Lane (g, r): row r, words (pixels) 16 j + 4 g .. + 3 of step j.
-  const uint4 *src = reinterpret_cast<const uint4 *>(mA + r * MA_STRIDE + 4 * g);
-  const uint4 a0 = src[0], a1 = src[4], a2 = src[8], a3 = src[12];
+  const uint4 *src = reinterpret_cast<const uint4 *>(mA + (lane & 15) * MA_STRIDE + 4 * (lane >> 4));
+  bf16x8 a[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) a[j] = __builtin_bit_cast(bf16x8, src[4 * j]);
+  // In registers: the next group may rewrite the rows.
+  wave_lds_sync();
   float4v D = {0.f, 0.f, 0.f, 0.f};
-  D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a0), Bb[0], D, 0, 0, 0);
-  D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a1), Bb[1], D, 0, 0, 0);
-  D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a2), Bb[2], D, 0, 0, 0);
-  D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a3), Bb[3], D, 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], Bb[j], D, 0, 0, 0);
   if constexpr (BLO) {
-    D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a0), Bl[0], D, 0, 0, 0);
-    D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a1), Bl[1], D, 0, 0, 0);
-    D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a2), Bl[2], D, 0, 0, 0);
-    D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a3), Bl[3], D, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], Bl[j], D, 0, 0, 0);
   }
   return D;
 }
 
-// Store the useful products of a contraction of nq entries into the
-// wavefront's own per-entry sums s_sum[entry][NMOM] (entry q's slot in byte
-// q of slots; a wavefront meets each entry once per sub-batch, so plain
-// stores suffice and the four wavefronts never contend for an address).
-// Lane (g, col) holds rows 4g..4g+3: entry 2g (dLdP row, w row) and entry
-// 2g+1.  Columns 0-5 are taken from the dLdP rows, 6-9 from the w rows.
-__device__ __forceinline__ void mfma_consume(const float4v &D, int nq, uint64_t slots, float *s_sum) {
+// Store a group's contraction into the wavefront's own per-entry sums
+// (sum[e][NMOM]; a wavefront meets each entry once, so plain stores suffice).
+// Lane (g, col) holds rows 4g..4g+3: entry 2g (high row, low row) and entry
+// 2g+1.  Bit e of used: some pixel of the wave blended entry e; the sums of
+// the others are 0 (the products are too, unless an upstream gradient is not
+// finite).
+__device__ __forceinline__ void store_sums(const float4v &D, uint32_t used, float *sum) {
   const int lane = __lane_id();
   const int g = lane >> 4;
   const int col = lane & 15;
   if (col < NMOM) {
-    const bool mom = col < 6;
-    const int q0 = 2 * g, q1 = 2 * g + 1;
-    if (q0 < nq) s_sum[(int)((slots >> (8 * q0)) & 255u) * NMOM + col] = mom ? D[0] : D[1];
-    if (q1 < nq) s_sum[(int)((slots >> (8 * q1)) & 255u) * NMOM + col] = mom ? D[2] : D[3];
+    const uint32_t u = used >> (2 * g);
+    sum[(2 * g) * NMOM + col] = (u & 1u) ? D[0] + D[1] : 0.f;
+    sum[(2 * g + 1) * NMOM + col] = (u & 2u) ? D[2] + D[3] : 0.f;
   }
+}
+
+// Maximum over the wavefront of v >= 0, in a scalar register.
+__device__ __forceinline__ int wave_max(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // row_shr:1
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));  // row_shr:2
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));  // row_shr:4
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));  // row_shr:8
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// State of a pixel's backward walk (see tile_backward).
+struct BwdPixel {
+  float T, B;           // transmittance behind the current entry; blend behind it
+  float Kf, zr;
+  float gC0, gC1, gC2, gD;
+  int last;
+  float lx, ly;
+};
+
+// The chain of half a group, back to front: dLdP and w of this lane's pixel go
+// to its rows.  PLAIN: every lane walks every entry of the half, some lane
+// blends each and none has its alpha clamped, which saves the selects.
+template <bool PLAIN>
+__device__ __forceinline__ void backward_half(const float alpha[BHALF], const float oG[BHALF], const float4v &Q,
+                                              int first, const RenderConsts &rc, BwdPixel &px, uint32_t *rows) {
+#pragma unroll
+  for (int u = BHALF - 1; u >= 0; --u) {
+    const bool has = (PLAIN || first + u < px.last) && alpha[u] >= rc.alpha_min;
+    // Lanes without a contribution take alpha = 0, which leaves T and B
+    // unchanged (1 / (1 - 0) is exactly 1) and gives w = dLdP = 0.
+    const float ae = has ? alpha[u] : 0.f;
+    const float rinv = __builtin_amdgcn_rcpf(1.f - ae);
+    const float Tk = px.T * rinv;  // transmittance in front of this Gaussian
+    px.T = Tk;
+    const float w = ae * Tk;
+    const float QB = PLAIN || has ? Q[u] - px.B : 0.f;
+    const float dLda = __fmaf_rn(Tk, QB, px.Kf * rinv);
+    px.B = __fmaf_rn(ae, QB, px.B);
+    // dL/dP with G = 2^P (the ln 2 and the conic pre-scale are applied at the
+    // flush); dL/d(opacity) = dLdP / o there.  Below the clamp o G is alpha.
+    const float dLdP = PLAIN || oG[u] <= rc.alpha_max ? dLda * ae : 0.f;
+    split_pair(dLdP, w, rows[(2 * u) * MA_STRIDE], rows[(2 * u + 1) * MA_STRIDE]);
+  }
+}
+
+// One group of entries.  slot: its first entry's place in s_rec, first: in the
+// list; g holds the geometry of its upper half, then of the group in front.
+// all: every entry lies below the last contributor of every pixel of the wave.
+// Returns the entries that some pixel of the wave blends.
+__device__ __forceinline__ uint32_t backward_group(const Staged *s_rec, int slot, int first, bool all,
+                                                   const RenderConsts &rc, BwdPixel &px, uint32_t *rows,
+                                                   GroupGeo<BHALF> &g) {
+  static_assert(BHALF == 4, "one outer4 step per channel");
+  uint32_t used = 0u;
+#pragma unroll
+  for (int h = BGROUP / BHALF - 1; h >= 0; --h) {
+    float alpha[BHALF], oG[BHALF];
+    // Q of the half's four entries at this lane's pixel (see tile_backward):
+    // lane 4 b + i supplies the colour of entry i.
+    const float3 col = *reinterpret_cast<const float3 *>(&s_rec[slot + h * BHALF + (threadIdx.x & 3)].col);
+    float4v Q;
+#pragma unroll
+    for (int u = 0; u < BHALF; ++u) Q[u] = px.gD * (g.geo[u].w - px.zr);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = BHALF - 1; u >= 0; --u)
+      alpha[u] = splat_alpha(g.geo[u], g.con[u], g.geo[u].x - px.lx, g.geo[u].y - px.ly, rc.alpha_max, oG[u]);
+    Q = outer4(col.x, px.gC0, Q);
+    Q = outer4(col.y, px.gC1, Q);
+    Q = outer4(col.z, px.gC2, Q);
+    g.load(s_rec + max(slot + (h - 1) * BHALF, 0));
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t u4 = 0u;
+#pragma unroll
+    for (int u = 0; u < BHALF; ++u) u4 |= __builtin_amdgcn_ballot_w64(alpha[u] >= rc.alpha_min) != 0 ? 1u << u : 0u;
+    const bool clamped =
+        __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(oG[0], oG[1]), fmaxf(oG[2], oG[3])) > rc.alpha_max) != 0;
+    if (all && u4 == 15u && !clamped) {
+      backward_half<true>(alpha, oG, Q, first + h * BHALF, rc, px, rows + 2 * h * BHALF * MA_STRIDE);
+    } else {
+      u4 = 0u;
+#pragma unroll
+      for (int u = 0; u < BHALF; ++u)
+        u4 |= __builtin_amdgcn_ballot_w64(first + h * BHALF + u < px.last && alpha[u] >= rc.alpha_min) != 0 ? 1u << u : 0u;
+      backward_half<false>(alpha, oG, Q, first + h * BHALF, rc, px, rows + 2 * h * BHALF * MA_STRIDE);
+    }
+    used |= u4 << (h * BHALF);
+  }
+  return used;
 }
 
 // Walk the tile's list back to front; per entry, dLdP and w of every pixel
@@ -308,7 +499,6 @@ __device__ __forceinline__ void mfma_consume(const float4v &D, int nq, uint64_t 
 // keeps the result independent of the order the tiles finish in).  grad2d
 // fields: (u, v, conic a, b, c, opacity, r, g, b, depth).
 //
-// The per-entry sums run on the bf16 matrix cores (mfma_issue_split).
 // Without BLO (the fused step) the upstream columns are the residual signs
 // in.sC / in.sD and the colour and depth sums are scaled by w_rgb and
 // w_depth at the flush; with BLO (the separate backward, any upstream
@@ -326,14 +516,14 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
   const float lx = (float)(threadIdx.x & (TILE - 1));
   const float ly = (float)(threadIdx.x >> 4);
   const int lane = __lane_id();
-  const int wv = threadIdx.x >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float *mA = s_mA + wv * MA_WAVE;
   float *my_part = s_part + wv * SUB * NMOM;  // this wavefront's per-entry sums
-  if (threadIdx.x == 0) *s_max = 0;
+  const int wmax = wave_max(in.last);
+  const int wmin = INT_MAX - wave_max(INT_MAX - in.last);
+  if (lane == 0) s_max[wv] = wmax;
   __syncthreads();
-  if (in.last > 0) atomicMax(s_max, in.last);
-  __syncthreads();
-  const int maxlast = *s_max;
+  const int maxlast = __builtin_amdgcn_readfirstlane(max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3])));
   if (maxlast == 0) return;
 
   // Per-pixel constants of the contraction, in the B-operand layout,
@@ -342,12 +532,14 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
   bf16x8 Bb[4];
   bf16x8 Bl[BLO ? 4 : 1];
   {
-    // Step j, lane (g, col): elements 2 i and 2 i + 1 hold column col of
-    // pixel x = 4 g + i of the wave's row j (y = 4 wv + j).
+    // Step j, lane (g, col): elements 2 i and 2 i + 1 hold column col of the
+    // moments and of the upstream values of pixel x = 4 g + i of the wave's
+    // row j (y = 4 wv + j).
     mA[0 * MA_STRIDE + lane] = BLO ? in.gC0 : in.sC0;
     mA[1 * MA_STRIDE + lane] = BLO ? in.gC1 : in.sC1;
     mA[2 * MA_STRIDE + lane] = BLO ? in.gC2 : in.sC2;
     mA[3 * MA_STRIDE + lane] = BLO ? in.gD : in.sD;
+    mA[4 * MA_STRIDE + lane] = 0.f;  // (read by the lanes of the other columns)
     wave_lds_sync();
     // Rebuilt per tile from an opaque copy of the lane index: kept out of
     // the tile loop, these tile-invariant values would be held in registers
@@ -355,47 +547,54 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
     int lane_t = lane;
     __asm__ volatile("" : "+v"(lane_t));
     const int col = lane_t & 15, g = lane_t >> 4;
-    const bool up = col >= 6 && col < NMOM;
+    const int row = col >= 6 && col < NMOM ? col - 6 : 4;
+    // Moment columns 1, xc, yc, xc^2, xc yc, yc^2: products fx fy.
+    float fx[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float xc = (float)(4 * g + i) - 7.5f;
+      fx[i] = col == 1 || col == 4 ? xc : (col == 3 ? xc * xc : (col < 6 ? 1.f : 0.f));
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float yc = (float)(4 * wv + j) - 7.5f;
-      const float4 q = *reinterpret_cast<const float4 *>(mA + (up ? col - 6 : 0) * MA_STRIDE + 16 * j + 4 * g);
-      const float qv[4] = {q.x, q.y, q.z, q.w};
+      const float fy = col == 2 || col == 4 ? yc : (col == 5 ? yc * yc : 1.f);
+      const float4v q = *reinterpret_cast<const float4v *>(mA + row * MA_STRIDE + 16 * j + 4 * g);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float xc = (float)(4 * g + i) - 7.5f;
-        // Columns 1, xc, yc, xc^2, xc yc, yc^2, then the upstream values.
-        const float a = col == 1 || col == 3 || col == 4 ? xc : (col == 2 || col == 5 ? yc : 1.f);
-        const float b = col == 3 ? xc : (col == 4 || col == 5 ? yc : 1.f);
-        const float x = up ? qv[i] : (col < 6 ? a * b : 0.f);
-        const __bf16 v = (__bf16)x;
-        Bb[j][2 * i] = v;
-        Bb[j][2 * i + 1] = v;
+        Bb[j][2 * i] = (__bf16)(fx[i] * fy);
+        Bb[j][2 * i + 1] = (__bf16)q[i];
         if constexpr (BLO) {
-          const __bf16 vl = (__bf16)(x - (float)v);
-          Bl[j][2 * i] = vl;
-          Bl[j][2 * i + 1] = vl;
+          Bl[j][2 * i] = (__bf16)0.f;
+          Bl[j][2 * i + 1] = (__bf16)(q[i] - (float)Bb[j][2 * i + 1]);
         }
       }
     }
     wave_lds_sync();
   }
 
-  float T = in.T;
-  const float Tf = in.T;
   // Blend behind the current entry, normalised by the transmittance in front
   // of it, enters dL/dalpha only through the upstream-weighted scalar
-  //   S = gC . aC + gD . aDs,
+  //   B = gC . aC + gD . aDs,
   // (aC: colour behind, starting at the background; aDs: depth behind,
   // relative to the depth zr of the pixel's last contributor), which obeys
-  // the same recurrence S <- S + alpha (Q - S) with Q = gC . c + gD (z - zr).
+  // the same recurrence B <- B + alpha (Q - B) with Q = gC . c + gD (z - zr).
   // With the telescoping identity sum_m alpha_m T_m = 1 - T_f,
-  //   dL/dalpha_k = T_k (Q_k - S_k) + (gD zr - gT) T_f / (1 - alpha_k).
+  //   dL/dalpha_k = T_k (Q_k - B_k) + (gD zr - gT) T_f / (1 - alpha_k).
   // On a surface all depths agree to a few mm, so the shifted terms keep
   // their float32 digits (z_k - aD_k itself would cancel).
-  float S = in.gC0 * rc.bg[0] + in.gC1 * rc.bg[1] + in.gC2 * rc.bg[2];
-  const float zr = in.zr;
-  const float Kf = (in.gD * zr - in.gT) * Tf;
+  BwdPixel px;
+  px.T = in.T;
+  px.B = in.gC0 * rc.bg[0] + in.gC1 * rc.bg[1] + in.gC2 * rc.bg[2];
+  px.Kf = (in.gD * in.zr - in.gT) * in.T;
+  px.zr = in.zr;
+  px.gC0 = in.gC0;
+  px.gC1 = in.gC1;
+  px.gC2 = in.gC2;
+  px.gD = in.gD;
+  px.last = in.last;
+  px.lx = lx;
+  px.ly = ly;
 
   // Sub-batches [b SUB, (b + 1) SUB), walked from the last one that holds
   // an entry below maxlast.  Those inside the forward's last batch (still
@@ -415,71 +614,40 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
         const uint32_t id = next_lo == lo ? next_id : ids[ti.range.x + lo + threadIdx.x];
         s_id[threadIdx.x] = id;
         s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, recA, recB, recC);
+      } else if ((int)threadIdx.x < padded(cnt)) {
+        s_rec[threadIdx.x] = empty_record();
       }
     }
     if (lo >= SUB && !(staged_lo >= 0 && lo - SUB >= staged_lo)) {
       if ((int)threadIdx.x < SUB) next_id = ids[ti.range.x + lo - SUB + threadIdx.x];
       next_lo = lo - SUB;
     }
+    // This wavefront's groups of the sub-batch, from the one that holds the
+    // last contributor of any of its pixels; the entries behind keep zero sums.
+    const int ng = (min(max(wmax - lo, 0), cnt) + BGROUP - 1) / BGROUP;
     {
-      // Entries without a contribution in this wavefront keep zero sums.
       float4 *z = reinterpret_cast<float4 *>(my_part);
-      for (int k = lane; k < SUB * NMOM / 4; k += 64) z[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int k = ng * (BGROUP * NMOM / 4) + lane; k < SUB * NMOM / 4; k += 64) z[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
-    int nq = 0;
-    uint64_t slots = 0;
-    float4v pD = {0.f, 0.f, 0.f, 0.f};  // contraction of the previous group, not yet added
-    int p_nq = 0;
-    uint64_t p_slots = 0;
-    // One step past the batch (k = lo - 1) contracts the last partial group.
-    for (int k = hi - 1; k >= lo - 1; --k) {
-      const int j = k - lo;
-      if (k >= lo) {
-        const float4 geo = s_rec[off + j].geo;
-        const float4 con = s_rec[off + j].con;
-        const float dx = geo.x - lx, dy = geo.y - ly;
-        float G, oG;
-        const float alpha = splat_alpha(geo, con, dx, dy, rc.alpha_max, G, oG);
-        const bool has = k < in.last && alpha >= rc.alpha_min;
-        // Wave-uniform guard; inside it every lane computes and the lanes
-        // without a contribution are masked with selects (NaN-safe).
-        if (__any(has)) {
-          const float4 col = s_rec[off + j].col;
-          // Lanes without a contribution take alpha = 0, which leaves T and
-          // S unchanged (1 / (1 - 0) is exactly 1) and gives w = 0.
-          const float ae = has ? alpha : 0.f;
-          const float rinv = __builtin_amdgcn_rcpf(1.f - ae);
-          const float Tk = T * rinv;  // transmittance in front of this Gaussian
-          T = Tk;
-          const float w = ae * Tk;
-          const float Q = __fmaf_rn(in.gD, geo.w - zr, __fmaf_rn(in.gC2, col.z, __fmaf_rn(in.gC1, col.y, in.gC0 * col.x)));
-          const float QS = Q - S;
-          const float dLda = __fmaf_rn(Tk, QS, Kf * rinv);
-          S = __fmaf_rn(ae, QS, S);
-          const bool open = has && oG <= rc.alpha_max;
-          // dL/dP with G = 2^P (the ln 2 and the conic pre-scale are applied
-          // at the flush); dL/d(opacity) = dLdP / o there.
-          const float dLdP = open ? dLda * oG : 0.f;
-          uint32_t *mw = reinterpret_cast<uint32_t *>(mA);
-          mw[(2 * nq) * MA_STRIDE + lane] = split_bf16(dLdP);
-          mw[(2 * nq + 1) * MA_STRIDE + lane] = split_bf16(w);
-          slots |= (uint64_t)j << (8 * nq);
-          ++nq;
-        }
+    if (ng > 0) {
+      // A group's sums are stored behind the next group's walk, so that the
+      // matrix cores work beside it.
+      uint32_t used = 0u;
+      GroupGeo<BHALF> g;
+      g.load(s_rec + off + ng * BGROUP - BHALF);
+      float4v D = {0.f, 0.f, 0.f, 0.f};
+      uint32_t *rows = reinterpret_cast<uint32_t *>(mA);
+      for (int q = ng - 1; q >= 0; --q) {
+        const int first = lo + q * BGROUP;
+        const uint32_t now =
+            backward_group(s_rec, off + q * BGROUP, first, first + BGROUP <= wmin, rc, px, rows + lane, g);
+        if (q < ng - 1) store_sums(D, used, my_part + (q + 1) * BGROUP * NMOM);
+        D = contract<BLO>(rows, Bb, Bl);
+        used = now;
       }
-      if (nq == 8 || (k < lo && nq > 0)) {
-        if (p_nq > 0) mfma_consume(pD, p_nq, p_slots, my_part);
-        pD = mfma_issue_split<BLO>(mA, Bb, Bl);
-        p_nq = nq;
-        p_slots = slots;
-        nq = 0;
-        slots = 0;
-        // The rows were read into registers; the next group may rewrite them.
-        wave_lds_sync();
-      }
+      store_sums(D, used, my_part);
     }
-    if (p_nq > 0) mfma_consume(pD, p_nq, p_slots, my_part);
     __syncthreads();
     // Flush.  First one thread per Gaussian of the batch converts its sums:
     // with the centre relative to the tile centre (uc, vc) and the pixel
@@ -594,7 +762,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   __shared__ Staged s_rec[SUB];
   __shared__ float s_part[4 * SUB * NMOM];
   __shared__ uint32_t s_id[SUB];
-  __shared__ int s_max;
+  __shared__ int s_max[4];
   __shared__ __align__(16) float s_mA[4 * MA_WAVE];
   const TileInfo ti = tile_info(blockIdx.x, a.views, a.tile_view, a.ranges);
   BwdIn in{1.f, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -610,12 +778,27 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     in.gD = g_depth ? g_depth[ti.pix] : 0.f;
     in.gT = g_T ? g_T[ti.pix] : 0.f;
   }
-  tile_backward<true>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id,
-                            &s_max, s_mA);
+  tile_backward<true>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id, s_max, s_mA);
 }
 
 __device__ __forceinline__ float sgnf(float x) { return (float)((x > 0.f) - (x < 0.f)); }
 
+// The walks are bound by the vector units: at 1200x680 (300 000 Gaussians,
+// 3 225 tiles) a step evaluates 1.16 M wave-entries in each direction, and a
+// wave-entry cost 25 vector instructions forward and 44 backward when entries
+// were taken one at a time.  It costs about 17 and 29 now, and k_render_fused
+// went from 210 to 160 us (86 % of the vector units' issue slots in use):
+//  - records are read a group ahead, and the tile's number, view and list are
+//    scalar: 317 -> 290 us a step;
+//  - a group asks once whether any of its pixels stops, resp. whether every
+//    entry is plain (backward_half), instead of selecting at each entry;
+//  - colours run on v_mfma_f32_4x4x1 (an FP32 matrix instruction that uses the
+//    vector units, but half the cycles of the four FMAs): 290 -> 283 us;
+//  - the two halves of dLdP and w are split as a pair (split_pair).
+// Measured and dropped: two pixels a thread (355 us: half the wavefronts and
+// 158 registers), the contraction in FP32 (290 us against 274), the residual
+// of the split from v_dot2c (the same time).
+//
 // Persistent fused step: blocks take tiles from an atomic counter (in index
 // order, or in the longest-first order of `queue`); per tile run the
 // forward blend, the L1 loss gradient of every pixel, and the backward walk
@@ -635,14 +818,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   __shared__ Staged s_rec[NB];
   __shared__ float s_part[4 * SUB * NMOM];
   __shared__ uint32_t s_id[NB];
-  __shared__ int s_max;
+  __shared__ int s_max[4];
   __shared__ __align__(16) float s_mA[4 * MA_WAVE];
   __shared__ int s_q;
   __shared__ float s_loss[4];
   for (;;) {
     if (threadIdx.x == 0) s_q = (int)atomicAdd(hdr + HDR_QUEUE, (uint32_t)tiles_per_pop);
     __syncthreads();
-    const int q0 = s_q;
+    const int q0 = __builtin_amdgcn_readfirstlane(s_q);  // (scalar: so are the tile's number, view and list)
     __syncthreads();
     if (q0 >= total_tiles) break;
     const int q1 = min(q0 + tiles_per_pop, total_tiles);
@@ -704,7 +887,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       const float ls = wave_sum(lpx);
       if ((threadIdx.x & 63) == 0) s_loss[threadIdx.x >> 6] = ls;
-      tile_backward<false>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id, &s_max,
+      tile_backward<false>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id, s_max,
                            s_mA, staged_lo, w_rgb, w_depth);
       if (threadIdx.x == 0) {
         tile_loss[tile] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
