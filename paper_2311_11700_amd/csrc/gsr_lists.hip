@@ -13,9 +13,9 @@
 // the sequence can be captured in a HIP graph.
 //
 // Measured against radix passes over the records and the pairs (17 dependent
-// kernels): 300k Gaussians at 1200x680, projection and lists 171 us -> 85 us;
-// 72 views of 500k, 12.2 ms -> 3.6 ms; 2 000 Gaussians at 160x120 as a whole
-// call 155 us -> 94 us.
+// kernels): 300k Gaussians at 1200x680, projection and lists 171 us -> 78 us;
+// 72 views of 500k, 12.2 ms -> 3.2 ms; 2 000 Gaussians at 160x120 as a whole
+// call 155 us -> 81 us.
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -74,6 +74,15 @@ void launch_lists_begin(const Workspace &ws, hipStream_t s) {
 // sorted entries whose mask has the tile's bit: per row of 64 entries one
 // ballot gives the tile's entries and each lane's place, so consecutive lanes
 // write consecutive words.
+//
+// Bound by the latency of the reads of the entries and by the block's LDS (one
+// block a CU at its 12 288 entries).  A bin of 7 000 entries (72 views of
+// 500 000 Gaussians) took 67 us: 20 to collect its groups, 10 to order the
+// slots, 8 for the masks and 21 to write.  It takes 51 us with the group table
+// read at once and four groups in flight (13), up to four entries of a slot
+// ordered in registers (8), id and mask read together, and the places counted
+// from the tile's next one in the lanes' registers (12): 5 512 bins 1.65 -> 1.2
+// ms, the 209 bins of 2 500 of a 1200x680 view 39 -> 33 us.
 constexpr int LB = 1024;         // threads
 constexpr int LW = LB / 64;      // wavefronts
 constexpr int LBITS = 8;         // bits per digit pass
@@ -95,11 +104,12 @@ struct ListsLds {
   union {
     uint16_t cnt[LW][LDIGITS];  // per-wavefront digit counts, then next positions
     uint32_t part[LPARTS / 2];  // counts of the parts (two per word), then next positions
+    uint2 group[LB];            // first entry and place of the groups that are being read
   };
   uint32_t w[LW];
   uint32_t tile[LW][NTILE];    // per-wavefront entries of each tile, then their first places
   uint32_t next[NTILE];        // next place of each tile's list
-  uint32_t kmin, kmax, n, most;
+  uint32_t kmin, kmax, n, most, end;
 };
 
 // One stable digit pass over n positions, from -> to, by `per` bits at sh of
@@ -174,6 +184,42 @@ __device__ __forceinline__ void order_span(const ListsArrays &a, uint16_t *from,
   }
 }
 
+// The same for the entries of one slot: up to four distinct keys (a slot holds
+// one entry on average) are ordered in registers, since an insertion step
+// waits for two dependent LDS reads.
+__device__ __forceinline__ void order_slot(const ListsArrays &a, uint16_t *from, int first, int last,
+                                           const Entry *__restrict__ entries) {
+  constexpr int N = 4;
+  const int n = last - first + 1;
+  if (n <= N) {
+    uint32_t f[N], k[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = i < n ? from[first + i] : 0u;
+#pragma unroll
+    for (int i = 0; i < N; ++i) k[i] = i < n ? a.key[f[i]] : 0xFFFFFFFFu;  // (keys are below 2^31)
+    auto order = [&](int i, int j) {
+      const bool swap = k[j] < k[i];
+      const uint32_t ki = k[i], fi = f[i];
+      k[i] = swap ? k[j] : ki;
+      f[i] = swap ? f[j] : fi;
+      k[j] = swap ? ki : k[j];
+      f[j] = swap ? fi : f[j];
+    };
+    order(0, 1);
+    order(2, 3);
+    order(0, 2);
+    order(1, 3);
+    order(1, 2);
+    if (k[0] != k[1] && (n < 3 || k[1] != k[2]) && (n < 4 || k[2] != k[3])) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (i < n) from[first + i] = (uint16_t)f[i];
+      return;
+    }
+  }
+  order_span(a, from, first, last, entries);
+}
+
 // Exclusive scan of `count` 16-bit counters in place (two per word); s.most
 // becomes the largest of them if that exceeds `limit`.
 __device__ __forceinline__ void scan_counters(ListsLds &s, uint32_t *words, int count, uint32_t limit) {
@@ -236,7 +282,7 @@ __device__ __forceinline__ void sort_entries(ListsLds &s, ListsArrays &a, int n,
     __syncthreads();
     for (int t = threadIdx.x; t < n; t += LB) {
       const int first = t ? a.to[t - 1] : 0, last = (int)a.to[t] - 1;
-      if (last > first) order_span(a, a.from, first, last, entries);
+      if (last > first) order_slot(a, a.from, first, last, entries);
     }
     __syncthreads();
     return;
@@ -268,22 +314,137 @@ __device__ __forceinline__ void sort_entries(ListsLds &s, ListsArrays &a, int n,
   __syncthreads();
 }
 
-// Calls f(first entry, count, lane of the team) for every group of the bin
-// (the entries one projection batch wrote for it), a team of LTEAM lanes a
-// group: the teams of a wavefront read LTEAM consecutive entries each.
-constexpr int LTEAM = 8;
-template <typename F>
-__device__ __forceinline__ void for_groups(const Workspace &ws, const ViewInfo &vi, int view, int local, int groups,
-                                           F f) {
+// Calls use(place, entry, load(entry)) for every entry of the bin, place
+// counting them group after group (the entries one projection batch wrote for
+// the bin); returns their number.  The groups' first entries and places come
+// from one read of the group table by the whole block, so that the reads of
+// the entries depend on LDS alone and LUNROLL groups of a team of LTEAM lanes
+// are in flight at a time: reading a group's place, then its entries, one
+// group after the other, took 20 of a bin's 67 us with 980 groups of 7 entries.
+constexpr int LTEAM = 16;
+constexpr int LUNROLL = 4;
+template <typename L, typename U>
+__device__ __forceinline__ int for_entries(ListsLds &s, const Workspace &ws, const ViewInfo &vi, int view, int local,
+                                           int groups, L load, U use) {
   const int stride = vi.BX * vi.BY + 1;
   const int sub = threadIdx.x & (LTEAM - 1);
+  constexpr int TEAMS = LB / LTEAM;
   const uint32_t *bases = ws.block_base + (size_t)view * groups;
-  for (int j = threadIdx.x / LTEAM; j < groups; j += LB / LTEAM) {
-    const uint32_t base = bases[j];
-    if (base == NO_BASE) continue;
-    const uint32_t *row = ws.group_off + vi.mat_off + (int64_t)j * stride + local;
-    const uint32_t first = row[0], n = row[1] - first;
-    if (n > 0u) f(base + first, n, sub);
+  uint32_t E = 0u;
+  for (int g0 = 0; g0 < groups; g0 += LB) {
+    const int j = g0 + (int)threadIdx.x;
+    uint32_t first = 0u, n = 0u, total;
+    if (j < groups) {
+      const uint32_t base = bases[j];
+      const uint32_t *row = ws.group_off + vi.mat_off + (int64_t)j * stride + local;
+      const uint32_t r0 = row[0], r1 = row[1];  // (not written where base is NO_BASE)
+      if (base != NO_BASE) {
+        first = base + r0;
+        n = r1 - r0;
+      }
+    }
+    __syncthreads();  // (the table's place: s.part, s.w)
+    const uint32_t pre = block_exclusive_scan<LB>(n, s.w, total) + E;
+    s.group[threadIdx.x] = make_uint2(first, pre);
+    if (threadIdx.x == 0) s.end = E + total;
+    E += total;
+    __syncthreads();
+    const int ng = min(LB, groups - g0);
+    for (int t0 = threadIdx.x / LTEAM; t0 < ng; t0 += TEAMS * LUNROLL) {
+      uint32_t e[LUNROLL], q[LUNROLL], left[LUNROLL];
+      decltype(load(0u)) v[LUNROLL];
+#pragma unroll
+      for (int u = 0; u < LUNROLL; ++u) {
+        const int t = t0 + u * TEAMS;
+        left[u] = 0u;
+        if (t < ng) {
+          const uint2 g = s.group[t];
+          const uint32_t next = t + 1 < ng ? s.group[t + 1].y : s.end;
+          e[u] = g.x + sub;
+          q[u] = g.y + sub;
+          left[u] = next > q[u] ? next - q[u] : 0u;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < LUNROLL; ++u)
+        if (left[u]) v[u] = load(e[u]);
+#pragma unroll
+      for (int u = 0; u < LUNROLL; ++u)
+        if (left[u]) {
+          use(q[u], e[u], v[u]);
+          for (uint32_t k = LTEAM; k < left[u]; k += LTEAM) use(q[u] + k, e[u] + k, load(e[u] + k));
+        }
+    }
+  }
+  __syncthreads();
+  return (int)E;
+}
+
+// The sorted entries' record ids and masks in order, in the place of the keys
+// and of the free positions (a thread reads and writes its own places only),
+// and the wavefront's entries of each of the bin's NT tiles.
+template <int NT>
+__device__ __forceinline__ void order_masks(ListsLds &s, const ListsArrays &a, const Entry *__restrict__ entries, int n,
+                                            int I, int at) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t c[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) c[t] = 0u;
+  for (int r0 = 0; r0 < I; r0 += LUNROLL) {
+    // (LUNROLL rows' reads in flight)
+    uint32_t m[LUNROLL], id[LUNROLL];
+#pragma unroll
+    for (int u = 0; u < LUNROLL; ++u) {
+      const int q = at + 64 * (r0 + u);
+      m[u] = 0u;
+      if (r0 + u < I && q < n) {
+        const Entry *e = entries + a.at[a.from[q]];
+        id[u] = e->id;
+        m[u] = e->mask;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < LUNROLL; ++u) {
+      if (r0 + u >= I) break;
+      const int q = at + 64 * (r0 + u);
+      if (q < n) {
+        a.key[q] = id[u];
+        a.to[q] = (uint16_t)m[u];
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) c[t] += (uint32_t)__popcll(__ballot((m[u] & (1u << t)) != 0u));
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    if (lane == t) s.tile[wave][t] = c[t];
+}
+
+// The wavefront's part of the NT lists, from s.tile on: in a row of 64 entries
+// the lanes whose mask has the tile's bit write consecutive words.
+template <int NT>
+__device__ __forceinline__ void write_lists(const ListsLds &s, const ListsArrays &a, uint32_t *__restrict__ ids, int n,
+                                            int I, int at) {
+  const int wave = threadIdx.x >> 6;
+  uint32_t c[NT];  // next place (held per lane: the count of the lanes in front starts from it)
+#pragma unroll
+  for (int t = 0; t < NT; ++t) c[t] = s.tile[wave][t];
+  for (int r = 0; r < I; ++r) {
+    const int q = at + 64 * r;
+    uint32_t m = 0u, id = 0u;
+    if (q < n) {
+      m = a.to[q];
+      id = a.key[q];
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const bool in = (m & (1u << t)) != 0u;
+      const uint64_t b = __builtin_amdgcn_ballot_w64(in);
+      const uint32_t place =
+          __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, c[t]));
+      if (in) ids[place] = id;
+      c[t] += (uint32_t)__popcll(b);
+    }
   }
 }
 
@@ -340,25 +501,20 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
   if (threadIdx.x == 0) {
     s.kmin = 0xFFFFFFFFu;
     s.kmax = 0u;
-    s.n = 0u;
   }
-  __syncthreads();
+  int E;
   {
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-    for_groups(ws, vi, view, local, groups, [&](uint32_t e, uint32_t n, int sub) {
-      uint32_t q = 0u;
-      if (sub == 0) q = atomicAdd(&s.n, n);
-      q = __shfl(q, 0, LTEAM);
-      for (uint32_t k = sub; k < n; k += LTEAM) {
-        const uint32_t key = entries[e + k].key;
-        kmin = min(kmin, key);
-        kmax = max(kmax, key);
-        if (q + k < (uint32_t)cap) {
-          a.key[q + k] = key;
-          a.at[q + k] = e + k;
-        }
-      }
-    });
+    E = for_entries(
+        s, ws, vi, view, local, groups, [&](uint32_t e) { return entries[e].key; },
+        [&](uint32_t q, uint32_t e, uint32_t key) {
+          kmin = min(kmin, key);
+          kmax = max(kmax, key);
+          if (q < (uint32_t)cap) {
+            a.key[q] = key;
+            a.at[q] = e;
+          }
+        });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       kmin = min(kmin, __shfl_xor(kmin, o));
@@ -370,7 +526,6 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
     }
   }
   __syncthreads();
-  const int E = (int)s.n;
   if (E == 0) {
     if (my_tile) ws.ranges[tile] = make_int2(0, 0);
     return;
@@ -381,10 +536,11 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
     // The tiles' totals, needed before the first round writes.
     if (threadIdx.x < NTILE) s.next[threadIdx.x] = 0u;
     __syncthreads();
-    for_groups(ws, vi, view, local, groups, [&](uint32_t e, uint32_t n, int sub) {
-      for (uint32_t k = sub; k < n; k += LTEAM)
-        for (uint32_t m = entries[e + k].mask; m; m &= m - 1u) atomicAdd(&s.next[__ffs(m) - 1], 1u);
-    });
+    for_entries(
+        s, ws, vi, view, local, groups, [&](uint32_t e) { return entries[e].mask; },
+        [&](uint32_t, uint32_t, uint32_t mask) {
+          for (uint32_t m = mask; m; m &= m - 1u) atomicAdd(&s.next[__ffs(m) - 1], 1u);
+        });
     __syncthreads();
   }
 
@@ -406,12 +562,12 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
         for (int b = threadIdx.x; b < LPARTS; b += LB) hist[b] = 0u;
         if (threadIdx.x == 0) s.n = (uint32_t)LPARTS;
         __syncthreads();
-        for_groups(ws, vi, view, local, groups, [&](uint32_t e, uint32_t cnt, int sub) {
-          for (uint32_t i = e + sub; i < e + cnt; i += LTEAM) {
-            const uint64_t k = (uint64_t)entries[i].key << 32 | entries[i].id;
-            if (k >= lo && (k - lo) >> sh < (uint64_t)LPARTS) atomicAdd(&hist[(k - lo) >> sh], 1u);
-          }
-        });
+        for_entries(
+            s, ws, vi, view, local, groups,
+            [&](uint32_t e) { return (uint64_t)entries[e].key << 32 | entries[e].id; },
+            [&](uint32_t, uint32_t, uint64_t k) {
+              if (k >= lo && (k - lo) >> sh < (uint64_t)LPARTS) atomicAdd(&hist[(k - lo) >> sh], 1u);
+            });
         __syncthreads();
         // Parts in order while their sum fits: the first part whose
         // inclusive sum exceeds cap ends the range.
@@ -437,17 +593,16 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
       __syncthreads();
       if (threadIdx.x == 0) s.n = 0u;
       __syncthreads();
-      for_groups(ws, vi, view, local, groups, [&](uint32_t e, uint32_t cnt, int sub) {
-        for (uint32_t i = e + sub; i < e + cnt; i += LTEAM) {
-          const uint32_t dk = entries[i].key;
-          const uint64_t k = (uint64_t)dk << 32 | entries[i].id;
-          if (k >= lo && k < hi) {
-            const uint32_t q = atomicAdd(&s.n, 1u);
-            a.key[q] = dk;
-            a.at[q] = i;
-          }
-        }
-      });
+      for_entries(
+          s, ws, vi, view, local, groups,
+          [&](uint32_t e) { return (uint64_t)entries[e].key << 32 | entries[e].id; },
+          [&](uint32_t, uint32_t e, uint64_t k) {
+            if (k >= lo && k < hi) {
+              const uint32_t q = atomicAdd(&s.n, 1u);
+              a.key[q] = (uint32_t)(k >> 32);
+              a.at[q] = e;
+            }
+          });
       __syncthreads();
       n = (int)s.n;
     }
@@ -457,25 +612,9 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
     const int I = (n + LB - 1) / LB;
     const int at = wave * 64 * I + lane;
     sort_entries(s, a, n, I, at, key0, key1 <= key0 ? 0 : 32 - __clz(key1 - key0), entries, id0, id_bits);
-    // Masks in order (in the keys' place) and the wavefront's entries of each
-    // tile; a thread reads and writes its own places only.
-    uint32_t c[NTILE];
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t) c[t] = 0u;
-    for (int r = 0; r < I; ++r) {
-      const int q = at + 64 * r;
-      uint32_t m = 0u;
-      if (q < n) {
-        m = entries[a.at[a.from[q]]].mask;
-        a.key[q] = m;
-      }
-#pragma unroll
-      for (int t = 0; t < NTILE; ++t)
-        if (t < nt) c[t] += (uint32_t)__popcll(__ballot((m >> t) & 1u));
-    }
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t)
-      if (lane == t) s.tile[wave][t] = c[t];
+    if (shift == 2) order_masks<16>(s, a, entries, n, I, at);
+    else if (shift == 1) order_masks<4>(s, a, entries, n, I, at);
+    else order_masks<1>(s, a, entries, n, I, at);
     __syncthreads();
     if (threadIdx.x < 64) {
       uint32_t mine = 0u;
@@ -520,26 +659,9 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
     __syncthreads();
     if (!placed && s.most == 0xFFFFFFFFu) return;
     placed = true;
-    const uint64_t lt = lanemask_lt();
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t) c[t] = t < nt ? __builtin_amdgcn_readfirstlane(s.tile[wave][t]) : 0u;
-    for (int r = 0; r < I; ++r) {
-      const int q = at + 64 * r;
-      uint32_t m = 0u, id = 0u;
-      if (q < n) {
-        m = a.key[q];
-        id = entries[a.at[a.from[q]]].id;
-      }
-#pragma unroll
-      for (int t = 0; t < NTILE; ++t) {
-        if (t < nt) {
-          const bool in = (m >> t) & 1u;
-          const uint64_t b = __ballot(in);
-          if (in) ws.ids[c[t] + (uint32_t)__popcll(b & lt)] = id;
-          c[t] += (uint32_t)__popcll(b);
-        }
-      }
-    }
+    if (shift == 2) write_lists<16>(s, a, ws.ids, n, I, at);
+    else if (shift == 1) write_lists<4>(s, a, ws.ids, n, I, at);
+    else write_lists<1>(s, a, ws.ids, n, I, at);
     __syncthreads();
   }
 }
