@@ -137,7 +137,7 @@ struct Workspace {
   float *zr;               // [total_pixels] depth of the last blended entry (forward -> backward)
   unsigned long long *counts;  // [4] work totals (gsr_work_counts)
   double *grad2d;          // [n_rec][NGRAD2D], FP64 sums over tiles
-  double *pose_part;       // [n_pose_blocks][n_views][6]
+  double *pose_part;       // [n_views][6][n_pose_blocks]
   uint32_t *queue;         // [total_tiles] work order of the persistent rasteriser
   unsigned long long *expand_bits;  // [chunks][8][4] adding step: one bit per pixel (ballot words)
   uint32_t *expand_cnt;    // [chunks] adding step: unreliable pixels per chunk, then their exclusive scan
