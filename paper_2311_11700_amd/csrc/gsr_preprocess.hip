@@ -44,16 +44,21 @@ __device__ __forceinline__ void quat_rot(T w, T x, T y, T z, T R[9]) {
 // cutoff sqrt(A) with A <= |J_0|^2 max(scale)^2 + lowpass; the bound is
 // evaluated in float32 with margins far above its rounding, and any
 // comparison with a NaN keeps the record for the exact tests.
-__device__ __forceinline__ bool surely_culled(const gsr_gaussians &g, const gsr_camera &cam, const ViewInfo &vi,
-                                              const PreConsts &pc, int64_t i) {
-  if (g.mask && g.mask[i] == 0) return true;
-  const double mx = g.mean[3 * i], my = g.mean[3 * i + 1], mz = g.mean[3 * i + 2];
+struct Early {
+  float m[3], ls[3];  // mean, log scales
+  uint8_t keep;       // mask
+};
+
+__device__ __forceinline__ bool surely_culled(const Early &e, const gsr_camera &cam, const ViewInfo &vi,
+                                              const PreConsts &pc) {
+  if (e.keep == 0) return true;
+  const double mx = e.m[0], my = e.m[1], mz = e.m[2];
   const double x = (((double)cam.R[0] * mx + (double)cam.R[1] * my) + (double)cam.R[2] * mz) + (double)cam.t[0];
   const double y = (((double)cam.R[3] * mx + (double)cam.R[4] * my) + (double)cam.R[5] * mz) + (double)cam.t[1];
   const double z = (((double)cam.R[6] * mx + (double)cam.R[7] * my) + (double)cam.R[8] * mz) + (double)cam.t[2];
   if (z <= (double)pc.z_near) return true;
   if ((pc.flags & GSR_FULL_RECT) || !(cam.fx > 0.f) || !(cam.fy > 0.f)) return false;
-  const float ls = fmaxf(fmaxf(g.log_scale[3 * i], g.log_scale[3 * i + 1]), g.log_scale[3 * i + 2]);
+  const float ls = fmaxf(fmaxf(e.ls[0], e.ls[1]), e.ls[2]);
   const float smax = __expf(ls) * 1.001f;
   const float rz = 1.f / (float)z, xz = (float)x * rz, yz = (float)y * rz;
   float tx = fabsf(xz), ty = fabsf(yz);
@@ -71,9 +76,8 @@ __device__ __forceinline__ bool surely_culled(const gsr_gaussians &g, const gsr_
 }
 
 // What the binning needs of a visible record: its tile rectangle, depth key,
-// conic and alpha support.
+// conic (its alpha support lies apart).
 struct Staged {
-  Support sp;
   float a, b, c;
   uint32_t key, rec;
   uint16_t tx0, tx1, ty0, ty1;
@@ -97,7 +101,7 @@ struct ProjArgs {
 // (170 instead of 90, and one block per CU less).
 template <bool SH>
 __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, const gsr_camera *camp, int64_t i,
-                                                         int64_t rec, Staged *out) {
+                                                         int64_t rec, Staged *out, Support *support) {
   const gsr_gaussians &g = args->g;
   const ViewInfo &vi = args->vi;
   const PreConsts &pc = args->pc;
@@ -236,7 +240,7 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
       sp.U = sp.V = sp.t = sp.dys = sp.ra = 0.0;
       sp.hy = -1.0;  // no row reaches it
     }
-    out->sp = sp;
+    *support = sp;
   }
   ws.count[rec] = (uint32_t)(tx1 - tx0 + 1) * (uint32_t)(ty1 - ty0 + 1);
   out->a = fb.x;
@@ -261,16 +265,30 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
 // kept in LDS, the rest found again where they are used); then, per bin row of
 // every record, the entries per bin are counted (lds_bins bins at a time) and
 // one global add reserves the batch's place; then they are written grouped by
-// bin.
+// bin, from the list that the count kept of them (in the supports' place) or,
+// where that does not hold them all, by walking the bin rows again.
+// Bound by the latency of these phases where the grid is about a block a CU
+// (2 048 records of 160x120 and 300 000 of 1200x680: 24 and 44 us before the
+// early test read its rounds together, rows and bin rows knew their record
+// without a search and the second sweep gave way to the list; 19 and 36 now),
+// by memory over many views (36 M records, 5 GB read and written: 1.9 ms).
 constexpr int ROW_CACHE = 3072;
+constexpr int UNIT_CACHE = 2048;  // bin rows whose record is kept
+
+// An entry of the batch: its record and mask, its bin and its number there.
+struct Item {
+  uint16_t rec, mask, bin, at;
+};
+constexpr int ITEMS = PRE_BLOCK * (int)(sizeof(Support) / sizeof(Item));
+static_assert(BIN_MAX * BIN_MAX <= 16 && ITEMS <= 65536, "16-bit fields");
 
 // Column range of one tile row of a record: first column | length << 16 (length
 // 0 where the alpha support does not reach the row).
-__device__ __forceinline__ uint32_t row_range(const Staged &t, bool cull, int ty) {
+__device__ __forceinline__ uint32_t row_range(const Staged &t, const Support &sp, bool cull, int ty) {
   int c0 = t.tx0, len = (int)t.tx1 - (int)t.tx0 + 1;
   if (cull) {
     c0 = 0;
-    len = support_row(t.sp, (double)t.a, (double)t.b, (double)t.c, ty, t.tx0, t.tx1, c0);
+    len = support_row(sp, (double)t.a, (double)t.b, (double)t.c, ty, t.tx0, t.tx1, c0);
   }
   return (uint32_t)c0 | (uint32_t)len << 16;
 }
@@ -308,13 +326,18 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   extern __shared__ uint32_t s_cur[];  // [lds_bins]
   __shared__ ProjArgs s_args;
   __shared__ Staged s_rec[PRE_BLOCK];  // the records of a batch (the visible ones filled in)
+  __shared__ union {
+    Support support[PRE_BLOCK];
+    Item item[ITEMS];
+  } s_u;
+  __shared__ uint16_t s_unit[UNIT_CACHE];
   __shared__ uint32_t s_first[PRE_BLOCK];
   __shared__ uint32_t s_rowat[PRE_BLOCK];  // first tile row of each record
   __shared__ uint32_t s_rows[ROW_CACHE];
   __shared__ uint16_t s_left[PRE_BLOCK * PRE_ROUNDS_MAX];  // records the early test leaves
   __shared__ uint32_t s_w[NW];
   __shared__ unsigned long long s_pairs[NW];
-  __shared__ uint32_t s_base, s_nleft;
+  __shared__ uint32_t s_base, s_nleft, s_nitem;
   const int view = blockIdx.x / bpv, blk = blockIdx.x - view * bpv;
   const ViewInfo vi = views[view];
   const gsr_camera &cam = cams[view];
@@ -330,18 +353,36 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     s_args = ProjArgs{g, vi, pc, ws.recA, ws.recB, ws.recC, ws.count, ws.grad2d, cull ? 1 : 0};
   }
   __syncthreads();
-  for (int r = 0; r < rounds; ++r) {
-    const int64_t i = i0 + r * PRE_BLOCK + threadIdx.x;
-    bool left = false;
-    if (i < g.n) {
-      left = !surely_culled(g, cam, vi, pc, i);
-      if (!left) ws.count[rec0 + i] = 0u;
+  {
+    // (the reads of all rounds are in flight together)
+    Early e[PRE_ROUNDS_MAX];
+#pragma unroll
+    for (int r = 0; r < PRE_ROUNDS_MAX; ++r) {
+      const int64_t i = i0 + r * PRE_BLOCK + threadIdx.x;
+      if (r < rounds && i < g.n) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          e[r].m[k] = g.mean[3 * i + k];
+          e[r].ls[k] = g.log_scale[3 * i + k];
+        }
+        e[r].keep = g.mask ? g.mask[i] : 1;
+      }
     }
-    const uint64_t m = __ballot(left);
-    uint32_t at = 0u;
-    if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&s_nleft, (uint32_t)__popcll(m));
-    at = __shfl(at, 0);
-    if (left) s_left[at + (uint32_t)__popcll(m & lanemask_lt())] = (uint16_t)(r * PRE_BLOCK + threadIdx.x);
+#pragma unroll
+    for (int r = 0; r < PRE_ROUNDS_MAX; ++r) {
+      if (r >= rounds) break;
+      const int64_t i = i0 + r * PRE_BLOCK + threadIdx.x;
+      bool left = false;
+      if (i < g.n) {
+        left = !surely_culled(e[r], cam, vi, pc);
+        if (!left) ws.count[rec0 + i] = 0u;
+      }
+      const uint64_t m = __ballot(left);
+      uint32_t at = 0u;
+      if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&s_nleft, (uint32_t)__popcll(m));
+      at = __shfl(at, 0);
+      if (left) s_left[at + (uint32_t)__popcll(m & lanemask_lt())] = (uint16_t)(r * PRE_BLOCK + threadIdx.x);
+    }
   }
   __syncthreads();
   const int nleft = (int)s_nleft;
@@ -358,7 +399,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     bool vis = false;
     if (k < nleft) {
       const int64_t i = i0 + (int)s_left[k];
-      vis = project_record<SH>(&s_args, &cam, i, rec0 + i, &s_rec[threadIdx.x]);
+      vis = project_record<SH>(&s_args, &cam, i, rec0 + i, &s_rec[threadIdx.x], &s_u.support[threadIdx.x]);
     }
     uint32_t units, tile_rows;
     {
@@ -370,15 +411,23 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
         nu = (uint32_t)((t.ty1 >> shift) - (t.ty0 >> shift) + 1);
         pairs += (unsigned long long)(t.tx1 - t.tx0 + 1) * nr;
       }
-      s_first[threadIdx.x] = block_exclusive_scan<PRE_BLOCK>(nu, s_w, units);
-      s_rowat[threadIdx.x] = block_exclusive_scan<PRE_BLOCK>(nr, s_w, tile_rows);
+      if (threadIdx.x == 0) s_nitem = 0u;
+      const uint32_t u0 = block_exclusive_scan<PRE_BLOCK>(nu, s_w, units);
+      const uint32_t r0 = block_exclusive_scan<PRE_BLOCK>(nr, s_w, tile_rows);
+      s_first[threadIdx.x] = u0;
+      s_rowat[threadIdx.x] = r0;
+      // The rows and bin rows in the caches name their record.
+      for (uint32_t u = u0; u < min(u0 + nu, (uint32_t)UNIT_CACHE); ++u) s_unit[u] = (uint16_t)threadIdx.x;
+      for (uint32_t u = r0; u < min(r0 + nr, (uint32_t)ROW_CACHE); ++u) s_rows[u] = threadIdx.x;
     }
     __syncthreads();
     for (uint32_t u = threadIdx.x; u < min(tile_rows, (uint32_t)ROW_CACHE); u += PRE_BLOCK) {
-      const int o = owner_of(s_rowat, nrec, u);
-      s_rows[u] = row_range(s_rec[o], cull, s_rec[o].ty0 + (int)(u - s_rowat[o]));
+      const int o = (int)s_rows[u];
+      s_rows[u] = row_range(s_rec[o], s_u.support[o], cull, s_rec[o].ty0 + (int)(u - s_rowat[o]));
     }
     __syncthreads();
+    // The supports are needed no more, unless rows are to be found again.
+    const bool listing = tile_rows <= (uint32_t)ROW_CACHE && nb <= lds_bins;
     uint32_t *row = ws.group_off + vi.mat_off + ((int64_t)blk * rounds + batch) * (nb + 1);
     uint32_t carry = 0u;
     // Sweep 0 over all bins (counts and offsets), then sweep 1 (entries).
@@ -393,7 +442,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
           __syncthreads();
         }
         for (uint32_t u = threadIdx.x; u < units; u += PRE_BLOCK) {
-          const int o = owner_of(s_first, nrec, u);
+          const int o = u < (uint32_t)UNIT_CACHE ? (int)s_unit[u] : owner_of(s_first, nrec, u);
           const Staged &t = s_rec[o];
           const int by = (t.ty0 >> shift) + (int)(u - s_first[o]);
           uint32_t rows[BIN_MAX];
@@ -403,7 +452,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
             rows[r] = 0u;
             if (r < S && ty >= (int)t.ty0 && ty <= (int)t.ty1) {
               const uint32_t at = s_rowat[o] + (uint32_t)(ty - (int)t.ty0);
-              rows[r] = at < (uint32_t)ROW_CACHE ? s_rows[at] : row_range(t, cull, ty);
+              rows[r] = at < (uint32_t)ROW_CACHE ? s_rows[at] : row_range(t, s_u.support[o], cull, ty);
             }
           }
           for (int bx = t.tx0 >> shift; bx <= t.tx1 >> shift; ++bx) {
@@ -412,7 +461,12 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
             const uint32_t m = unit_mask(rows, bx, shift);
             if (m == 0u) continue;
             const uint32_t p = atomicAdd(&s_cur[b], 1u);
-            if (sweep == 1) ws.entries[s_base + p] = Entry{t.key, t.rec, m};
+            if (sweep == 1) {
+              ws.entries[s_base + p] = Entry{t.key, t.rec, m};
+            } else if (listing) {
+              const uint32_t k = atomicAdd(&s_nitem, 1u);
+              if (k < (uint32_t)ITEMS) s_u.item[k] = Item{(uint16_t)o, (uint16_t)m, (uint16_t)b, (uint16_t)p};
+            }
           }
         }
         __syncthreads();
@@ -444,6 +498,14 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
         }
         __syncthreads();
         if (s_base == NO_BASE) break;
+        if (listing && carry <= (uint32_t)ITEMS) {
+          for (uint32_t k = threadIdx.x; k < carry; k += PRE_BLOCK) {
+            const Item it = s_u.item[k];
+            const Staged &t = s_rec[it.rec];
+            ws.entries[s_base + s_cur[it.bin] + it.at] = Entry{t.key, t.rec, it.mask};
+          }
+          break;
+        }
       }
     }
     __syncthreads();  // the next batch takes the staging

@@ -99,3 +99,31 @@ def test_lists_of_a_view_with_many_bins(gsr_lib):
     tiles = np.random.default_rng(1).choice(proj["TX"] * proj["TY"], 150, replace=False).tolist()
     _, n_gpu, _ = H.check_view_lists(rng, ids, 0, 0, proj, O.tile_lists(proj), *size, ocfg, tiles=tiles)
     assert n_gpu > 0
+
+
+@pytest.mark.parametrize("n", [100, 512, 1500])
+def test_lists_of_wide_gaussians(gsr_lib, n):
+    """Gaussians about 500 px wide and a few tile rows high: a batch of 512 has
+    more entries than the count's list holds (3 072) while all its tile rows
+    stay in LDS; 100 fit the list, 1 500 take three batches of the two kinds."""
+    gsr = gsr_lib
+    size = (640, 480)
+    sc = W.needle_scene(n, seed=2, z=(2.5, 3.5), half_width=0.4, sigma_y=(0.2, 0.5), sigma_thin=0.004)
+    sc.mean[:, :2] = sc.mean[:, 1::-1]  # lying instead of standing
+    sc.mean[:, 0] *= 2.0
+    sc.log_scale[:, :2] = sc.log_scale[:, 1::-1]
+    cam = W.camera_tum()
+    r = gsr.Renderer()
+    r.plan(n, [size], pair_capacity=2_000_000)
+    cfg = gsr.Config()
+    r.render_forward(H.gpu_scene(gsr, sc), gsr.pack_cameras([cam]), cfg)
+    rng, ids = (x.numpy() for x in r.debug_tiles())
+    ocfg = H.oracle_cfg_of(cfg)
+    proj = O.project(sc, cam, ocfg.as_f32())
+    rect = proj["rect"][proj["valid"]]
+    rows, bins = rect[:, 3] - rect[:, 2] + 1, (rect[:, 1] // 4 - rect[:, 0] // 4 + 1) * (rect[:, 3] // 4 - rect[:, 2] // 4 + 1)
+    assert rows.sum() / n <= 6 and bins.sum() / n > 7  # 512: at most 3 072 rows, more than 3 072 entries
+    assert r.pair_count() == H.rect_pairs(proj)
+    tiles = np.random.default_rng(n).choice(proj["TX"] * proj["TY"], 80, replace=False).tolist()
+    _, n_gpu, _ = H.check_view_lists(rng, ids, 0, 0, proj, O.tile_lists(proj), *size, ocfg, tiles=tiles)
+    assert n_gpu > 0
