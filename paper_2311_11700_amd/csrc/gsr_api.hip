@@ -98,10 +98,8 @@ Workspace make_ws(const Plan &p, void *base_v) {
   char *base = static_cast<char *>(base_v);
   Workspace w{};
   w.hdr = reinterpret_cast<uint32_t *>(base + p.off_hdr);
-  w.recA = reinterpret_cast<float4 *>(base + p.off_recA);
-  w.recB = reinterpret_cast<float4 *>(base + p.off_recB);
-  w.recC = reinterpret_cast<float4 *>(base + p.off_recC);
-  w.count = reinterpret_cast<uint32_t *>(base + p.off_count);
+  w.rec = reinterpret_cast<float4 *>(base + p.off_rec);
+  w.visible = reinterpret_cast<uint32_t *>(base + p.off_visible);
   w.entries = reinterpret_cast<Entry *>(base + p.off_entries);
   w.group_off = reinterpret_cast<uint32_t *>(base + p.off_group);
   w.block_base = reinterpret_cast<uint32_t *>(base + p.off_base);
@@ -113,6 +111,7 @@ Workspace make_ws(const Plan &p, void *base_v) {
   w.zr = reinterpret_cast<float *>(base + p.off_zr);
   w.counts = reinterpret_cast<unsigned long long *>(base + p.off_counts);
   w.grad2d = reinterpret_cast<double *>(base + p.off_grad2d);
+  w.grad_col = reinterpret_cast<double *>(base + p.off_grad_col);
   w.pose_part = reinterpret_cast<double *>(base + p.off_pose);
   w.queue = reinterpret_cast<uint32_t *>(base + p.off_queue);
   w.tile_cost = reinterpret_cast<uint32_t *>(base + p.off_tile_cost);
@@ -150,10 +149,10 @@ RenderConsts consts(const gsr_config &c, const gsr_gaussians &g) {
   rc.bg[0] = c.bg[0];
   rc.bg[1] = c.bg[1];
   rc.bg[2] = c.bg[2];
-  // Opacity and colour gradients (fields 5-8) feed only the Gaussian
+  // Opacity and colour gradients (fields 6-9) feed only the Gaussian
   // parameters, except that spherical-harmonic colour depends on the
   // viewing direction and so on the pose; a pose-only backward skips the rest.
-  rc.grad_fields = (c.flags & GSR_GAUSS_GRAD) ? 0x3FFu : (g.sh ? 0x3FFu & ~0x020u : 0x3FFu & ~0x1E0u);
+  rc.grad_fields = (c.flags & GSR_GAUSS_GRAD) ? 0x3FFu : (g.sh ? 0x3BFu : 0x03Fu);
   return rc;
 }
 
@@ -197,6 +196,12 @@ void prof_end(gsr_ctx *ctx, hipStream_t s, int first_unmarked) {
   if (!ctx->cur_events) return;
   for (int j = first_unmarked; j < GSR_NSTAGES; ++j) (void)hipEventRecord(ctx->cur_events[j + 1], s);
   ctx->cur_events = nullptr;
+}
+
+// The gradient rows that a backward with these constants adds to.
+void launch_clear_grads(const Workspace &ws, int64_t n_rec, const RenderConsts &rc, hipStream_t s) {
+  launch_fill_f32(reinterpret_cast<float *>(ws.grad2d), 0.f, 2 * n_rec * GEO_ROW, s);
+  if (rc.grad_fields >> GEO_FIELDS) launch_fill_f32(reinterpret_cast<float *>(ws.grad_col), 0.f, 2 * n_rec * COL_ROW, s);
 }
 
 // Projection and tile lists.  The projection also clears grad2d for a fused
@@ -364,10 +369,9 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   };
   const size_t nr = (size_t)p.n_rec, cap = (size_t)p.capacity;
   p.off_hdr = take(HDR_WORDS * 4);
-  p.off_recA = take(16 * nr);
-  p.off_recB = take(16 * nr);
-  p.off_recC = take(16 * nr);
-  p.off_count = take(4 * nr);
+  p.off_rec = take(sizeof(float4) * REC_ROW * nr);
+  p.vis_words = bpv * rounds * (PRE_BLOCK / 32);
+  p.off_visible = take(4 * (size_t)p.vis_words * n_views);
   const size_t pre_blocks = (size_t)p.blocks_per_view * n_views;
   p.off_entries = take(sizeof(Entry) * cap);
   p.off_base = take(4 * pre_blocks * rounds);
@@ -381,7 +385,8 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   // the per-pixel state, and take its place where they fit.
   p.off_group = 4 * (size_t)mat <= off - p.off_T ? p.off_T : take(4 * (size_t)mat);
   p.off_counts = take(64);
-  p.off_grad2d = take(8 * NGRAD2D * nr);
+  p.off_grad2d = take(8 * GEO_ROW * nr);
+  p.off_grad_col = take(8 * COL_ROW * nr);
   p.off_pose = take(8 * 6 * (size_t)n_views * p.n_pose_blocks);
   p.off_queue = take(4 * (size_t)p.total_tiles);
   p.off_tile_cost = take(4 * (size_t)p.total_tiles);
@@ -475,7 +480,7 @@ gsr_status gsr_render_backward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_c
   prof_begin(ctx, s);
   // The gradient rows are cleared inside the (otherwise empty) stages before
   // the backward rasteriser, so its stage times the kernel alone.
-  launch_fill_f32(reinterpret_cast<float *>(ws.grad2d), 0.f, 2 * p.n_rec * NGRAD2D, s);
+  launch_clear_grads(ws, p.n_rec, consts(*cfg, *g), s);
   for (int j = 0; j <= GSR_STAGE_RASTER; ++j) prof_mark(ctx, s, j);
   launch_render_backward(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), g_rgb, g_depth, g_T, s);
   prof_mark(ctx, s, GSR_STAGE_RASTER_BWD);
@@ -725,7 +730,7 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
     for (int r = 0; r <= reps && st == GSR_OK; ++r) {
       launch_fill_u32(ws.hdr + HDR_QUEUE, 0u, 1, s);
       if (t.lpt_order) launch_queue_order(ws, p.total_tiles, s);
-      launch_fill_f32(reinterpret_cast<float *>(ws.grad2d), 0.f, 2 * p.n_rec * NGRAD2D, s);
+      launch_clear_grads(ws, p.n_rec, consts(*cfg, *g), s);
       (void)hipEventRecord(e0, s);
       launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), target_rgb, target_depth,
                           pixel_mask, w_rgb, w_depth, nullptr, nullptr, t, ctx->num_cus, s);

@@ -12,7 +12,11 @@ namespace gsr {
 
 constexpr int TILE = 16;          // tile edge in pixels
 constexpr int BLOCK = 256;        // one thread per pixel of a tile
-constexpr int NGRAD2D = 10;       // u, v, conic a, b, c, opacity, r, g, b, depth
+constexpr int NGRAD2D = 10;       // 2D gradient fields: u, v, conic a, b, c, depth, opacity, r, g, b
+constexpr int GEO_FIELDS = 7;     // of these in a geometry row (GEO_ROW doubles, one cache line);
+constexpr int GEO_ROW = 8;        // the others in a colour row of COL_ROW
+constexpr int COL_ROW = 4;
+constexpr int REC_ROW = 4;        // float4s of a record (one cache line)
 constexpr int PRE_BLOCK = 512;    // records projected at a time by a projection block
 constexpr int PRE_ROUNDS_MAX = 4; // PRE_BLOCKs of records per block, at most
 constexpr int BIN_MAX = 4;        // largest bin edge S in tiles
@@ -120,10 +124,10 @@ constexpr uint32_t NO_BASE = 0xFFFFFFFFu;
 
 struct Workspace {
   uint32_t *hdr;
-  float4 *recA;            // [n_rec] (u_hi, u_lo, v_hi, v_lo)
-  float4 *recB;            // [n_rec] (conic a, b, c, opacity)
-  float4 *recC;            // [n_rec] (r, g, b, camera-frame depth)
-  uint32_t *count;         // [n_rec] tiles touched (0 = culled)
+  // [n_rec][REC_ROW]: (u_hi, u_lo, v_hi, v_lo), (conic a, b, c, opacity),
+  // (r, g, b, camera-frame depth), 0.
+  float4 *rec;
+  uint32_t *visible;       // [n_views][vis_words] bit i: record i of the view is not culled
   // Bin entries: each projection batch's, grouped by bin, from block_base on;
   // group_off[view][batch][bin] .. [bin + 1] is the bin's group among them.
   Entry *entries;          // [capacity]
@@ -136,7 +140,9 @@ struct Workspace {
   int32_t *last;           // [total_pixels]
   float *zr;               // [total_pixels] depth of the last blended entry (forward -> backward)
   unsigned long long *counts;  // [4] work totals (gsr_work_counts)
-  double *grad2d;          // [n_rec][NGRAD2D], FP64 sums over tiles
+  // FP64 sums over tiles: [n_rec][GEO_ROW] (a pose-only step touches only
+  // these) and [n_rec][COL_ROW].
+  double *grad2d, *grad_col;
   double *pose_part;       // [n_views][6][n_pose_blocks]
   uint32_t *queue;         // [total_tiles] work order of the persistent rasteriser
   unsigned long long *expand_bits;  // [chunks][8][4] adding step: one bit per pixel (ballot words)
@@ -158,10 +164,11 @@ struct Plan {
   int lds_bins = 0;        // bins that a projection block counts in LDS at a time
   int lists_cap = 0;       // bin entries that the lists kernel sorts at a time
   int n_pose_blocks = 0;
+  int64_t vis_words = 0;   // words of a view's visibility bits
   size_t bytes = 0;
   // byte offsets inside the workspace
-  size_t off_hdr, off_recA, off_recB, off_recC, off_count, off_entries, off_group, off_base, off_pairs, off_ids, off_ranges,
-      off_T, off_last, off_zr, off_grad2d, off_pose, off_queue, off_counts, off_tile_cost, off_expand_bits,
+  size_t off_hdr, off_rec, off_visible, off_entries, off_group, off_base, off_pairs, off_ids, off_ranges,
+      off_T, off_last, off_zr, off_grad2d, off_grad_col, off_pose, off_queue, off_counts, off_tile_cost, off_expand_bits,
       off_expand_cnt;
 };
 

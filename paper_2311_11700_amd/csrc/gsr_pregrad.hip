@@ -56,7 +56,7 @@ __device__ __forceinline__ void quat_rot_r(R w, R x, R y, R z, R M[9]) {
 
 // ----------------------------------------------------------------------------
 // Backward: per Gaussian, loop over the views, chain the per-view 2D
-// gradients (u, v, conic, opacity, colour, depth) through Eq. 3 to the
+// gradients (u, v, conic, depth, opacity, colour) through Eq. 3 to the
 // camera-frame point and to L = R_q diag(s) (Sigma = L L^T), accumulate
 // dL/dmean and dL/dL over the views, then chain dL/dL to the log-scales and
 // the quaternion once.  With P = J W (2x3) and T = P L the projected covariance
@@ -70,15 +70,15 @@ __device__ __forceinline__ void quat_rot_r(R w, R x, R y, R z, R M[9]) {
 // A block takes BLOCK Gaussians and `vpb` views: all of them when the
 // Gaussians' gradients are wanted (they are summed in registers), otherwise
 // POSE_VIEWS, so that the views spread over the chip.  Bound by the latency of
-// the dependent reads (visible counts, then the gradients of the records that
+// the dependent reads (visibility bits, then the gradients of the records that
 // are visible) and, over many views, by FP64 work in wavefronts of which a
-// quarter to a half of the lanes is visible.  The counts of VCHUNK views are
+// quarter to a half of the lanes is visible.  The bits of VCHUNK views are
 // read at a time and the next view's gradients ahead; the covariance form
 // (three 3x3 products more, 224 registers) took 755 us for the poses of 72
 // views of 500 000 Gaussians, 237 us for 16 views of a million, 11 us for the
-// pose of one view of 150 000: 415, 224 and 6.6 us now (300 000 Gaussians and
+// pose of one view of 150 000: 304, 205 and 6.5 us now (300 000 Gaussians and
 // one view 19 us before and after).  72, 16, 8 and 4 views a block for the 72:
-// 460, 412, 415 and 440 us.
+// 460, 412, 415 and 440 us (with 80-byte gradient rows).
 
 // SH: the colour is degree-1 spherical harmonics; GAUSS: the Gaussians'
 // gradients are wanted (instantiated separately for their registers).
@@ -87,7 +87,7 @@ constexpr int POSE_VIEWS = 8;  // views of a block without Gaussian gradients
 
 template <bool SH, bool GAUSS>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_preprocess_bwd(
-    gsr_gaussians g, const gsr_camera *__restrict__ cams, int n_views, int vpb, PreConstsB pc, Workspace ws,
+    gsr_gaussians g, const gsr_camera *__restrict__ cams, int n_views, int vpb, int64_t vis_words, PreConstsB pc, Workspace ws,
     gsr_grads gr) {
   extern __shared__ double s_dyn[];  // [4 waves][vpb][6]
   const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
@@ -150,22 +150,30 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
   for (int v0 = view0; v0 < view1; v0 += VCHUNK) {
     uint32_t visible = 0u;  // bit k: in view v0 + k
     {
-      uint32_t cnt[VCHUNK];
+      // (a word per wavefront and view)
+      const uint64_t *words = reinterpret_cast<const uint64_t *>(ws.visible) + blockIdx.x * (BLOCK / 64) + wave;
+      uint64_t w[VCHUNK];
 #pragma unroll
-      for (int k = 0; k < VCHUNK; ++k)
-        cnt[k] = active && v0 + k < view1 ? ws.count[(int64_t)(v0 + k) * g.n + i] : 0u;
+      for (int k = 0; k < VCHUNK; ++k) w[k] = v0 + k < view1 ? words[(int64_t)(v0 + k) * (vis_words / 2)] : 0ull;
 #pragma unroll
-      for (int k = 0; k < VCHUNK; ++k) visible |= cnt[k] != 0u ? 1u << k : 0u;
+      for (int k = 0; k < VCHUNK; ++k) visible |= (uint32_t)(w[k] >> lane & 1u) << k;
     }
     uint32_t todo = 0u;  // views in which some lane is visible
 #pragma unroll
     for (int k = 0; k < VCHUNK; ++k) todo |= __any((visible >> k) & 1u) ? 1u << k : 0u;
-    auto read = [&](int k, double2 d[NGRAD2D / 2]) {
-      const double2 *src = reinterpret_cast<const double2 *>(ws.grad2d + ((int64_t)(v0 + k) * g.n + i) * NGRAD2D);
+    constexpr bool COL = SH || GAUSS;  // the colour fields matter
+    constexpr int NG = GEO_ROW / 2, NC = COL ? COL_ROW / 2 : 0;
+    auto read = [&](int k, double2 d[NG + NC]) {
+      const int64_t rec = (int64_t)(v0 + k) * g.n + i;
+      const double2 *geo = reinterpret_cast<const double2 *>(ws.grad2d + rec * GEO_ROW);
+      const double2 *col = reinterpret_cast<const double2 *>(ws.grad_col + rec * COL_ROW);
+      const bool vis = (visible >> k) & 1u;
 #pragma unroll
-      for (int f = 0; f < NGRAD2D / 2; ++f) d[f] = (visible >> k) & 1u ? src[f] : make_double2(0., 0.);
+      for (int f = 0; f < NG - (COL ? 0 : 1); ++f) d[f] = vis ? geo[f] : make_double2(0., 0.);
+#pragma unroll
+      for (int f = 0; f < NC; ++f) d[NG + f] = vis ? col[f] : make_double2(0., 0.);
     };
-    double2 next[NGRAD2D / 2];
+    double2 next[NG + NC];
     if (todo) read(__builtin_ctz(todo), next);
     while (todo) {
       const int view = v0 + __builtin_ctz(todo);
@@ -173,10 +181,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
       R g2[NGRAD2D];
       bool has = false;
 #pragma unroll
-      for (int k = 0; k < NGRAD2D / 2; ++k) {
-        g2[2 * k] = next[k].x;
-        g2[2 * k + 1] = next[k].y;
-        has = has || next[k].x != 0. || next[k].y != 0.;
+      for (int f = 0; f < NGRAD2D; ++f) {
+        const int at = f < GEO_FIELDS ? f : GEO_ROW + f - GEO_FIELDS;
+        g2[f] = f < (COL ? NGRAD2D : 6) ? (at & 1 ? next[at >> 1].y : next[at >> 1].x) : 0.;
+        has = has || g2[f] != 0.;
       }
       // The next view's gradients are read while this one's are chained.
       if (todo) read(__builtin_ctz(todo), next);
@@ -184,8 +192,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
       R pr[6] = {0, 0, 0, 0, 0, 0};
       if (has) {
         if (GAUSS) {
-          gop += g2[5];
-          gc0 += g2[6]; gc1 += g2[7]; gc2 += g2[8];
+          gop += g2[6];
+          gc0 += g2[7]; gc1 += g2[8]; gc2 += g2[9];
         }
         const gsr_camera &cam = cams[view];
         R W[9];
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
           }
         }
         const R GJ00 = D0[0], GJ02 = D0[2], GJ11 = D1[1], GJ12 = D1[2];
-        const R gu = g2[0], gv = g2[1], gzd = g2[9];
+        const R gu = g2[0], gv = g2[1], gzd = g2[5];
         // Through the projected centre and depth.
         const R pX0 = gu * fx * iz;
         const R pX1 = gv * fy * iz;
@@ -287,7 +295,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
           const R il = R(1) / sqrt(vx * vx + vy * vy + vz * vz);
           const R dx = vx * il, dy = vy * il, dz = vz * il;
           const R Y[3] = {SH_C1 * dy, SH_C1 * dz, SH_C1 * dx};
-          const R gc[3] = {g2[6], g2[7], g2[8]};
+          const R gc[3] = {g2[7], g2[8], g2[9]};
           if (GAUSS) {
 #pragma unroll
             for (int k = 0; k < 3; ++k)
@@ -448,7 +456,7 @@ void launch_preprocess_backward(const Plan &p, const gsr_gaussians &g, const gsr
     const auto kernel = g.sh ? (gauss ? k_preprocess_bwd<true, true> : k_preprocess_bwd<true, false>)
                              : (gauss ? k_preprocess_bwd<false, true> : k_preprocess_bwd<false, false>);
     hipLaunchKernelGGL(kernel, dim3(p.n_pose_blocks, (unsigned)((p.n_views + vpb - 1) / vpb)), dim3(BLOCK), lds, s, g,
-                       cams, p.n_views, vpb, pc, ws, gr);
+                       cams, p.n_views, vpb, p.vis_words, pc, ws, gr);
   } else if (want_pose && overwrite) {
     // No Gaussian, no gradient: an overwritten pose gradient is zero.
     launch_fill_f32(gr.d_pose, 0.f, (int64_t)p.n_views * 6, s);

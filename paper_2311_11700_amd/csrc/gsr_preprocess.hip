@@ -21,7 +21,7 @@ struct PreConsts {
   float fov_guard;
   float alpha_min;
   double inv_alpha_min;
-  int clear_grad2d;  // zero each record's grad2d row (start of a fused step)
+  int clear_grads;  // zero each record's geometry row (1) or both gradient rows (2): start of a fused step
 };
 
 // Rotation matrix of a unit quaternion (w, x, y, z) (GS-SLAM supplement,
@@ -88,9 +88,8 @@ struct ProjArgs {
   gsr_gaussians g;
   ViewInfo vi;
   PreConsts pc;
-  float4 *recA, *recB, *recC;
-  uint32_t *count;
-  double *grad2d;
+  float4 *rec;
+  double *grad2d, *grad_col;
   int cull;
 };
 
@@ -196,15 +195,19 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
     }
   }
 
-  if (!ok) {
-    ws.count[rec] = 0u;
-    return false;
-  }
+  if (!ok) return false;
   // Only records that enter tile lists receive or give back 2D gradients.
-  if (pc.clear_grad2d) {
-    double2 *gz = reinterpret_cast<double2 *>(ws.grad2d + rec * NGRAD2D);
+  // (whole cache lines are written here and below, pads included: a line
+  // written in part is read first)
+  if (pc.clear_grads) {
+    double2 *gz = reinterpret_cast<double2 *>(ws.grad2d + rec * GEO_ROW);
 #pragma unroll
-    for (int k = 0; k < NGRAD2D / 2; ++k) gz[k] = make_double2(0.0, 0.0);
+    for (int k = 0; k < GEO_ROW / 2; ++k) gz[k] = make_double2(0.0, 0.0);
+    if (pc.clear_grads > 1) {
+      double2 *gc = reinterpret_cast<double2 *>(ws.grad_col + rec * COL_ROW);
+#pragma unroll
+      for (int k = 0; k < COL_ROW / 2; ++k) gc[k] = make_double2(0.0, 0.0);
+    }
   }
   const float zf = (float)z;
   const float uh = (float)u, vh = (float)v;
@@ -212,8 +215,6 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
   const float4 fa = make_float4(uh, (float)(u - (double)uh), vh, (float)(v - (double)vh));
   const double idet = 1.0 / det;
   const float4 fb = make_float4((float)(C * idet), (float)(-B * idet), (float)(A * idet), op);
-  ws.recA[rec] = fa;
-  ws.recB[rec] = fb;
   float fc0 = col[0], fc1 = col[1], fc2 = col[2];
   if constexpr (SH) {
     // Degree-1 spherical harmonics of the viewing direction d from the
@@ -233,7 +234,11 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
     fc1 = (float)c[1];
     fc2 = (float)c[2];
   }
-  ws.recC[rec] = make_float4(fc0, fc1, fc2, zf);
+  float4 *row = ws.rec + rec * REC_ROW;
+  row[0] = fa;
+  row[1] = fb;
+  row[2] = make_float4(fc0, fc1, fc2, zf);
+  row[3] = make_float4(0.f, 0.f, 0.f, 0.f);
   if (args->cull) {
     Support sp;
     if (!support_of(fa, fb, pc.inv_alpha_min, sp)) {
@@ -242,7 +247,6 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
     }
     *support = sp;
   }
-  ws.count[rec] = (uint32_t)(tx1 - tx0 + 1) * (uint32_t)(ty1 - ty0 + 1);
   out->a = fb.x;
   out->b = fb.y;
   out->c = fb.z;
@@ -271,7 +275,10 @@ __device__ __attribute__((noinline)) bool project_record(const ProjArgs *args, c
 // (2 048 records of 160x120 and 300 000 of 1200x680: 24 and 44 us before the
 // early test read its rounds together, rows and bin rows knew their record
 // without a search and the second sweep gave way to the list; 19 and 36 now),
-// by memory over many views (36 M records, 5 GB read and written: 1.9 ms).
+// by memory over many views: 36 M records in 72 views wrote 3.5 GB in 1.9 ms
+// with records in three arrays and gradient rows of 80 bytes (lines written in
+// part), and write 2.65 GB in 1.45 ms in whole cache lines with bits for the
+// visible ones.
 constexpr int ROW_CACHE = 3072;
 constexpr int UNIT_CACHE = 2048;  // bin rows whose record is kept
 
@@ -335,6 +342,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   __shared__ uint32_t s_rowat[PRE_BLOCK];  // first tile row of each record
   __shared__ uint32_t s_rows[ROW_CACHE];
   __shared__ uint16_t s_left[PRE_BLOCK * PRE_ROUNDS_MAX];  // records the early test leaves
+  __shared__ uint32_t s_visible[PRE_ROUNDS_MAX * PRE_BLOCK / 32];
   __shared__ uint32_t s_w[NW];
   __shared__ unsigned long long s_pairs[NW];
   __shared__ uint32_t s_base, s_nleft, s_nitem;
@@ -348,9 +356,10 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   // tiles its alpha support does not reach (none in the full-rectangle mode
   // or without an alpha threshold).
   const bool cull = !(pc.flags & GSR_FULL_RECT) && pc.alpha_min > 0.f;
+  if (threadIdx.x < PRE_ROUNDS_MAX * PRE_BLOCK / 32) s_visible[threadIdx.x] = 0u;
   if (threadIdx.x == 0) {
     s_nleft = 0u;
-    s_args = ProjArgs{g, vi, pc, ws.recA, ws.recB, ws.recC, ws.count, ws.grad2d, cull ? 1 : 0};
+    s_args = ProjArgs{g, vi, pc, ws.rec, ws.grad2d, ws.grad_col, cull ? 1 : 0};
   }
   __syncthreads();
   {
@@ -373,10 +382,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
       if (r >= rounds) break;
       const int64_t i = i0 + r * PRE_BLOCK + threadIdx.x;
       bool left = false;
-      if (i < g.n) {
-        left = !surely_culled(e[r], cam, vi, pc);
-        if (!left) ws.count[rec0 + i] = 0u;
-      }
+      if (i < g.n) left = !surely_culled(e[r], cam, vi, pc);
       const uint64_t m = __ballot(left);
       uint32_t at = 0u;
       if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&s_nleft, (uint32_t)__popcll(m));
@@ -398,8 +404,10 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     const int nrec = min(nleft - batch * PRE_BLOCK, PRE_BLOCK);
     bool vis = false;
     if (k < nleft) {
-      const int64_t i = i0 + (int)s_left[k];
+      const int local = s_left[k];
+      const int64_t i = i0 + local;
       vis = project_record<SH>(&s_args, &cam, i, rec0 + i, &s_rec[threadIdx.x], &s_u.support[threadIdx.x]);
+      if (vis) atomicOr(&s_visible[local >> 5], 1u << (local & 31));
     }
     uint32_t units, tile_rows;
     {
@@ -510,6 +518,9 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     }
     __syncthreads();  // the next batch takes the staging
   }
+  const int words = rounds * (PRE_BLOCK / 32);
+  if ((int)threadIdx.x < words)
+    ws.visible[(int64_t)blockIdx.x * words + threadIdx.x] = s_visible[threadIdx.x];
   for (int o = 32; o > 0; o >>= 1) pairs += __shfl_xor(pairs, o);
   if ((threadIdx.x & 63) == 0) s_pairs[wave] = pairs;
   __syncthreads();
@@ -520,9 +531,9 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
 }
 
 void launch_preprocess(const Plan &p, const gsr_gaussians &g, const gsr_camera *cams, const ViewInfo *views,
-                       const gsr_config &cfg, const Workspace &ws, bool clear_grad2d, hipStream_t s) {
+                       const gsr_config &cfg, const Workspace &ws, bool clear_grads, hipStream_t s) {
   PreConsts pc{cfg.z_near, cfg.lowpass, cfg.cutoff_sigma, cfg.flags, cfg.fov_guard, cfg.alpha_min,
-               cfg.alpha_min > 0.f ? 1.0 / (double)cfg.alpha_min : 0.0, clear_grad2d ? 1 : 0};
+               cfg.alpha_min > 0.f ? 1.0 / (double)cfg.alpha_min : 0.0, clear_grads ? ((cfg.flags & GSR_GAUSS_GRAD) || g.sh ? 2 : 1) : 0};
   if (g.n > 0)
     hipLaunchKernelGGL(g.sh ? k_preprocess<true> : k_preprocess<false>,
                        dim3((unsigned)(p.blocks_per_view * p.n_views)), dim3(PRE_BLOCK), (size_t)4 * p.lds_bins, s, g,

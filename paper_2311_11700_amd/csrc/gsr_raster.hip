@@ -70,13 +70,13 @@ __device__ __forceinline__ TileInfo tile_info(int tile, const ViewInfo *__restri
   return ti;
 }
 
-// Load record `id` into this thread's staging slot (three 16-byte loads).
-__device__ __forceinline__ Staged stage_record(uint32_t id, float x0, float y0, const float4 *__restrict__ recA,
-                                               const float4 *__restrict__ recB,
-                                               const float4 *__restrict__ recC) {
-  const float4 A = recA[id];
-  const float4 Bc = recB[id];
-  const float4 C = recC[id];
+// Load record `id` into this thread's staging slot (three 16-byte loads of one
+// cache line).
+__device__ __forceinline__ Staged stage_record(uint32_t id, float x0, float y0, const float4 *__restrict__ rec) {
+  const float4 *row = rec + (size_t)id * REC_ROW;
+  const float4 A = row[0];
+  const float4 Bc = row[1];
+  const float4 C = row[2];
   Staged s;
   // (u_hi - x0) is exact for |u_hi| < 2^24 and integer x0; the low word adds
   // the remaining bits.
@@ -158,9 +158,9 @@ struct FwdState {
 // Depth of list entry pos of the tile, from the staged batch that starts at
 // entry lo when it holds pos, else from the record.
 __device__ __forceinline__ float entry_depth(int pos, int lo, const Staged *s_rec, const TileInfo &ti,
-                                            const uint32_t *__restrict__ ids, const float4 *__restrict__ recC) {
+                                            const uint32_t *__restrict__ ids, const float4 *__restrict__ rec) {
   if (pos >= lo) return s_rec[pos - lo].geo.w;
-  return recC[ids[ti.range.x + pos]].w;
+  return rec[(size_t)ids[ti.range.x + pos] * REC_ROW + 2].w;
 }
 
 // With COUNT, the walk also adds its work to counts (wave totals, once per
@@ -168,9 +168,7 @@ __device__ __forceinline__ float entry_depth(int pos, int lo, const Staged *s_re
 // entry that stopped a pixel), counts[2] += entries blended.  The render
 // kernels do not count; gsr_work_counts re-walks the lists with counting on.
 template <bool COUNT, int NB = BATCH>
-__device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, const float4 *__restrict__ recA,
-                                             const float4 *__restrict__ recB,
-                                             const float4 *__restrict__ recC,
+__device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, const float4 *__restrict__ rec,
                                              const uint32_t *__restrict__ ids, const RenderConsts &rc,
                                              Staged *s_rec, FwdState &st, unsigned long long *counts,
                                              uint32_t *s_id = nullptr, int *staged_lo = nullptr) {
@@ -201,7 +199,7 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
     if ((int)threadIdx.x < cnt) {
       const uint32_t id = next_id;
       if (s_id) s_id[threadIdx.x] = id;
-      s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, recA, recB, recC);
+      s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, rec);
       if (pos + NB < ti.range.y) next_id = ids[pos + NB];
     } else if ((int)threadIdx.x < padded(cnt)) {
       s_rec[threadIdx.x] = empty_record();
@@ -285,7 +283,7 @@ __device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, cons
   if (staged_lo) *staged_lo = lo_last;
   // The reference depth: the last blended entry's, read once per pixel (an
   // entry was blended, so a batch was staged).
-  if (st.last > 0) st.zr = entry_depth(st.last - 1, lo_last, s_rec, ti, ids, recC);
+  if (st.last > 0) st.zr = entry_depth(st.last - 1, lo_last, s_rec, ti, ids, rec);
   if (COUNT && __lane_id() == 0 && nev_w) {
     atomicAdd(counts + 1, (unsigned long long)nev_w);
     atomicAdd(counts + 2, (unsigned long long)nbl_w);
@@ -497,7 +495,7 @@ __device__ __forceinline__ uint32_t backward_group(const Staged *s_rec, int slot
 // into the 2D gradients, added to grad2d with one FP64 atomic per field (a
 // Gaussian that covers many tiles sums partials of both signs; the FP64 sum
 // keeps the result independent of the order the tiles finish in).  grad2d
-// fields: (u, v, conic a, b, c, opacity, r, g, b, depth).
+// fields: (u, v, conic a, b, c, depth, opacity), grad_col: (r, g, b).
 //
 // Without BLO (the fused step) the upstream columns are the residual signs
 // in.sC / in.sD and the colour and depth sums are scaled by w_rgb and
@@ -505,11 +503,9 @@ __device__ __forceinline__ uint32_t backward_group(const Staged *s_rec, int slot
 // gradient) they are in.gC / in.gD themselves, split into high and low bf16
 // halves like the A values.
 template <bool BLO>
-__device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, const float4 *__restrict__ recA,
-                                              const float4 *__restrict__ recB,
-                                              const float4 *__restrict__ recC,
+__device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, const float4 *__restrict__ rec,
                                               const uint32_t *__restrict__ ids, const RenderConsts &rc,
-                                              const BwdIn &in, double *__restrict__ grad2d,
+                                              const BwdIn &in, double *__restrict__ grad2d, double *__restrict__ grad_col,
                                               Staged *s_rec, float *s_part, uint32_t *s_id, int *s_max,
                                               float *s_mA, int staged_lo = -1, float w_rgb = 1.f,
                                               float w_depth = 1.f) {
@@ -613,7 +609,7 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
       if ((int)threadIdx.x < cnt) {
         const uint32_t id = next_lo == lo ? next_id : ids[ti.range.x + lo + threadIdx.x];
         s_id[threadIdx.x] = id;
-        s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, recA, recB, recC);
+        s_rec[threadIdx.x] = stage_record(id, ti.x0, ti.y0, rec);
       } else if ((int)threadIdx.x < padded(cnt)) {
         s_rec[threadIdx.x] = empty_record();
       }
@@ -659,7 +655,7 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
     //   dL/da = -Sxx/2, dL/db = -Sxy, dL/dc = -Syy/2, dL/do = M1 / o.
     // Then the block adds them to grad2d field-parallel: consecutive lanes
     // take consecutive fields of one Gaussian, so each atomic instruction
-    // touches a few contiguous 80-byte rows.
+    // touches a few cache lines.
     double *s_out = reinterpret_cast<double *>(s_mA);  // [SUB][NGRAD2D], free during the flush
     if ((int)threadIdx.x < cnt) {
       // The four wavefronts' sums, added in a fixed order.
@@ -682,18 +678,20 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
       o[2] = -0.5 * Sxx;
       o[3] = -Sxy;
       o[4] = -0.5 * Syy;
-      o[5] = M1 / (double)sr.geo.z;
+      o[6] = M1 / (double)sr.geo.z;
       constexpr bool SCALED = !BLO;  // the upstream columns were the residual signs
-      o[6] = SCALED ? m[6] * (double)w_rgb : m[6];
-      o[7] = SCALED ? m[7] * (double)w_rgb : m[7];
-      o[8] = SCALED ? m[8] * (double)w_rgb : m[8];
-      o[9] = SCALED ? m[9] * (double)w_depth : m[9];
+      o[5] = SCALED ? m[9] * (double)w_depth : m[9];
+      o[7] = SCALED ? m[6] * (double)w_rgb : m[6];
+      o[8] = SCALED ? m[7] * (double)w_rgb : m[7];
+      o[9] = SCALED ? m[8] * (double)w_rgb : m[8];
     }
     __syncthreads();
     for (int t = threadIdx.x; t < cnt * NGRAD2D; t += BLOCK) {
       const int e = t / NGRAD2D, f = t - e * NGRAD2D;
       const double v = s_out[t];
-      if (v != 0.0 && ((rc.grad_fields >> f) & 1u)) atomicAdd(grad2d + (size_t)s_id[off + e] * NGRAD2D + f, v);
+      const size_t id = s_id[off + e];
+      double *to = f < GEO_FIELDS ? grad2d + id * GEO_ROW + f : grad_col + id * COL_ROW + (f - GEO_FIELDS);
+      if (v != 0.0 && ((rc.grad_fields >> f) & 1u)) atomicAdd(to, v);
     }
     __syncthreads();
   }
@@ -702,9 +700,7 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
 // ------------------------------------------------------------------ kernels
 
 struct RasterArgs {
-  const float4 *recA;
-  const float4 *recB;
-  const float4 *recC;  // (r, g, b, camera-frame depth) per record
+  const float4 *rec;
   const uint32_t *ids;
   const int2 *ranges;
   const ViewInfo *views;
@@ -715,7 +711,7 @@ struct RasterArgs {
 
 static RasterArgs raster_args(const Workspace &ws, const ViewInfo *views, const int32_t *tile_view,
                               const gsr_gaussians &g, const RenderConsts &rc) {
-  return RasterArgs{ws.recA, ws.recB, ws.recC, ws.ids, ws.ranges, views, tile_view, g.n, rc};
+  return RasterArgs{ws.rec, ws.ids, ws.ranges, views, tile_view, g.n, rc};
 }
 
 // Per-pixel forward state that a separate backward reads (the unfused
@@ -736,7 +732,7 @@ __global__ __launch_bounds__(BLOCK) void k_render_fwd(RasterArgs a, PixelState p
   __shared__ Staged s_rec[BATCH];
   const TileInfo ti = tile_info(blockIdx.x, a.views, a.tile_view, a.ranges);
   FwdState st;
-  tile_forward<false>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, s_rec, st, nullptr);
+  tile_forward<false>(ti, a.n, a.rec, a.ids, a.rc, s_rec, st, nullptr);
   if (!ti.inside) return;
   save_state(ps, ti.pix, st);
   const int64_t loc = ti.pix - ti.pix_off;
@@ -757,7 +753,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                                                       const float *__restrict__ g_rgb,
                                                       const float *__restrict__ g_depth,
                                                       const float *__restrict__ g_T,
-                                                      double *__restrict__ grad2d) {
+                                                      double *__restrict__ grad2d, double *__restrict__ grad_col) {
   // Without a forward in the same kernel the walk stages SUB entries at a time.
   __shared__ Staged s_rec[SUB];
   __shared__ float s_part[4 * SUB * NMOM];
@@ -778,7 +774,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     in.gD = g_depth ? g_depth[ti.pix] : 0.f;
     in.gT = g_T ? g_T[ti.pix] : 0.f;
   }
-  tile_backward<true>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id, s_max, s_mA);
+  tile_backward<true>(ti, a.n, a.rec, a.ids, a.rc, in, grad2d, grad_col, s_rec, s_part, s_id, s_max, s_mA);
 }
 
 __device__ __forceinline__ float sgnf(float x) { return (float)((x > 0.f) - (x < 0.f)); }
@@ -813,7 +809,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                                                         const uint8_t *__restrict__ pmask, float w_rgb,
                                                         float w_depth, const float *__restrict__ loss_cap,
                                                         gsr_images out, float *__restrict__ tile_loss,
-                                                        double *__restrict__ grad2d, PixelState ps,
+                                                        double *__restrict__ grad2d, double *__restrict__ grad_col, PixelState ps,
                                                         uint32_t *__restrict__ tile_cost) {
   __shared__ Staged s_rec[NB];
   __shared__ float s_part[4 * SUB * NMOM];
@@ -847,7 +843,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       FwdState st;
       int staged_lo;
-      tile_forward<false, NB>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, s_rec, st, nullptr, s_id,
+      tile_forward<false, NB>(ti, a.n, a.rec, a.ids, a.rc, s_rec, st, nullptr, s_id,
                           &staged_lo);
       BwdIn in{st.T, ti.inside ? st.last : 0, st.zr, 0.f, 0.f, 0.f, 0.f, 0.f};
       float lpx = 0.f;
@@ -887,7 +883,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       const float ls = wave_sum(lpx);
       if ((threadIdx.x & 63) == 0) s_loss[threadIdx.x >> 6] = ls;
-      tile_backward<false>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, in, grad2d, s_rec, s_part, s_id, s_max,
+      tile_backward<false>(ti, a.n, a.rec, a.ids, a.rc, in, grad2d, grad_col, s_rec, s_part, s_id, s_max,
                            s_mA, staged_lo, w_rgb, w_depth);
       if (threadIdx.x == 0) {
         tile_loss[tile] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
@@ -968,7 +964,7 @@ void launch_render_backward(const Plan &p, const Workspace &ws, const ViewInfo *
                             const float *g_rgb, const float *g_depth, const float *g_T, hipStream_t s) {
   const RasterArgs a = raster_args(ws, views, tile_view, g, rc);
   hipLaunchKernelGGL(k_render_bwd, dim3(p.total_tiles), dim3(BLOCK), 0, s, a, ws.T_final, ws.last, ws.zr, g_rgb,
-                     g_depth, g_T, ws.grad2d);
+                     g_depth, g_T, ws.grad2d, ws.grad_col);
 }
 
 void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *views,
@@ -987,7 +983,7 @@ void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *vie
   const uint32_t *queue = tun.lpt_order ? ws.queue : nullptr;
 #define GSR_LAUNCH_FUSED(NB_)                                                                                  \
   hipLaunchKernelGGL(k_render_fused<NB_>, dim3(grid), dim3(BLOCK), 0, s, a, ws.hdr, queue, p.total_tiles,            \
-                     tun.tiles_per_pop, t_rgb, t_depth, pmask, w_rgb, w_depth, loss_cap, o, ws.tile_loss, ws.grad2d, ps,      \
+                     tun.tiles_per_pop, t_rgb, t_depth, pmask, w_rgb, w_depth, loss_cap, o, ws.tile_loss, ws.grad2d, ws.grad_col, ps,      \
                      ws.tile_cost)
   switch (tun.batch) {
     case 64: GSR_LAUNCH_FUSED(64); break;
@@ -1010,7 +1006,7 @@ __global__ __launch_bounds__(BLOCK) void k_count_walk(RasterArgs a, const uint32
   __shared__ Staged s_rec[BATCH];
   const TileInfo ti = tile_info(blockIdx.x, a.views, a.tile_view, a.ranges);
   FwdState st;
-  tile_forward<true>(ti, a.n, a.recA, a.recB, a.recC, a.ids, a.rc, s_rec, st, counts);
+  tile_forward<true>(ti, a.n, a.rec, a.ids, a.rc, s_rec, st, counts);
   unsigned long long c = ti.inside ? (unsigned long long)st.last : 0ull;
   for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(counts + 3, c);
