@@ -136,8 +136,10 @@ def _cams_ptr(cams: torch.Tensor, n_views: int):
 
 
 def _stream_ptr(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # torch.cuda.current_stream().cuda_stream without the Python object (a few us a call)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class Renderer:
@@ -220,11 +222,15 @@ class Renderer:
                     T_final=torch.empty(P, device=self.device),
                     last=torch.empty(P, dtype=torch.int32, device=self.device) if last else None)
 
-    def new_grads(self, n: int, sh: bool = False):
-        """Zeroed gradient buffers; with `sh`, d_sh [n, 4, 3] in place of d_rgb."""
-        z = lambda *s: torch.zeros(*s, device=self.device)  # noqa: E731
+    def new_grads(self, n: int, sh: bool = False, written: int = 0):
+        """Zeroed gradient buffers; with `sh`, d_sh [n, 4, 3] in place of d_rgb.
+        Those that a backward with the flags `written` overwrites are left
+        uninitialised."""
+        over = written & A.GSR_GRAD_OVERWRITE
+        make = [torch.empty if over and written & f else torch.zeros for f in (A.GSR_GAUSS_GRAD, A.GSR_POSE_GRAD)]
+        z = lambda *s: make[0](*s, device=self.device)  # noqa: E731
         g = dict(d_mean=z(n, 3), d_log_scale=z(n, 3), d_quat=z(n, 4), d_opacity_logit=z(n),
-                 d_rgb=None if sh else z(n, 3), d_pose=z(self.n_views, 6))
+                 d_rgb=None if sh else z(n, 3), d_pose=make[1](self.n_views, 6, device=self.device))
         if sh:
             g["d_sh"] = z(n, 4, 3)
         return g
@@ -603,7 +609,12 @@ class _RenderFn(torch.autograd.Function):
         g_rgb = torch.zeros(3 * P, device=dev) if g_rgb is None else g_rgb.contiguous()
         g_depth = torch.zeros(P, device=dev) if g_depth is None else g_depth.contiguous()
         g_T = None if g_T is None else g_T.contiguous()
-        grads = r.render_backward(g, ctx.cams, ctx.cfg, g_rgb, g_depth, g_T, generation=ctx.generation)
+        # Fresh buffers: what the backward computes is written, not added (a
+        # zeroed buffer each and the chain's reads of them are six launches and
+        # 17 MB at 300 000 Gaussians); what it does not compute is zero.
+        cfg = dataclasses.replace(ctx.cfg, flags=ctx.cfg.flags | A.GSR_GRAD_OVERWRITE)
+        grads = r.new_grads(g.n, sh=g.sh is not None, written=cfg.flags)
+        r.render_backward(g, ctx.cams, cfg, g_rgb, g_depth, g_T, grads=grads, generation=ctx.generation)
         d_xi = r.pose_xi_grad(ctx.xi, grads["d_pose"])
         d_col = grads["d_sh"] if g.sh is not None else grads["d_rgb"]
         return (grads["d_mean"], grads["d_log_scale"], grads["d_quat"], grads["d_opacity_logit"], d_col,

@@ -43,3 +43,31 @@ def test_chain_over_views(gsr_lib, n, n_views):
         # The same FP64 sums in the same order, but for the order of the 2D
         # gradients' FP64 atomics: equal to a float32 rounding.
         np.testing.assert_allclose(alone[v], got["pose"][v], rtol=3e-7, atol=1e-7 * np.abs(got["pose"][v]).max())
+
+
+@pytest.mark.parametrize("which", ["gauss", "pose", "both"])
+def test_autograd_buffers_are_written(gsr_lib, which):
+    """The autograd backward's buffers: written where the flags ask for the
+    gradient and zero elsewhere, whatever their memory held before."""
+    import torch
+    gsr = gsr_lib
+    flags = dict(gauss=gsr.GSR_GAUSS_GRAD, pose=gsr.GSR_POSE_GRAD, both=gsr.GSR_GAUSS_GRAD | gsr.GSR_POSE_GRAD)[which]
+    n = 300
+    sc, cam = W.random_scene(n, seed=3, log_scale_mu=-2.0), W.camera_small().with_size(30.0, 30.0, 16.0, 12.0, 33, 25)
+    r = gsr.Renderer()
+    r.plan(n, [(33, 25)])
+    cams, cfg = gsr.pack_cameras([cam]), gsr.Config(flags=flags)
+    g = H.gpu_scene(gsr, sc)
+    leaves = [x.clone().requires_grad_() for x in (g.mean, g.log_scale, g.quat, g.opacity_logit, g.rgb)]
+    xi = torch.zeros(1, 6, device="cuda", requires_grad=True)
+    up = [H.to_dev(x) for x in H.flat_upstream([(33, 25)], seed=2)]
+    out = gsr.render(r, *leaves, cams, cfg, pose_xi=xi)
+    junk = [torch.full(s, float("nan"), device="cuda") for s in ((n, 3), (n, 3), (n, 4), (n,), (n, 3), (1, 6)) for _ in range(4)]
+    del junk  # the allocator hands these out next
+    got = torch.autograd.grad(out, [*leaves, xi], grad_outputs=up)
+    r.render_forward(g, cams, cfg)
+    ref = r.render_backward(g, cams, cfg, *up)
+    for a, k in zip(got, ("d_mean", "d_log_scale", "d_quat", "d_opacity_logit", "d_rgb", "d_pose")):
+        np.testing.assert_allclose(a.cpu().numpy(), ref[k].cpu().numpy(), rtol=1e-6, atol=1e-7 * float(ref[k].abs().max()))
+        asked = which == "both" or (k == "d_pose") == (which == "pose")
+        assert bool((a != 0).any()) == asked, k
