@@ -324,7 +324,16 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   p.n_rec = n * n_views;
   p.capacity = pair_capacity;
   std::vector<ViewInfo> views(n_views);
-  const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(PRE_ROUNDS_MAX, n * n_views / (PRE_BLOCK * 256)));
+  // Records of a projection block, in PRE_BLOCKs: more of them leave fuller
+  // batches behind the early test (many views see a small part of the scene
+  // each), but a block projects its batches one after the other.  Several
+  // views: about one block a CU before it takes more (three views of 100 000,
+  // two rounds 255 us, one 263).  One view, which may see all of its Gaussians:
+  // one round up to 1.2 M (fused step at 1200x680, all in view: 300 000 two
+  // rounds 255 us, one 240; 500 000 three rounds 300, one 281; a million four
+  // 393, one 382; with 43 % in view 259 and 260, 308 and 288, 544 and 512).
+  const int64_t per_round = PRE_BLOCK * (n_views > 1 ? 256 : 1200);
+  const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(PRE_ROUNDS_MAX, n * n_views / per_round));
   const int64_t bpv = (n + PRE_BLOCK * rounds - 1) / (PRE_BLOCK * rounds);
   int64_t tiles = 0, pixels = 0, bins = 0, mat = 0, most = 0;
   int max_bins = 1;

@@ -71,8 +71,7 @@ constexpr uint32_t HDR_MAGIC0 = 0x67737248u, HDR_MAGIC1 = 0x2311B700u;
 // contiguous run of tiles: the x-range of the ellipse within the row's band
 // of pixel-centre rows [16 ty, 16 ty + 15], mapped to the columns whose
 // pixel centres [16 tx, 16 tx + 15] it overlaps.  Every input is a stored
-// float32 value (centre as hi + lo, conic, opacity), so the projection
-// kernel (parameters) and the emission kernel (per-pair test) agree with an
+// float32 value (centre as hi + lo, conic, opacity), so the runs agree with an
 // FP64 reference evaluated in the same order.
 struct Support {
   double U, V, t, hy, dys, ra;  // centre, level, half-height, dy of the rightmost point, 1 / a
