@@ -4,10 +4,9 @@
 Headline: forward + L1 loss + backward (all Gaussian parameters and the se(3)
 pose) of 300k Gaussians at 1200x680 in a room-shaped synthetic scene,
 reported as Mpixel/s.  One step = one launch of the HIP graph that holds the
-whole fused step (projection, depth sort, pair emission, tile sort, ranges,
-persistent forward/L1/backward rasteriser, chain to parameters and pose),
-plus zeroing the gradient buffers.  Also reported: per-stage times and the
-roofline of the dominant kernel (from an eager, event-timed loop of the same
+whole fused step (projection, tile lists, persistent forward/L1/backward
+rasteriser, chain to parameters and pose), which overwrites the gradient
+buffers.  Also reported: per-stage times and the roofline of the dominant kernel (from an eager, event-timed loop of the same
 step), the backward composite's algorithmic bytes against the copy-measured
 achievable HBM bandwidth, the batched 16-keyframe launch against 16
 per-frame launches, 72 pose hypotheses in one launch against 72 calls, the
