@@ -210,7 +210,7 @@ void launch_clear_grads(const Workspace &ws, int64_t n_rec, const RenderConsts &
 void enqueue_lists(gsr_ctx *ctx, const gsr_gaussians &g, const gsr_camera *cams, const gsr_config &cfg,
                    Workspace &ws, bool clear_grad2d, bool order_queue, hipStream_t s) {
   const Plan &p = ctx->plan;
-  launch_lists_begin(ws, s);
+  if (g.n == 0) launch_lists_begin(ws, s);
   launch_preprocess(p, g, cams, ctx->views_dev, cfg, ws, clear_grad2d, s);
   prof_mark(ctx, s, GSR_STAGE_PREPROCESS);
   prof_mark(ctx, s, GSR_STAGE_DEPTH_SORT);

@@ -49,9 +49,11 @@ void launch_fill_f32(float *ptr, float value, int64_t count, hipStream_t s) {
 
 // ----------------------------------------------------------------- header
 
-// Start of a call: the header's per-call words and the entry cursor.
+// Start of a call without Gaussians; otherwise the projection does it.
 __global__ void k_lists_begin(uint32_t *__restrict__ hdr) {
-  if (threadIdx.x == 0) reset_header_words(hdr);
+  if (threadIdx.x != 0) return;
+  reset_header_words(hdr);
+  *entry_cursor(hdr) = ENTRY_TAG;
 }
 
 void launch_lists_begin(const Workspace &ws, hipStream_t s) {
@@ -465,7 +467,17 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
     if (threadIdx.x == 0) {
       for (int w = 1; w < LW; ++w) x += part[w];
       *reinterpret_cast<unsigned long long *>(ws.hdr + HDR_NPAIRS) = x;
-      if (x > cap_pairs) {
+      // Entries are no more than pairs: a count above the capacity with fewer
+      // pairs did not start at 0 (a call that ended between the projection and
+      // here, a word overwritten).  It is reported as an overflow, and the next
+      // call starts clean.  No tag in a workspace never used: no entries.
+      const unsigned long long cur = read_entry_cursor(ws.hdr);
+      const bool tagged = (cur & ~ENTRY_COUNT_MASK) == ENTRY_TAG;
+      const unsigned long long used = tagged || header_used(ws.hdr) ? cur - ENTRY_TAG : 0ull;
+      *entry_cursor(ws.hdr) = ENTRY_TAG;
+      ws.hdr[HDR_MAGIC] = HDR_MAGIC0;
+      ws.hdr[HDR_MAGIC + 1] = HDR_MAGIC1;
+      if (x > cap_pairs || used > cap_pairs) {
         unsigned long long *req = reinterpret_cast<unsigned long long *>(ws.hdr + HDR_REQUIRED);
         ws.hdr[HDR_OVERFLOW] = 1u;
         if (x > *req) *req = x;

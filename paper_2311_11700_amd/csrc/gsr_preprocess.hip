@@ -345,7 +345,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   __shared__ uint32_t s_visible[PRE_ROUNDS_MAX * PRE_BLOCK / 32];
   __shared__ uint32_t s_w[NW];
   __shared__ unsigned long long s_pairs[NW];
-  __shared__ uint32_t s_base, s_nleft, s_nitem;
+  __shared__ uint32_t s_base, s_nleft, s_nitem, s_used;
   const int view = blockIdx.x / bpv, blk = blockIdx.x - view * bpv;
   const ViewInfo vi = views[view];
   const gsr_camera &cam = cams[view];
@@ -358,6 +358,8 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   const bool cull = !(pc.flags & GSR_FULL_RECT) && pc.alpha_min > 0.f;
   if (threadIdx.x < PRE_ROUNDS_MAX * PRE_BLOCK / 32) s_visible[threadIdx.x] = 0u;
   if (threadIdx.x == 0) {
+    s_used = header_used(ws.hdr) ? 1u : 0u;
+    if (blockIdx.x == 0) reset_header_words(ws.hdr);  // (read by the kernels behind this one)
     s_nleft = 0u;
     s_args = ProjArgs{g, vi, pc, ws.rec, ws.grad2d, ws.grad_col, cull ? 1 : 0};
   }
@@ -497,8 +499,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
           row[nb] = carry;
           uint32_t base = NO_BASE;
           if (carry > 0u) {
-            const unsigned long long at =
-                atomicAdd(reinterpret_cast<unsigned long long *>(ws.hdr + HDR_ENTRIES), (unsigned long long)carry);
+            const unsigned long long at = reserve_entries(ws.hdr, s_used != 0u, carry);
             if (at + carry <= cap) base = (uint32_t)at;
           }
           ws.block_base[group] = base;

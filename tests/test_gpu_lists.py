@@ -127,3 +127,56 @@ def test_lists_of_wide_gaussians(gsr_lib, n):
     tiles = np.random.default_rng(n).choice(proj["TX"] * proj["TY"], 80, replace=False).tolist()
     _, n_gpu, _ = H.check_view_lists(rng, ids, 0, 0, proj, O.tile_lists(proj), *size, ocfg, tiles=tiles)
     assert n_gpu > 0
+
+
+@pytest.mark.parametrize("fill", ["zeros", "ones", "random", "stale", "stale_full", "no_tag"])
+def test_lists_in_a_workspace_of_any_contents(gsr_lib, fill):
+    """A workspace's first call, whatever its memory held, and a call behind one
+    that left the entries' cursor (words 32-33: a tag above a count) above 0:
+    the same lists, or the overflow report once when the count leaves no room."""
+    import torch
+    gsr = gsr_lib
+    n, size = 20_000, (96, 64)
+    sc, cam = W.random_scene(n, seed=4), W.camera_small().with_size(70.0, 70.0, 47.5, 31.5, *size)
+    r = gsr.Renderer()
+    r.plan(n, [size], pair_capacity=400_000)
+    g, cams, cfg = H.gpu_scene(gsr, sc), gsr.pack_cameras([cam]), gsr.Config()
+    r.render_forward(g, cams, cfg)
+    pairs = r.pair_count()
+    want = [x.numpy() for x in r.debug_tiles()]
+    words = r.workspace.view(torch.int32)
+    count = {"stale": 1234, "stale_full": 400_000, "no_tag": -(0xA53C7 << 44)}.get(fill)
+    for again in range(3):
+        if count is None and again == 0:
+            r.workspace.view(torch.uint8).copy_({
+                "zeros": torch.zeros_like, "ones": lambda t: torch.full_like(t, 255),
+                "random": lambda t: torch.randint(0, 256, t.shape, dtype=torch.uint8, device=t.device)}[fill](
+                    r.workspace.view(torch.uint8)))
+        elif count is not None and again == 0:
+            cursor = (0xA53C7 << 44) + count
+            words[32] = cursor & 0x7FFFFFFF
+            words[33] = (cursor >> 32) - 2**32 if cursor >> 63 else cursor >> 32
+        r.render_forward(g, cams, cfg, check=False)
+        torch.cuda.synchronize()
+        if fill in ("stale_full", "no_tag") and again == 0:
+            with pytest.raises(gsr.GsrError):
+                r.check_overflow()
+            continue
+        r.check_overflow()
+        assert r.pair_count() == pairs
+        got = [x.numpy() for x in r.debug_tiles()]
+        assert np.array_equal(got[0], want[0])
+        assert np.array_equal(got[1][:want[0][-1, 1]], want[1][:want[0][-1, 1]])
+
+
+def test_no_entries_in_a_workspace_never_used(gsr_lib):
+    """Nothing in view and garbage in the header: no overflow, empty lists."""
+    import torch
+    gsr = gsr_lib
+    sc, cam = W.random_scene(500, seed=4), W.camera_small()
+    sc.mean[:, 2] -= 50.0
+    r = gsr.Renderer()
+    r.plan(500, [(cam.width, cam.height)])
+    r.workspace.view(torch.uint8).fill_(255)
+    out = r.render_forward(H.gpu_scene(gsr, sc), gsr.pack_cameras([cam]), gsr.Config())
+    assert r.pair_count() == 0 and float(out["T_final"].min()) == 1.0
