@@ -204,8 +204,9 @@ int64_t gsr_forward_generation(const gsr_ctx *ctx);
  * depth and final-transmittance outputs.  forward_generation must be the
  * gsr_forward_generation() value of the forward whose state the workspace
  * holds, i.e. of the last forward on this context, on this workspace, with no
- * fused step, autotune or plan since; otherwise GSR_E_STATE (the state of an
- * earlier forward has been overwritten).  Accumulates into `grads` according
+ * fused step, autotune or plan since, nor a replay of a graph captured on this
+ * workspace; otherwise GSR_E_STATE (the state of an earlier forward has been
+ * overwritten).  Accumulates into `grads` according
  * to cfg->flags.  Asynchronous. */
 gsr_status gsr_render_backward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *cams,
                                int n_views, const gsr_config *cfg, void *workspace,
@@ -270,7 +271,8 @@ gsr_status gsr_render_l1_fused_noalloc(gsr_ctx *ctx, const gsr_gaussians *g, con
 
 /* Capture gsr_render_l1_fused with these exact arguments (pointers and
  * scalar values are baked in; buffer CONTENTS may change between launches)
- * into a HIP graph owned by the context, replacing any earlier capture. */
+ * into a HIP graph owned by the context, replacing any earlier capture.  A
+ * later gsr_plan drops the graph (gsr_graph_launch then returns GSR_E_STATE). */
 gsr_status gsr_graph_capture(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *cams,
                              int n_views, const gsr_config *cfg, const float *target_rgb,
                              const float *target_depth, const uint8_t *pixel_mask, float w_rgb,

@@ -25,6 +25,7 @@ struct gsr_ctx {
   Tuning tuning;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
+  const void *graph_ws = nullptr;  // workspace that the captured step fills
   const void *last_forward_ws = nullptr;
   int64_t fwd_generation = 0;  // successful gsr_render_forward calls on this context
   // Counters of gsr_loss_median, allocated by gsr_plan for plans with a large
@@ -70,6 +71,15 @@ gsr_status fail(gsr_ctx *ctx, gsr_status st, const std::string &msg) {
 gsr_status hip_check(gsr_ctx *ctx, hipError_t e, const char *what) {
   if (e == hipSuccess) return GSR_OK;
   return fail(ctx, GSR_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
+}
+
+// Drops the captured graph: its kernels hold the plan's tables and layout.
+void drop_graph(gsr_ctx *ctx) {
+  if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
+  if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
+  ctx->gexec = nullptr;
+  ctx->graph = nullptr;
+  ctx->graph_ws = nullptr;
 }
 
 gsr_status last_launch(gsr_ctx *ctx, const char *what) {
@@ -299,8 +309,7 @@ gsr_status gsr_create(int device, gsr_ctx **out) {
 
 void gsr_destroy(gsr_ctx *ctx) {
   if (!ctx) return;
-  if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
-  if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
+  drop_graph(ctx);
   if (ctx->views_dev) (void)hipFree(ctx->views_dev);
   if (ctx->tile_view_dev) (void)hipFree(ctx->tile_view_dev);
   if (ctx->median_dev) (void)hipFree(ctx->median_dev);
@@ -415,6 +424,8 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   ctx->tile_view_dev = nullptr;
   ctx->median_dev = nullptr;
   ctx->planned = false;
+  // (hipFree above has waited for replays in flight)
+  drop_graph(ctx);
   int64_t largest_view = 0;
   for (const ViewInfo &vi : views) largest_view = std::max<int64_t>(largest_view, (int64_t)vi.W * vi.H);
   std::vector<int32_t> tv(tiles + bins);
@@ -604,10 +615,7 @@ gsr_status gsr_graph_capture(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_cam
   if (st != GSR_OK) return st;
   if (!stream) return fail(ctx, GSR_E_INVALID, "gsr_graph_capture needs a non-null stream");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
-  if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
-  ctx->gexec = nullptr;
-  ctx->graph = nullptr;
+  drop_graph(ctx);
   st = hip_check(ctx, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
   if (st != GSR_OK) return st;
   Workspace ws = make_ws(ctx->plan, workspace);
@@ -627,13 +635,16 @@ gsr_status gsr_graph_capture(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_cam
   }
   ctx->graph = graph;
   ctx->gexec = exec;
+  ctx->graph_ws = workspace;
   ctx->last_forward_ws = nullptr;
   return GSR_OK;
 }
 
 gsr_status gsr_graph_launch(gsr_ctx *ctx, gsr_stream stream) {
   if (!ctx) return GSR_E_INVALID;
-  if (!ctx->gexec) return fail(ctx, GSR_E_STATE, "no captured graph");
+  if (!ctx->gexec) return fail(ctx, GSR_E_STATE, "no captured graph (gsr_plan drops it)");
+  // The replay overwrites the state that a forward left in its workspace.
+  if (ctx->last_forward_ws == ctx->graph_ws) ctx->last_forward_ws = nullptr;
   return hip_check(ctx, hipGraphLaunch(ctx->gexec, static_cast<hipStream_t>(stream)), "hipGraphLaunch");
 }
 
