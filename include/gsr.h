@@ -332,7 +332,8 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
  * float bits).  cap_out is DEVICE float [n_views], the loss_cap argument of
  * the next step.  Asynchronous; calls on several streams of one context take
  * turns where a view has more than 32768 pixels (they share counters of the
- * context, which a captured call does not use). */
+ * context, which a captured call does not use: there, and on the null stream
+ * while another stream is captured, one block counts a view of any size). */
 gsr_status gsr_loss_median(gsr_ctx *ctx, const float *px_loss, const uint8_t *pixel_mask, float factor,
                            float *cap_out, gsr_stream stream);
 

@@ -536,9 +536,14 @@ gsr_status gsr_loss_median(gsr_ctx *ctx, const float *px_loss, const uint8_t *pi
   uint32_t *scratch = ctx->median_dev;
   if (scratch) {
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    gsr_status st = hip_check(ctx, hipStreamIsCapturing(s, &capturing), "hipStreamIsCapturing");
-    if (st != GSR_OK) return st;
-    if (capturing != hipStreamCaptureStatusNone) scratch = nullptr;
+    if (hipStreamIsCapturing(s, &capturing) != hipSuccess) {
+      // The null stream while a stream that waits for it is captured: a kernel
+      // may be launched there, an event neither awaited nor recorded.
+      (void)hipGetLastError();
+      scratch = nullptr;
+    } else if (capturing != hipStreamCaptureStatusNone) {
+      scratch = nullptr;
+    }
   }
   if (scratch) {
     gsr_status st = hip_check(ctx, hipStreamWaitEvent(s, ctx->median_done, 0), "hipStreamWaitEvent");
