@@ -206,7 +206,11 @@ int64_t gsr_forward_generation(const gsr_ctx *ctx);
  * holds, i.e. of the last forward on this context, on this workspace, with no
  * fused step, autotune or plan since, nor a replay of a graph captured on this
  * workspace; otherwise GSR_E_STATE (the state of an earlier forward has been
- * overwritten).  Accumulates into `grads` according
+ * overwritten).  A g_rgb, g_depth or g_T that is not finite at one pixel
+ * reaches the gradients of the Gaussians that the pixel blends and, for g_rgb
+ * and g_depth, that channel's gradient (resp. the one of the depth, which
+ * enters d_mean and d_pose) of the others blended in the same four rows of the
+ * pixel's tile.  Accumulates into `grads` according
  * to cfg->flags.  Asynchronous. */
 gsr_status gsr_render_backward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *cams,
                                int n_views, const gsr_config *cfg, void *workspace,

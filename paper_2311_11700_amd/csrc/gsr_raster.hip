@@ -490,6 +490,49 @@ __device__ __forceinline__ uint32_t backward_group(const Staged *s_rec, int slot
   return used;
 }
 
+// A dLdP or w that is not finite would reach every sum of its entry, and those
+// of entries that its pixel does not blend: 0 times it, in a lane without a
+// contribution or beside a 0 of B, is NaN.  So in a wild wavefront (see
+// tile_backward) they are taken out of the group's rows in front of the
+// contraction, and the sums that they belong to are made NaN behind it.
+// Bits 8 + e and 16 + e of the result: the dLdP, resp. w, of entry e was not
+// finite at some pixel, the dLdP at one that blends it.  (Found again here, so
+// that the walk itself pays one test a group.  A step over three ragged views,
+// whose longest tile is the tail of the step: 282 us without the test, 286 with
+// it, 297 with the selects in the walk, 303 with a second loop over the groups,
+// which spills 50 registers; 300 000 Gaussians at 1200x680: 257.5, 256.4, 258.6,
+// 280 us.)
+__device__ __forceinline__ uint32_t clean_rows(const Staged *s_rec, int slot, int first, const RenderConsts &rc,
+                                               const BwdPixel &px, uint32_t *rows) {
+  uint32_t bad = 0u;
+#pragma unroll 1
+  for (int e = 0; e < BGROUP; ++e) {
+    const Staged *r = s_rec + slot + e;
+    float oG;
+    const float alpha = splat_alpha(r->geo, *reinterpret_cast<const float3 *>(&r->con), r->geo.x - px.lx,
+                                    r->geo.y - px.ly, rc.alpha_max, oG);
+    const bool has = first + e < px.last && alpha >= rc.alpha_min;
+    const uint32_t h = rows[2 * e * MA_STRIDE], l = rows[(2 * e + 1) * MA_STRIDE];
+    auto wrong = [](uint32_t x, uint32_t exponent) { return (x & exponent) == exponent; };
+    const bool p = wrong(h, 0x7F80u) || wrong(l, 0x7F80u), w = wrong(h, 0x7F800000u) || wrong(l, 0x7F800000u);
+    const uint32_t keep = (p ? 0u : 0xFFFFu) | (w ? 0u : 0xFFFF0000u);
+    rows[2 * e * MA_STRIDE] = h & keep;
+    rows[(2 * e + 1) * MA_STRIDE] = l & keep;
+    bad |= (__builtin_amdgcn_ballot_w64(p && has) != 0 ? 0x100u << e : 0u) |
+           (__builtin_amdgcn_ballot_w64(w) != 0 ? 0x10000u << e : 0u);
+  }
+  return bad;
+}
+
+// The sums of a group whose clean_rows gave the bits of bad: moments from dLdP,
+// the others from w.
+__device__ __forceinline__ void spoil_sums(uint32_t bad, float *sum) {
+  for (int k = __lane_id(); k < BGROUP * NMOM; k += 64) {
+    const int e = k / NMOM, f = k - e * NMOM;
+    if (bad >> ((f < 6 ? 8 : 16) + e) & 1u) sum[k] = __builtin_nanf("");
+  }
+}
+
 // Walk the tile's list back to front; per entry, dLdP and w of every pixel
 // go through the contraction above, and the flush turns the per-entry sums
 // into the 2D gradients, added to grad2d with one FP64 atomic per field (a
@@ -591,6 +634,12 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
   px.last = in.last;
   px.lx = lx;
   px.ly = ly;
+  // Wild: some pixel's upstream gradient is infinite or NaN (or so large that a
+  // product might be), or its transmittance has reached 0, which the walk
+  // divides.  Only the sums of the Gaussians that the pixel blends may see it,
+  // and of these only the ones that it enters.
+  const bool wild = __builtin_amdgcn_ballot_w64(!(fabsf(px.gC0) + fabsf(px.gC1) + fabsf(px.gC2) + fabsf(px.gD) +
+                                                  fabsf(px.Kf) < 1e30f) || !(px.T > 0.f)) != 0;
 
   // Sub-batches [b SUB, (b + 1) SUB), walked from the last one that holds
   // an entry below maxlast.  Those inside the forward's last batch (still
@@ -636,13 +685,18 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
       uint32_t *rows = reinterpret_cast<uint32_t *>(mA);
       for (int q = ng - 1; q >= 0; --q) {
         const int first = lo + q * BGROUP;
-        const uint32_t now =
+        uint32_t now =
             backward_group(s_rec, off + q * BGROUP, first, first + BGROUP <= wmin, rc, px, rows + lane, g);
         if (q < ng - 1) store_sums(D, used, my_part + (q + 1) * BGROUP * NMOM);
+        if (__builtin_expect(wild, false)) {
+          if (q < ng - 1) spoil_sums(used, my_part + (q + 1) * BGROUP * NMOM);
+          now |= clean_rows(s_rec, off + q * BGROUP, first, rc, px, rows + lane);
+        }
         D = contract<BLO>(rows, Bb, Bl);
         used = now;
       }
       store_sums(D, used, my_part);
+      if (__builtin_expect(wild, false)) spoil_sums(used, my_part);
     }
     __syncthreads();
     // Flush.  First one thread per Gaussian of the batch converts its sums:
