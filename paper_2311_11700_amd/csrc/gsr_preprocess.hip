@@ -39,18 +39,32 @@ __device__ __forceinline__ void quat_rot(T w, T x, T y, T z, T R[9]) {
   R[8] = T(1) - T(2) * (x * x + y * y);
 }
 
+// Upper bound of the squared spectral norm of the view's matrix W: the largest
+// row sum of |W W^T|.  1 for a rotation; the projection takes W as it is, a
+// similarity's scale or a drifted product of rotations too.
+__device__ __forceinline__ float norm2_bound(const float *W) {
+  float g[3][3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      g[i][j] = fabsf(W[3 * i] * W[3 * j] + W[3 * i + 1] * W[3 * j + 1] + W[3 * i + 2] * W[3 * j + 2]);
+  return fmaxf(fmaxf(g[0][0] + g[0][1] + g[0][2], g[1][0] + g[1][1] + g[1][2]), g[2][0] + g[2][1] + g[2][2]);
+}
+
 // Whether record i of the view is certainly culled: masked, not beyond the near
 // plane, or its tile rectangle empty.  The rectangle's half-width is
-// cutoff sqrt(A) with A <= |J_0|^2 max(scale)^2 + lowpass; the bound is
+// cutoff sqrt(A) with A <= |J_0|^2 |W|^2 max(scale)^2 + lowpass; the bound is
 // evaluated in float32 with margins far above its rounding, and any
-// comparison with a NaN keeps the record for the exact tests.
+// comparison with a NaN keeps the record for the exact tests.  norm2: at least
+// |W|^2.
 struct Early {
   float m[3], ls[3];  // mean, log scales
   uint8_t keep;       // mask
 };
 
 __device__ __forceinline__ bool surely_culled(const Early &e, const gsr_camera &cam, const ViewInfo &vi,
-                                              const PreConsts &pc) {
+                                              const PreConsts &pc, float norm2) {
   if (e.keep == 0) return true;
   const double mx = e.m[0], my = e.m[1], mz = e.m[2];
   const double x = (((double)cam.R[0] * mx + (double)cam.R[1] * my) + (double)cam.R[2] * mz) + (double)cam.t[0];
@@ -67,8 +81,8 @@ __device__ __forceinline__ bool surely_culled(const Early &e, const gsr_camera &
     ty = fminf(ty, pc.fov_guard * (0.5f * (float)vi.H) / cam.fy * 1.001f);
   }
   const float jx = cam.fx * rz, jy = cam.fy * rz;
-  const float rx = pc.cutoff * sqrtf(jx * jx * (1.f + tx * tx) * smax * smax + fabsf(pc.lowpass));
-  const float ry = pc.cutoff * sqrtf(jy * jy * (1.f + ty * ty) * smax * smax + fabsf(pc.lowpass));
+  const float rx = pc.cutoff * sqrtf(jx * jx * (1.f + tx * tx) * smax * smax * norm2 + fabsf(pc.lowpass));
+  const float ry = pc.cutoff * sqrtf(jy * jy * (1.f + ty * ty) * smax * smax * norm2 + fabsf(pc.lowpass));
   const float u = cam.fx * xz + cam.cx, v = cam.fy * yz + cam.cy;
   const float mu = rx * 1.001f + 1e-4f * (fabsf(u) + fabsf(cam.cx)) + 0.5f;
   const float mv = ry * 1.001f + 1e-4f * (fabsf(v) + fabsf(cam.cy)) + 0.5f;
@@ -365,6 +379,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   }
   __syncthreads();
   {
+    const float norm2 = norm2_bound(cam.R);
     // (the reads of all rounds are in flight together)
     Early e[PRE_ROUNDS_MAX];
 #pragma unroll
@@ -384,7 +399,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
       if (r >= rounds) break;
       const int64_t i = i0 + r * PRE_BLOCK + threadIdx.x;
       bool left = false;
-      if (i < g.n) left = !surely_culled(e[r], cam, vi, pc);
+      if (i < g.n) left = !surely_culled(e[r], cam, vi, pc, norm2);
       const uint64_t m = __ballot(left);
       uint32_t at = 0u;
       if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&s_nleft, (uint32_t)__popcll(m));
