@@ -810,7 +810,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                                                       double *__restrict__ grad2d, double *__restrict__ grad_col) {
   // Without a forward in the same kernel the walk stages SUB entries at a time.
   __shared__ Staged s_rec[SUB];
-  __shared__ float s_part[4 * SUB * NMOM];
+  __shared__ __align__(16) float s_part[4 * SUB * NMOM];
   __shared__ uint32_t s_id[SUB];
   __shared__ int s_max[4];
   __shared__ __align__(16) float s_mA[4 * MA_WAVE];
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                                                         double *__restrict__ grad2d, double *__restrict__ grad_col, PixelState ps,
                                                         uint32_t *__restrict__ tile_cost) {
   __shared__ Staged s_rec[NB];
-  __shared__ float s_part[4 * SUB * NMOM];
+  __shared__ __align__(16) float s_part[4 * SUB * NMOM];
   __shared__ uint32_t s_id[NB];
   __shared__ int s_max[4];
   __shared__ __align__(16) float s_mA[4 * MA_WAVE];
