@@ -115,6 +115,7 @@ Workspace make_ws(const Plan &p, void *base_v) {
   w.block_base = reinterpret_cast<uint32_t *>(base + p.off_base);
   w.block_pairs = reinterpret_cast<unsigned long long *>(base + p.off_pairs);
   w.ids = reinterpret_cast<uint32_t *>(base + p.off_ids);
+  w.shared_place = reinterpret_cast<unsigned long long *>(base + p.off_shared);
   w.ranges = reinterpret_cast<int2 *>(base + p.off_ranges);
   w.T_final = reinterpret_cast<float *>(base + p.off_T);
   w.last = reinterpret_cast<int32_t *>(base + p.off_last);
@@ -376,6 +377,12 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   p.total_bins = (int)bins;
   p.lds_bins = std::min(max_bins, LDS_BINS_MAX);
   p.lists_cap = (int)std::min<int64_t>(LISTS_CAP_MAX, std::max<int64_t>(LISTS_CAP_MIN, (3 * most + 1023) / 1024 * 1024));
+  // Bins no more than CUs: a block has a CU's LDS to itself.
+  if (bins + 2 <= ctx->num_cus) p.lists_cap = LISTS_CAP_MAX;
+  // Blocks that help with crowded bins, where a bin can be (it has n entries at
+  // most): a CU's worth of them for one view, fewer where each of many views has
+  // its own.  (They hold an estimate per bin in the LDS of the entries.)
+  if (n > p.lists_cap && bins * 4 <= (int64_t)p.lists_cap * LISTS_ENTRY_BYTES) p.lists_helpers = ctx->num_cus / n_views;
   p.blocks_per_view = (int)bpv;
   p.pre_rounds = rounds;
   p.n_pose_blocks = (int)std::max<int64_t>(1, (n + BLOCK - 1) / BLOCK);
@@ -395,6 +402,7 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   p.off_base = take(4 * pre_blocks * rounds);
   p.off_pairs = take(8 * pre_blocks);
   p.off_ids = take(4 * cap);
+  p.off_shared = take(p.lists_helpers > 0 ? 8 * (size_t)p.total_bins : 0);
   p.off_ranges = take(8 * (size_t)p.total_tiles);
   p.off_T = take(4 * (size_t)pixels);
   p.off_last = take(4 * (size_t)pixels);

@@ -135,6 +135,9 @@ struct Entry {
   uint32_t key, id, mask;
 };
 constexpr uint32_t NO_BASE = 0xFFFFFFFFu;
+// (a block has at most 2 048 records of 2^24 tiles, and 512 entries of a batch in a bin)
+constexpr int PAIRS_BITS = 48;
+constexpr unsigned long long PAIRS_MASK = (1ull << PAIRS_BITS) - 1ull;
 
 struct Workspace {
   uint32_t *hdr;
@@ -147,8 +150,10 @@ struct Workspace {
   Entry *entries;          // [capacity]
   uint32_t *group_off;
   uint32_t *block_base;    // [projection batches] (NO_BASE: none, or past the capacity)
-  unsigned long long *block_pairs;  // [projection blocks] pairs (rectangle tiles) of the block's records
+  unsigned long long *block_pairs;  // [projection blocks] pairs (rectangle tiles) of the block's records, and from
+                                    // PAIRS_BITS on the entries of its largest group
   uint32_t *ids;           // [capacity] record ids of the tile lists
+  unsigned long long *shared_place;  // [total_bins] place of a bin's lists that several blocks write (0: none yet)
   int2 *ranges;            // [total_tiles]
   float *T_final;          // [total_pixels]
   int32_t *last;           // [total_pixels]
@@ -177,11 +182,12 @@ struct Plan {
   int total_bins = 0;
   int lds_bins = 0;        // bins that a projection block counts in LDS at a time
   int lists_cap = 0;       // bin entries that the lists kernel sorts at a time
+  int lists_helpers = 0;   // blocks of the lists kernel beside the bins' own, for crowded bins
   int n_pose_blocks = 0;
   int64_t vis_words = 0;   // words of a view's visibility bits
   size_t bytes = 0;
   // byte offsets inside the workspace
-  size_t off_hdr, off_rec, off_visible, off_entries, off_group, off_base, off_pairs, off_ids, off_ranges,
+  size_t off_hdr, off_rec, off_visible, off_entries, off_group, off_base, off_pairs, off_ids, off_shared, off_ranges,
       off_T, off_last, off_zr, off_grad2d, off_grad_col, off_pose, off_queue, off_counts, off_tile_cost, off_expand_bits,
       off_expand_cnt;
 };
@@ -211,6 +217,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += __shfl_xor(v, 2);
   v += __shfl_xor(v, 1);
   return v;
+}
+
+// Maximum over the wavefront of v >= 0, in a scalar register.
+__device__ __forceinline__ int wave_max(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // row_shr:1
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));  // row_shr:2
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));  // row_shr:4
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));  // row_shr:8
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ bool header_used(const uint32_t *hdr) {

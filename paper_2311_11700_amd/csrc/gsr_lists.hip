@@ -71,9 +71,10 @@ void launch_lists_begin(const Workspace &ws, hipStream_t s) {
 // leaves about one entry a slot, and one thread orders the few that share one.
 // Depths that crowd even there (a slot over LSLOT) take stable
 // least-significant-digit passes over the differing bits instead, and equal
-// depths are put in index order afterwards.  A bin with more than `cap`
-// entries is taken in rounds of consecutive key ranges.  A tile's list is the
-// sorted entries whose mask has the tile's bit: per row of 64 entries one
+// depths are put in index order afterwards (entries of a single depth are sorted
+// by their index at once).  A bin with more than `cap` entries is taken in
+// rounds of consecutive key ranges, which several blocks share (see "crowded
+// bins").  A tile's list is the sorted entries whose mask has the tile's bit: per row of 64 entries one
 // ballot gives the tile's entries and each lane's place, so consecutive lanes
 // write consecutive words.
 //
@@ -83,7 +84,7 @@ void launch_lists_begin(const Workspace &ws, hipStream_t s) {
 // slots, 8 for the masks and 21 to write.  It takes 51 us with the group table
 // read at once and four groups in flight (13), up to four entries of a slot
 // ordered in registers (8), id and mask read together, and the places counted
-// from the tile's next one in the lanes' registers (12): 5 512 bins 1.65 -> 1.2
+// from the tile's next one in the lanes' registers (12): 5 512 bins 1.65 -> 1.14
 // ms, the 209 bins of 2 500 of a 1200x680 view 39 -> 33 us.
 constexpr int LB = 1024;         // threads
 constexpr int LW = LB / 64;      // wavefronts
@@ -93,6 +94,7 @@ constexpr int LRUN = 24;         // longest run of equal depths that one thread 
 constexpr int LPARTS = 4096;     // parts of the depth range
 constexpr uint32_t LSLOT = 24;   // most entries of a slot that one thread orders
 constexpr int NTILE = BIN_MAX * BIN_MAX;
+constexpr int LBOUNDS = 256;     // rounds that one histogram gives the ends of
 static_assert(LPARTS <= LISTS_CAP_MIN, "the rounds' histogram takes the keys' place");
 
 // Arrays of `cap` entries in dynamic LDS.
@@ -111,6 +113,10 @@ struct ListsLds {
   uint32_t w[LW];
   uint32_t tile[LW][NTILE];    // per-wavefront entries of each tile, then their first places
   uint32_t next[NTILE];        // next place of each tile's list
+  uint32_t total[NTILE], before[NTILE];  // a crowded bin's entries of each tile, and those in front of the round
+  uint16_t bound[LBOUNDS];     // ends of its rounds
+  uint32_t bounds;
+  uint32_t share[3];           // crowd_share's answer
   uint32_t kmin, kmax, n, most, end;
 };
 
@@ -353,7 +359,7 @@ __device__ __forceinline__ int for_entries(ListsLds &s, const Workspace &ws, con
     __syncthreads();
     const int ng = min(LB, groups - g0);
     for (int t0 = threadIdx.x / LTEAM; t0 < ng; t0 += TEAMS * LUNROLL) {
-      uint32_t e[LUNROLL], q[LUNROLL], left[LUNROLL];
+      uint32_t e[LUNROLL], q[LUNROLL], left[LUNROLL], most = 0u;
       decltype(load(0u)) v[LUNROLL];
 #pragma unroll
       for (int u = 0; u < LUNROLL; ++u) {
@@ -365,6 +371,7 @@ __device__ __forceinline__ int for_entries(ListsLds &s, const Workspace &ws, con
           e[u] = g.x + sub;
           q[u] = g.y + sub;
           left[u] = next > q[u] ? next - q[u] : 0u;
+          most = max(most, left[u]);
         }
       }
 #pragma unroll
@@ -372,10 +379,16 @@ __device__ __forceinline__ int for_entries(ListsLds &s, const Workspace &ws, con
         if (left[u]) v[u] = load(e[u]);
 #pragma unroll
       for (int u = 0; u < LUNROLL; ++u)
-        if (left[u]) {
-          use(q[u], e[u], v[u]);
-          for (uint32_t k = LTEAM; k < left[u]; k += LTEAM) use(q[u] + k, e[u] + k, load(e[u] + k));
-        }
+        if (left[u]) use(q[u], e[u], v[u]);
+      // What longer groups have left.
+      for (uint32_t k = LTEAM; k < most; k += LTEAM) {
+#pragma unroll
+        for (int u = 0; u < LUNROLL; ++u)
+          if (k < left[u]) v[u] = load(e[u] + k);
+#pragma unroll
+        for (int u = 0; u < LUNROLL; ++u)
+          if (k < left[u]) use(q[u] + k, e[u] + k, v[u]);
+      }
     }
   }
   __syncthreads();
@@ -450,16 +463,215 @@ __device__ __forceinline__ void write_lists(const ListsLds &s, const ListsArrays
   }
 }
 
+// order_masks and write_lists by the bin's edge.
+__device__ __forceinline__ void masks_of(int shift, ListsLds &s, const ListsArrays &a, const Entry *entries, int n, int I,
+                                         int at) {
+  if (shift == 2) order_masks<16>(s, a, entries, n, I, at);
+  else if (shift == 1) order_masks<4>(s, a, entries, n, I, at);
+  else order_masks<1>(s, a, entries, n, I, at);
+}
+
+__device__ __forceinline__ void lists_of(int shift, const ListsLds &s, const ListsArrays &a, uint32_t *ids, int n, int I,
+                                         int at) {
+  if (shift == 2) write_lists<16>(s, a, ids, n, I, at);
+  else if (shift == 1) write_lists<4>(s, a, ids, n, I, at);
+  else write_lists<1>(s, a, ids, n, I, at);
+}
+
+// Exclusive scan over the tiles (lanes below NTILE of a whole wavefront; the
+// other lanes have v = 0), and the sum.
+__device__ __forceinline__ uint32_t tile_scan(uint32_t v, uint32_t &all) {
+  const int lane = threadIdx.x & 63;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < NTILE; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  all = __shfl(x, NTILE - 1);
+  return x - v;
+}
+
+// ---------------------------------------------------------- crowded bins
+//
+// A map seen from afar lies in a few bins, which then have hundreds of
+// thousands of entries.  Each pass over them is the work of one block, but the
+// rounds are independent once their ends are known, so they are shared: the
+// plan adds blocks behind the bins' own (lists_helpers) that look for crowded
+// bins.  A helper finds the bin's entries, the rounds' ends and the tiles'
+// totals for itself, as the bin's own block does, and takes every parts-th
+// round.  What they must agree on depends on the entries alone, but for the
+// place of the lists (shared_reserve).
+//
+// Bound by what one CU reads: a pass over 120 000 entries takes a block 60 to
+// 80 us (25 GB/s), and a block makes three, for the keys, the histogram and its
+// round; a round of 12 288 is sorted and written in 55.  Lists of 400 000 and
+// 1.6 M Gaussians in four bins of 640x480: 3.1 and 57 ms by one block a bin with
+// two passes for every round, 0.41 and 1.4 ms so.  A forward of a million at a
+// quarter, a tenth and a twentieth of the view's width 3.6, 14 and 26 ms -> 0.78,
+// 1.27 and 2.8 (by radix passes over all pairs 0.89, 1.25, 3.9); with all of
+// them in view, where every bin has 1.3 rounds, 405 -> 343 us.
+
+// Entries of each tile of the bin among a thread's own.
+__device__ __forceinline__ void count_mask(uint32_t c[NTILE], uint32_t mask) {
+#pragma unroll
+  for (int t = 0; t < NTILE; ++t) c[t] += (mask >> t) & 1u;
+}
+
+// to[] += the block's counts (by all threads).
+__device__ __forceinline__ void add_counts(const uint32_t c[NTILE], uint32_t to[NTILE]) {
+#pragma unroll
+  for (int t = 0; t < NTILE; ++t) {
+    int x = (int)c[t];
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    if ((threadIdx.x & 63) == 63 && x) atomicAdd(&to[t], (uint32_t)x);
+  }
+}
+
+// Ends of the rounds (s.bound, in parts) by one wavefront: rounds of about equal
+// size, cap entries at most, up to a part that alone has more than cap.
+// front[]: entries in front of each part, s.end: of all.
+__device__ __forceinline__ void round_ends(ListsLds &s, const uint32_t *front, int cap) {
+  const int lane = threadIdx.x;
+  const uint32_t total = s.end;
+  const auto at = [&](int p) { return p < LPARTS ? front[p] : total; };
+  const uint32_t rounds = (total + (uint32_t)cap - 1u) / (uint32_t)cap;
+  // (a sixteenth more than an equal share, lest what the parts leave over makes
+  // a round of its own)
+  const uint32_t even = rounds ? total / rounds + total / (16u * rounds) + 64u : 0u;
+  int start = 0, bounds = 0;
+  while (start < LPARTS && bounds < LBOUNDS) {
+    int q = start;
+    for (uint32_t most = min(even, (uint32_t)cap);; most = (uint32_t)cap) {
+      // Last part boundary q with at most that many entries between start and
+      // it: 64 boundaries 64 apart, then the 64 from there on.  (The counts
+      // ascend: those in front of the first that fails.)
+      const uint32_t limit = at(start) + most;
+#pragma unroll
+      for (int step = 64; step > 0; step /= 64) {
+        const int p = q + (lane + 1) * step;
+        q += step * __popcll(__ballot(p <= LPARTS && at(p) <= limit));
+      }
+      if (q > start || most == (uint32_t)cap) break;
+    }
+    if (q == start) break;
+    if (lane == 0) s.bound[bounds] = (uint16_t)q;
+    ++bounds;
+    start = q;
+  }
+  if (lane == 0) s.bounds = (uint32_t)bounds;
+}
+
+// Helpers and their bins.  Every block that asks finds the same: the entries of
+// each bin are estimated from some of its view's groups, a bin that may be
+// crowded asks for as many blocks as it has rounds, and the helpers are dealt
+// out in the order of the bins.  The estimate decides on speed alone.  For
+// helper number `idx` (want < 0) returns its bin, -1 for none; for the bin
+// `want` itself; with the block's part of how many.
+constexpr int CROWD_WORDS = 65536;  // of the group table, read by a block at most (but for 8 groups a view)
+__device__ __forceinline__ int crowd_share(ListsLds &s, uint32_t *est, const Workspace &ws,
+                                           const ViewInfo *__restrict__ views, const int32_t *__restrict__ bin_view,
+                                           int total_bins, int groups, int cap, int helpers, int want, int idx, int &part,
+                                           int &parts) {
+  const int sample = min(groups, max(8, min(64, CROWD_WORDS / total_bins)));
+  const int slices = max(1, min(sample, LB / total_bins));
+  for (int b = threadIdx.x; b < total_bins; b += LB) est[b] = 0u;
+  if (threadIdx.x == 0) s.share[0] = 0xFFFFFFFFu;
+  __syncthreads();
+  for (int t = threadIdx.x; t < total_bins * slices; t += LB) {
+    const int b = t % total_bins, view = bin_view[b];
+    const ViewInfo &vi = views[view];
+    const int stride = vi.BX * vi.BY + 1;
+    const uint32_t *row0 = ws.group_off + vi.mat_off + (b - vi.bin_off);
+    const uint32_t *bases = ws.block_base + (size_t)view * groups;
+    uint32_t sum = 0u;
+#pragma unroll 4
+    for (int j = t / total_bins; j < sample; j += slices) {
+      const int g = (int)((int64_t)j * groups / sample);
+      const uint32_t *row = row0 + (int64_t)g * stride;
+      const uint32_t base = bases[g], r0 = row[0], r1 = row[1];
+      sum += base != NO_BASE ? r1 - r0 : 0u;
+    }
+    if (sum) atomicAdd(&est[b], sum);
+  }
+  __syncthreads();
+  // Blocks that a bin asks for beside its own.
+  const auto asked = [&](int b) {
+    const uint64_t e = (uint64_t)est[b] * (uint32_t)groups / (uint32_t)sample;
+    return (uint32_t)min((e + (e >> 3) + (uint64_t)cap - 1ull) / (uint32_t)cap, (uint64_t)helpers + 1ull);
+  };
+  const int per = (total_bins + LB - 1) / LB;
+  const int b0 = min((int)threadIdx.x * per, total_bins), b1 = min(b0 + per, total_bins);
+  uint32_t sum = 0u, all, dealt;
+  for (int b = b0; b < b1; ++b) {
+    const uint32_t k = asked(b);
+    sum += k > 1u ? k - 1u : 0u;
+  }
+  (void)block_exclusive_scan<LB>(sum, s.w, all);
+  const auto gets = [&](int b) {
+    const uint32_t k = asked(b), more = k > 1u ? k - 1u : 0u;
+    return all > (uint32_t)helpers ? (uint32_t)((uint64_t)more * (uint32_t)helpers / all) : more;
+  };
+  sum = 0u;
+  for (int b = b0; b < b1; ++b) sum += gets(b);
+  uint32_t first = block_exclusive_scan<LB>(sum, s.w, dealt);
+  for (int b = b0; b < b1; ++b) {
+    const uint32_t k = gets(b);
+    if (want < 0 ? (uint32_t)idx - first < k : b == want) {
+      s.share[0] = (uint32_t)b;
+      s.share[1] = want < 0 ? (uint32_t)idx - first + 1u : 0u;
+      s.share[2] = k + 1u;
+    }
+    first += k;
+  }
+  __syncthreads();
+  part = (int)s.share[1];
+  parts = (int)s.share[2];
+  return (int)s.share[0];
+}
+
+// Place of the lists of a bin that several blocks write.  The first of them that
+// comes to shared_reserve (one thread, once the tiles' totals are known) takes
+// it and tells the others in shared_place: 0 before that, 1 while it is taken,
+// then the place + 2, or NO_PLACE past the capacity.  shared_wait, needed a
+// collecting pass and a sort later, hardly ever waits, and always ends: 1 was
+// written by a block that is running and waits for nothing before the place
+// follows.  Relaxed atomics do: the words carry all that is told.  (Acquire and
+// release at device scope write back and invalidate the L2 under the other
+// blocks' reads and writes, and a chain of compare-and-swaps on one word, which
+// needs no wait, takes 1.4 us a bin: 990 and 660 us for 209 bins.)
+constexpr unsigned long long NO_PLACE = ~0ull;
+
+__device__ __forceinline__ void shared_reserve(const Workspace &ws, int bin, uint32_t all, unsigned long long cap_pairs) {
+  unsigned long long *word = ws.shared_place + bin;
+  if (atomicCAS(word, 0ull, 1ull) != 0ull) return;
+  const unsigned long long first =
+      atomicAdd(reinterpret_cast<unsigned long long *>(ws.hdr + HDR_NLISTED), (unsigned long long)all);
+  (void)atomicExch(word, first + all <= cap_pairs ? first + 2ull : NO_PLACE);
+}
+
+__device__ __forceinline__ unsigned long long shared_wait(const Workspace &ws, int bin) {
+  unsigned long long v;
+  while ((v = __hip_atomic_load(ws.shared_place + bin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < 2ull)
+    __builtin_amdgcn_s_sleep(4);
+  return v == NO_PLACE ? NO_PLACE : v - 2ull;
+}
+
 __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ views,
                                                   const int32_t *__restrict__ bin_view, Workspace ws, int64_t n_gauss,
                                                   int id_bits, int groups, int pre_blocks, unsigned long long cap_pairs,
-                                                  int cap, int order_total) {
+                                                  int cap, int order_total, int total_bins, int helpers) {
   extern __shared__ uint32_t dyn[];
   __shared__ ListsLds s;
   if (blockIdx.x == 0) {
     // The pair count, and the overflow record when it exceeds the capacity.
     unsigned long long x = 0ull;
-    for (int j = threadIdx.x; j < pre_blocks; j += LB) x += ws.block_pairs[j];
+    for (int j = threadIdx.x; j < pre_blocks; j += LB) x += ws.block_pairs[j] & PAIRS_MASK;
     unsigned long long *part = reinterpret_cast<unsigned long long *>(s.part);
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
@@ -497,7 +709,17 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
   a.at = dyn + cap;
   a.from = reinterpret_cast<uint16_t *>(dyn + 2 * cap);
   a.to = a.from + cap;
-  const int bin = blockIdx.x - 2;
+  // Blocks behind the bins' help with the crowded ones.
+  int bin = (int)blockIdx.x - 2, part = 0, parts = 1;
+  const bool helper = bin >= total_bins;
+  if (helper) {
+    // No bin has more entries than its view's groups times the largest of them.
+    uint32_t most = 0u;
+    for (int j = threadIdx.x; j < pre_blocks; j += LB) most = max(most, (uint32_t)(ws.block_pairs[j] >> PAIRS_BITS));
+    if (!__syncthreads_or((uint64_t)most * (uint32_t)groups > (uint32_t)cap)) return;
+    bin = crowd_share(s, dyn, ws, views, bin_view, total_bins, groups, cap, helpers, -1, bin - total_bins, part, parts);
+    if (bin < 0) return;
+  }
   const int view = bin_view[bin];
   const ViewInfo vi = views[view];
   const int shift = vi.bin_shift, S = 1 << shift, nt = S * S;
@@ -538,126 +760,44 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
     }
   }
   __syncthreads();
-  if (E == 0) {
-    if (my_tile) ws.ranges[tile] = make_int2(0, 0);
-    return;
-  }
-  const bool all_fit = E <= cap;
-  const uint32_t kmin = s.kmin, kmax = s.kmax;
-  if (!all_fit) {
-    // The tiles' totals, needed before the first round writes.
-    if (threadIdx.x < NTILE) s.next[threadIdx.x] = 0u;
-    __syncthreads();
-    for_entries(
-        s, ws, vi, view, local, groups, [&](uint32_t e) { return entries[e].mask; },
-        [&](uint32_t, uint32_t, uint32_t mask) {
-          for (uint32_t m = mask; m; m &= m - 1u) atomicAdd(&s.next[__ffs(m) - 1], 1u);
-        });
-    __syncthreads();
-  }
-
-  // Rounds over consecutive ranges [lo, hi) of the unique key (depth, record
-  // id) with at most cap entries each; one round when all entries fit.
-  const uint64_t end = ((uint64_t)kmax << 32 | 0xFFFFFFFFull) + 1ull;  // depth keys are below 2^31
-  uint64_t lo = (uint64_t)kmin << 32;
-  for (bool placed = false; lo < end;) {
-    uint64_t hi = end;
-    int n = E;
-    if (!all_fit) {
-      // The range's end comes from a histogram over LPARTS equal parts of
-      // what is left; a part that alone exceeds cap is divided again.
-      uint32_t *hist = a.key;
-      int sh = 0;
-      while ((end - lo) >> sh > (uint64_t)LPARTS) ++sh;
-      for (;;) {
-        __syncthreads();
-        for (int b = threadIdx.x; b < LPARTS; b += LB) hist[b] = 0u;
-        if (threadIdx.x == 0) s.n = (uint32_t)LPARTS;
-        __syncthreads();
-        for_entries(
-            s, ws, vi, view, local, groups,
-            [&](uint32_t e) { return (uint64_t)entries[e].key << 32 | entries[e].id; },
-            [&](uint32_t, uint32_t, uint64_t k) {
-              if (k >= lo && (k - lo) >> sh < (uint64_t)LPARTS) atomicAdd(&hist[(k - lo) >> sh], 1u);
-            });
-        __syncthreads();
-        // Parts in order while their sum fits: the first part whose
-        // inclusive sum exceeds cap ends the range.
-        constexpr int PER = LPARTS / LB;
-        uint32_t sum = 0u, total;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) sum += hist[threadIdx.x * PER + k];
-        uint32_t run = block_exclusive_scan<LB>(sum, s.w, total);
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-          const uint32_t h = hist[threadIdx.x * PER + k];
-          if (run <= (uint32_t)cap && run + h > (uint32_t)cap) s.n = threadIdx.x * PER + k;
-          run += h;
-        }
-        __syncthreads();
-        const uint32_t parts = s.n;
-        if (parts > 0u) {
-          hi = lo + ((uint64_t)parts << sh);
-          break;
-        }
-        sh = sh > 12 ? sh - 12 : 0;  // (at sh = 0 a part is one key, which one entry has)
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) s.n = 0u;
-      __syncthreads();
-      for_entries(
-          s, ws, vi, view, local, groups,
-          [&](uint32_t e) { return (uint64_t)entries[e].key << 32 | entries[e].id; },
-          [&](uint32_t, uint32_t e, uint64_t k) {
-            if (k >= lo && k < hi) {
-              const uint32_t q = atomicAdd(&s.n, 1u);
-              a.key[q] = (uint32_t)(k >> 32);
-              a.at[q] = e;
-            }
-          });
-      __syncthreads();
-      n = (int)s.n;
+  if (E <= cap) {
+    if (helper) return;
+    if (E == 0) {
+      if (my_tile) ws.ranges[tile] = make_int2(0, 0);
+      return;
     }
-    const uint32_t key0 = (uint32_t)(lo >> 32), key1 = min((uint32_t)((hi - 1ull) >> 32), kmax);
-    lo = hi;
-    if (n == 0) continue;
-    const int I = (n + LB - 1) / LB;
+    uint32_t key0 = s.kmin, key1 = s.kmax;
+    if (key0 == key1) {
+      // One depth: by index.
+      for (int q = threadIdx.x; q < E; q += LB) a.key[q] = entries[a.at[q]].id;
+      key0 = id0;
+      key1 = id0 + (uint32_t)n_gauss - 1u;
+      __syncthreads();
+    }
+    const int I = (E + LB - 1) / LB;
     const int at = wave * 64 * I + lane;
-    sort_entries(s, a, n, I, at, key0, key1 <= key0 ? 0 : 32 - __clz(key1 - key0), entries, id0, id_bits);
-    if (shift == 2) order_masks<16>(s, a, entries, n, I, at);
-    else if (shift == 1) order_masks<4>(s, a, entries, n, I, at);
-    else order_masks<1>(s, a, entries, n, I, at);
+    sort_entries(s, a, E, I, at, key0, key1 == key0 ? 0 : 32 - __clz(key1 - key0), entries, id0, id_bits);
+    masks_of(shift, s, a, entries, E, I, at);
     __syncthreads();
     if (threadIdx.x < 64) {
-      uint32_t mine = 0u;
+      uint32_t tot = 0u;
       if (lane < nt) {
 #pragma unroll
-        for (int w = 0; w < LW; ++w) mine += s.tile[w][lane];
+        for (int w = 0; w < LW; ++w) tot += s.tile[w][lane];
       }
-      uint32_t place = 0u;
-      if (!placed) {
-        // The bin's lists take consecutive places, tile after tile, reserved
-        // with one add on the listed-pair count.  Past the capacity (an
-        // overflow) they stay empty.
-        const uint32_t tot = all_fit ? mine : lane < NTILE ? s.next[lane] : 0u;
-        uint32_t x = tot;
-#pragma unroll
-        for (int o = 1; o < NTILE; o <<= 1) {
-          const uint32_t y = __shfl_up(x, o);
-          if (lane >= o) x += y;
-        }
-        const uint32_t all = __shfl(x, NTILE - 1);
-        unsigned long long first = 0ull;
-        if (lane == 0)
-          first = atomicAdd(reinterpret_cast<unsigned long long *>(ws.hdr + HDR_NLISTED), (unsigned long long)all);
-        first = __shfl(first, 0);
-        const bool fits = first + all <= cap_pairs;
-        place = (uint32_t)first + x - tot;
-        if (lane == 0) s.most = fits ? 0u : 0xFFFFFFFFu;
-        if (my_tile) ws.ranges[tile] = fits ? make_int2((int)place, (int)(place + tot)) : make_int2(0, 0);
-      } else if (lane < nt) {
-        place = s.next[lane];
-      }
+      // The bin's lists take consecutive places, tile after tile, reserved
+      // with one add on the listed-pair count.  Past the capacity (an
+      // overflow) they stay empty.
+      uint32_t all;
+      const uint32_t pre = tile_scan(tot, all);
+      unsigned long long first = 0ull;
+      if (lane == 0)
+        first = atomicAdd(reinterpret_cast<unsigned long long *>(ws.hdr + HDR_NLISTED), (unsigned long long)all);
+      first = __shfl(first, 0);
+      const bool fits = first + all <= cap_pairs;
+      uint32_t place = (uint32_t)first + pre;
+      if (lane == 0) s.most = fits ? 0u : 0xFFFFFFFFu;
+      if (my_tile) ws.ranges[tile] = fits ? make_int2((int)place, (int)(place + tot)) : make_int2(0, 0);
       if (lane < nt) {
 #pragma unroll
         for (int w = 0; w < LW; ++w) {
@@ -665,16 +805,153 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
           s.tile[w][lane] = place;
           place += k;
         }
-        s.next[lane] = place;
       }
     }
     __syncthreads();
-    if (!placed && s.most == 0xFFFFFFFFu) return;
-    placed = true;
-    if (shift == 2) write_lists<16>(s, a, ws.ids, n, I, at);
-    else if (shift == 1) write_lists<4>(s, a, ws.ids, n, I, at);
-    else write_lists<1>(s, a, ws.ids, n, I, at);
-    __syncthreads();
+    if (s.most == 0xFFFFFFFFu) return;
+    lists_of(shift, s, a, ws.ids, E, I, at);
+    return;
+  }
+
+  // A crowded bin: its rounds, every parts-th of them from `part` on.
+  if (!helper) {
+    part = 0;
+    parts = 1;
+    if (helpers > 0) crowd_share(s, dyn, ws, views, bin_view, total_bins, groups, cap, helpers, bin, -1, part, parts);
+  }
+  const uint32_t kmin = s.kmin, kmax = s.kmax;
+  const uint64_t end = ((uint64_t)kmax << 32 | 0xFFFFFFFFull) + 1ull;
+  uint64_t lo = (uint64_t)kmin << 32;
+  uint64_t counted = lo;  // s.before holds the entries below it
+  if (threadIdx.x < NTILE) s.total[threadIdx.x] = s.before[threadIdx.x] = 0u;
+  const auto whole = [&](uint32_t e) { return entries[e]; };
+  const auto unique = [](const Entry &e) { return (uint64_t)e.key << 32 | e.id; };
+  int turn = 0;
+  bool totals = false, reserved = false, placed = false;
+  while (lo < end) {
+    // The ends of the rounds come from a histogram over LPARTS equal parts of
+    // what is left; where the first part alone exceeds cap it is divided
+    // again.
+    uint32_t *hist = a.key;
+    int sh = 0;
+    while ((end - lo) >> sh > (uint64_t)LPARTS) ++sh;
+    for (;;) {
+      __syncthreads();
+      for (int b = threadIdx.x; b < LPARTS; b += LB) hist[b] = 0u;
+      __syncthreads();
+      uint32_t c[NTILE];
+#pragma unroll
+      for (int t = 0; t < NTILE; ++t) c[t] = 0u;
+      for_entries(s, ws, vi, view, local, groups, whole, [&](uint32_t, uint32_t, const Entry &e) {
+        const uint64_t k = unique(e);
+        if (k >= lo && (k - lo) >> sh < (uint64_t)LPARTS) atomicAdd(&hist[(k - lo) >> sh], 1u);
+        if (!totals) count_mask(c, e.mask);
+      });
+      if (!totals) add_counts(c, s.total);
+      totals = true;
+      // Entries in front of each part, then the rounds' ends.
+      {
+        constexpr int PER = LPARTS / LB;
+        uint32_t h[PER], sum = 0u, total;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) sum += h[k] = hist[threadIdx.x * PER + k];
+        uint32_t run = block_exclusive_scan<LB>(sum, s.w, total);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          hist[threadIdx.x * PER + k] = run;
+          run += h[k];
+        }
+        if (threadIdx.x == 0) s.end = total;
+      }
+      __syncthreads();
+      if (threadIdx.x < 64) round_ends(s, hist, cap);
+      if (threadIdx.x == 64 && parts > 1 && !reserved) {
+        uint32_t all = 0u;
+        for (int t = 0; t < NTILE; ++t) all += s.total[t];
+        shared_reserve(ws, bin, all, cap_pairs);
+      }
+      reserved = true;
+      __syncthreads();
+      if (s.bounds > 0u) break;
+      sh = sh > 12 ? sh - 12 : 0;  // (at sh = 0 a part is one key, which one entry has)
+    }
+    const int bounds = (int)s.bounds;
+    uint64_t from = lo;
+    for (int r = 0; r < bounds; ++r, ++turn) {
+      const uint64_t first = from, last = min(lo + ((uint64_t)s.bound[r] << sh), end);
+      from = last;
+      if (turn % parts != part) continue;
+      // The round's entries, and the tiles' entries in front of it.
+      const bool one = first >> 32 == (last - 1ull) >> 32;  // a single depth: by index
+      __syncthreads();
+      if (threadIdx.x == 0) s.n = 0u;
+      __syncthreads();
+      uint32_t c[NTILE];
+#pragma unroll
+      for (int t = 0; t < NTILE; ++t) c[t] = 0u;
+      for_entries(s, ws, vi, view, local, groups, whole, [&](uint32_t, uint32_t i, const Entry &e) {
+        const uint64_t k = unique(e);
+        if (k >= first && k < last) {
+          const uint32_t q = atomicAdd(&s.n, 1u);
+          a.key[q] = one ? e.id : e.key;
+          a.at[q] = i;
+        } else if (k >= counted && k < first) {
+          count_mask(c, e.mask);
+        }
+      });
+      add_counts(c, s.before);
+      counted = last;
+      __syncthreads();
+      const int n = (int)s.n;
+      if (n == 0) continue;
+      const uint32_t key0 = one ? max((uint32_t)first, id0) : (uint32_t)(first >> 32);
+      const uint32_t key1 = one ? min((uint32_t)(last - 1ull), id0 + (uint32_t)n_gauss - 1u)
+                                : min((uint32_t)((last - 1ull) >> 32), kmax);
+      const int I = (n + LB - 1) / LB;
+      const int at = wave * 64 * I + lane;
+      sort_entries(s, a, n, I, at, key0, key1 <= key0 ? 0 : 32 - __clz(key1 - key0), entries, id0, id_bits);
+      masks_of(shift, s, a, entries, n, I, at);
+      __syncthreads();
+      if (threadIdx.x < 64) {
+        if (!placed) {
+          const uint32_t tot = lane < NTILE ? s.total[lane] : 0u;
+          uint32_t all, start;
+          const uint32_t pre = tile_scan(tot, all);
+          unsigned long long at0 = 0ull;
+          if (lane == 0) {
+            if (parts > 1) {
+              at0 = shared_wait(ws, bin);
+            } else {
+              at0 = atomicAdd(reinterpret_cast<unsigned long long *>(ws.hdr + HDR_NLISTED), (unsigned long long)all);
+              if (at0 + all > cap_pairs) at0 = NO_PLACE;
+            }
+          }
+          at0 = __shfl(at0, 0);
+          const bool fits = at0 != NO_PLACE;
+          start = (uint32_t)at0 + pre;
+          if (lane == 0) s.most = fits ? 0u : 0xFFFFFFFFu;
+          if (lane < NTILE) s.next[lane] = start;
+          if (part == 0 && my_tile)
+            ws.ranges[tile] = fits ? make_int2((int)start, (int)(start + tot)) : make_int2(0, 0);
+        }
+        if (lane < nt) {
+          uint32_t seen = s.before[lane];
+          const uint32_t start = s.next[lane];
+#pragma unroll
+          for (int w = 0; w < LW; ++w) {
+            const uint32_t k = s.tile[w][lane];
+            s.tile[w][lane] = start + seen;
+            seen += k;
+          }
+          s.before[lane] = seen;
+        }
+      }
+      __syncthreads();
+      if (!placed && s.most == 0xFFFFFFFFu) return;
+      placed = true;
+      lists_of(shift, s, a, ws.ids, n, I, at);
+    }
+    lo = from;
   }
 }
 
@@ -682,9 +959,9 @@ void launch_bin_lists(const Plan &p, const Workspace &ws, const ViewInfo *views,
                       int order_total, hipStream_t s) {
   int id_bits = 1;
   while ((1ll << id_bits) < p.n) ++id_bits;
-  hipLaunchKernelGGL(k_bin_lists, dim3((unsigned)p.total_bins + 2u), dim3(LB), (size_t)p.lists_cap * LISTS_ENTRY_BYTES,
+  hipLaunchKernelGGL(k_bin_lists, dim3((unsigned)(p.total_bins + p.lists_helpers) + 2u), dim3(LB), (size_t)p.lists_cap * LISTS_ENTRY_BYTES,
                      s, views, bin_view, ws, p.n, id_bits, p.blocks_per_view * p.pre_rounds, p.blocks_per_view * p.n_views,
-                     (unsigned long long)p.capacity, p.lists_cap, order_total);
+                     (unsigned long long)p.capacity, p.lists_cap, order_total, p.total_bins, p.lists_helpers);
 }
 
 // ------------------------------------------------------- lists for inspection

@@ -342,7 +342,7 @@ template <bool SH>
 __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_preprocess(gsr_gaussians g, const gsr_camera *__restrict__ cams,
                                                           const ViewInfo *__restrict__ views, PreConsts pc,
                                                           Workspace ws, int bpv, int rounds, int lds_bins,
-                                                          unsigned long long cap) {
+                                                          unsigned long long cap, int shared_bins) {
   constexpr int NW = PRE_BLOCK / 64;
   extern __shared__ uint32_t s_cur[];  // [lds_bins]
   __shared__ ProjArgs s_args;
@@ -371,6 +371,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   // or without an alpha threshold).
   const bool cull = !(pc.flags & GSR_FULL_RECT) && pc.alpha_min > 0.f;
   if (threadIdx.x < PRE_ROUNDS_MAX * PRE_BLOCK / 32) s_visible[threadIdx.x] = 0u;
+  for (int b = blockIdx.x * PRE_BLOCK + threadIdx.x; b < shared_bins; b += gridDim.x * PRE_BLOCK) ws.shared_place[b] = 0ull;
   if (threadIdx.x == 0) {
     s_used = header_used(ws.hdr) ? 1u : 0u;
     if (blockIdx.x == 0) reset_header_words(ws.hdr);  // (read by the kernels behind this one)
@@ -411,6 +412,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   const int nleft = (int)s_nleft;
   const int shift = vi.bin_shift, S = 1 << shift, nb = vi.BX * vi.BY;
   unsigned long long pairs = 0ull;
+  uint32_t largest = 0u;  // entries of a group
   for (int batch = 0; batch < rounds; ++batch) {
     const int group = blockIdx.x * rounds + batch;
     if (batch * PRE_BLOCK >= nleft) {
@@ -499,7 +501,9 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
           for (int b0 = 0; b0 < cn; b0 += PRE_BLOCK) {
             const int b = b0 + (int)threadIdx.x;
             uint32_t total;
-            const uint32_t pre = block_exclusive_scan<PRE_BLOCK>(b < cn ? s_cur[b] : 0u, s_w, total) + carry;
+            const uint32_t count = b < cn ? s_cur[b] : 0u;
+            largest = max(largest, count);
+            const uint32_t pre = block_exclusive_scan<PRE_BLOCK>(count, s_w, total) + carry;
             if (b < cn) {
               s_cur[b] = pre;
               row[c0 + b] = pre;
@@ -538,11 +542,15 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   if ((int)threadIdx.x < words)
     ws.visible[(int64_t)blockIdx.x * words + threadIdx.x] = s_visible[threadIdx.x];
   for (int o = 32; o > 0; o >>= 1) pairs += __shfl_xor(pairs, o);
-  if ((threadIdx.x & 63) == 0) s_pairs[wave] = pairs;
+  largest = (uint32_t)wave_max((int)largest);
+  if ((threadIdx.x & 63) == 0) s_pairs[wave] = pairs | (unsigned long long)largest << PAIRS_BITS;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < NW; ++w) pairs += s_pairs[w];
-    ws.block_pairs[blockIdx.x] = pairs;
+    for (int w = 1; w < NW; ++w) {
+      pairs += s_pairs[w] & PAIRS_MASK;
+      largest = max(largest, (uint32_t)(s_pairs[w] >> PAIRS_BITS));
+    }
+    ws.block_pairs[blockIdx.x] = pairs | (unsigned long long)largest << PAIRS_BITS;
   }
 }
 
@@ -554,7 +562,7 @@ void launch_preprocess(const Plan &p, const gsr_gaussians &g, const gsr_camera *
     hipLaunchKernelGGL(g.sh ? k_preprocess<true> : k_preprocess<false>,
                        dim3((unsigned)(p.blocks_per_view * p.n_views)), dim3(PRE_BLOCK), (size_t)4 * p.lds_bins, s, g,
                        cams, views, pc, ws, p.blocks_per_view, p.pre_rounds, p.lds_bins,
-                       (unsigned long long)p.capacity);
+                       (unsigned long long)p.capacity, p.lists_helpers > 0 ? p.total_bins : 0);
 }
 
 // Reliable-Gaussian selection (Eq. 12): compare each centre's camera depth

@@ -398,17 +398,6 @@ __device__ __forceinline__ void store_sums(const float4v &D, uint32_t used, floa
   }
 }
 
-// Maximum over the wavefront of v >= 0, in a scalar register.
-__device__ __forceinline__ int wave_max(int v) {
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // row_shr:1
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));  // row_shr:2
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));  // row_shr:4
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));  // row_shr:8
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return __builtin_amdgcn_readlane(v, 63);
-}
-
 // State of a pixel's backward walk (see tile_backward).
 struct BwdPixel {
   float T, B;           // transmittance behind the current entry; blend behind it
