@@ -135,11 +135,17 @@ def _cams_ptr(cams: torch.Tensor, n_views: int):
     return cams.data_ptr()
 
 
+# torch.cuda.current_stream().cuda_stream without the Python object (a few us a
+# call), in the torch builds that have it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream=None):
     if stream is not None:
         return stream.cuda_stream
-    # torch.cuda.current_stream().cuda_stream without the Python object (a few us a call)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 class Renderer:
