@@ -209,12 +209,6 @@ void prof_end(gsr_ctx *ctx, hipStream_t s, int first_unmarked) {
   ctx->cur_events = nullptr;
 }
 
-// The gradient rows that a backward with these constants adds to.
-void launch_clear_grads(const Workspace &ws, int64_t n_rec, const RenderConsts &rc, hipStream_t s) {
-  launch_fill_f32(reinterpret_cast<float *>(ws.grad2d), 0.f, 2 * n_rec * GEO_ROW, s);
-  if (rc.grad_fields >> GEO_FIELDS) launch_fill_f32(reinterpret_cast<float *>(ws.grad_col), 0.f, 2 * n_rec * COL_ROW, s);
-}
-
 // Projection and tile lists.  The projection also clears grad2d for a fused
 // step; with order_queue the lists kernel writes the rasteriser's
 // longest-first work order.
@@ -510,7 +504,7 @@ gsr_status gsr_render_backward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_c
   prof_begin(ctx, s);
   // The gradient rows are cleared inside the (otherwise empty) stages before
   // the backward rasteriser, so its stage times the kernel alone.
-  launch_clear_grads(ws, p.n_rec, consts(*cfg, *g), s);
+  launch_clear_grads(p, ws, consts(*cfg, *g), s);
   for (int j = 0; j <= GSR_STAGE_RASTER; ++j) prof_mark(ctx, s, j);
   launch_render_backward(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), g_rgb, g_depth, g_T, s);
   prof_mark(ctx, s, GSR_STAGE_RASTER_BWD);
@@ -765,7 +759,7 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
     for (int r = 0; r <= reps && st == GSR_OK; ++r) {
       launch_fill_u32(ws.hdr + HDR_QUEUE, 0u, 1, s);
       if (t.lpt_order) launch_queue_order(ws, p.total_tiles, s);
-      launch_clear_grads(ws, p.n_rec, consts(*cfg, *g), s);
+      launch_clear_grads(p, ws, consts(*cfg, *g), s);
       (void)hipEventRecord(e0, s);
       launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), target_rgb, target_depth,
                           pixel_mask, w_rgb, w_depth, nullptr, nullptr, t, ctx->num_cus, s);

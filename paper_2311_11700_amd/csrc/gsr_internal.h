@@ -456,6 +456,10 @@ void launch_expand_add(const Plan &p, const ViewInfo *views, const gsr_camera *c
 void launch_expand_delete(const gsr_gaussians &g, const gsr_camera *cam, const float *depth_obs, int W, int H,
                           float gamma, float eta, float z_near, float *logit_out, uint8_t *decayed, hipStream_t s);
 
+// Clears the gradient rows that a backward with these constants adds to: those
+// of the records that the last projection on the workspace found visible.
+void launch_clear_grads(const Plan &p, const Workspace &ws, const RenderConsts &rc, hipStream_t s);
+
 // Backward preprocess (chain to parameters and pose; with loss, also the fused
 // step's tile losses summed into *loss).
 void launch_preprocess_backward(const Plan &p, const gsr_gaussians &g, const gsr_camera *cams,
