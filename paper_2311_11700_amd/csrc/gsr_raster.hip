@@ -486,11 +486,11 @@ __device__ __forceinline__ uint32_t backward_group(const Staged *s_rec, int slot
 // contraction, and the sums that they belong to are made NaN behind it.
 // Bits 8 + e and 16 + e of the result: the dLdP, resp. w, of entry e was not
 // finite at some pixel, the dLdP at one that blends it.  (Found again here, so
-// that the walk itself pays one test a group.  A step over three ragged views,
-// whose longest tile is the tail of the step: 282 us without the test, 286 with
-// it, 297 with the selects in the walk, 303 with a second loop over the groups,
-// which spills 50 registers; 300 000 Gaussians at 1200x680: 257.5, 256.4, 258.6,
-// 280 us.)
+// that the walk itself pays one test a group.  Measured in the fused step, which
+// needs none: three ragged views, whose longest tile is the tail of the step,
+// 282 us without it, 286 with it, 297 with the selects in the walk, 303 with a
+// second loop over the groups, which spills 50 registers; 300 000 Gaussians at
+// 1200x680 257.5, 256.4, 258.6, 280 us.)
 __device__ __forceinline__ uint32_t clean_rows(const Staged *s_rec, int slot, int first, const RenderConsts &rc,
                                                const BwdPixel &px, uint32_t *rows) {
   uint32_t bad = 0u;
@@ -626,8 +626,10 @@ __device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, con
   // Wild: some pixel's upstream gradient is infinite or NaN (or so large that a
   // product might be), or its transmittance has reached 0, which the walk
   // divides.  Only the sums of the Gaussians that the pixel blends may see it,
-  // and of these only the ones that it enters.
-  const bool wild = __builtin_amdgcn_ballot_w64(!(fabsf(px.gC0) + fabsf(px.gC1) + fabsf(px.gC2) + fabsf(px.gD) +
+  // and of these only the ones that it enters.  (Not in the fused step, whose
+  // upstream gradients are the weights with a sign; an alpha of exactly 1, which
+  // alone makes a 0 that is divided by 0, spoils the sums in front there.)
+  const bool wild = BLO && __builtin_amdgcn_ballot_w64(!(fabsf(px.gC0) + fabsf(px.gC1) + fabsf(px.gC2) + fabsf(px.gD) +
                                                   fabsf(px.Kf) < 1e30f) || !(px.T > 0.f)) != 0;
 
   // Sub-batches [b SUB, (b + 1) SUB), walked from the last one that holds
