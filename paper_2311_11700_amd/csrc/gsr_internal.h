@@ -263,8 +263,7 @@ __device__ __forceinline__ unsigned long long read_entry_cursor(uint32_t *hdr) {
 
 // First of n entries; used: header_used at the call's start.  (An untagged
 // word changes once, to a tagged one, so the loop runs twice at most.)  Should
-// the word of a used workspace hold no tag, the place is past any capacity
-// (and below 2^63, so that the end of the entries can be formed).
+// the word of a used workspace hold no tag, the place is past any capacity.
 __device__ __forceinline__ unsigned long long reserve_entries(uint32_t *hdr, bool used, uint32_t n) {
   if (!used) {
     unsigned long long seen = read_entry_cursor(hdr);
@@ -274,7 +273,8 @@ __device__ __forceinline__ unsigned long long reserve_entries(uint32_t *hdr, boo
       seen = old;
     }
   }
-  return (atomicAdd(entry_cursor(hdr), (unsigned long long)n) ^ ENTRY_TAG) & ~(1ull << 63);
+  const unsigned long long at = atomicAdd(entry_cursor(hdr), (unsigned long long)n);
+  return (at & ~ENTRY_COUNT_MASK) == ENTRY_TAG ? at & ENTRY_COUNT_MASK : 1ull << 62;
 }
 
 __device__ __forceinline__ unsigned long long lanemask_lt() {
