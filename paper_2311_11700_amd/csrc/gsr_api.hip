@@ -232,7 +232,7 @@ void enqueue_fused(gsr_ctx *ctx, const gsr_gaussians &g, const gsr_camera *cams,
   prof_begin(ctx, s);
   enqueue_lists(ctx, g, cams, cfg, ws, true, ctx->tuning.lpt_order != 0, s);
   prof_mark(ctx, s, GSR_STAGE_RANGES);
-  launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, g, consts(cfg, g), t_rgb, t_depth, pmask, w_rgb,
+  launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, consts(cfg, g), t_rgb, t_depth, pmask, w_rgb,
                       w_depth, loss_cap, out, ctx->tuning, ctx->num_cus, s);
   prof_mark(ctx, s, GSR_STAGE_RASTER);
   prof_mark(ctx, s, GSR_STAGE_RASTER_BWD);
@@ -335,7 +335,11 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
   // two rounds 255 us, one 263).  One view, which may see all of its Gaussians:
   // one round up to 1.2 M (fused step at 1200x680, all in view: 300 000 two
   // rounds 255 us, one 240; 500 000 three rounds 300, one 281; a million four
-  // 393, one 382; with 43 % in view 259 and 260, 308 and 288, 544 and 512).
+  // 393, one 382; with 43 % in view 259 and 260, 308 and 288, 544 and 512), and
+  // more above, where a block a CU is there several times over (forward, one,
+  // two and four rounds, 57 % in view: 1.5 M 379, 374, 365; 3 M 707, 706, 675;
+  // 5 M 1224, 1208, 1157; 22 % in view 306, 275, 274; 458, 418, 393; 568, 487,
+  // 457).
   const int64_t per_round = PRE_BLOCK * (n_views > 1 ? 256 : 1200);
   const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(PRE_ROUNDS_MAX, n * n_views / per_round));
   const int64_t bpv = (n + PRE_BLOCK * rounds - 1) / (PRE_BLOCK * rounds);
@@ -468,7 +472,7 @@ gsr_status gsr_render_forward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_ca
   prof_begin(ctx, s);
   enqueue_lists(ctx, *g, cams, *cfg, ws, false, false, s);
   prof_mark(ctx, s, GSR_STAGE_RANGES);
-  launch_render_forward(ctx->plan, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), out, s);
+  launch_render_forward(ctx->plan, ws, ctx->views_dev, ctx->tile_view_dev, consts(*cfg, *g), out, s);
   prof_end(ctx, s, GSR_STAGE_RASTER);
   if ((st = last_launch(ctx, "gsr_render_forward launch")) != GSR_OK) return st;
   ctx->last_forward_ws = workspace;
@@ -506,7 +510,7 @@ gsr_status gsr_render_backward(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_c
   // the backward rasteriser, so its stage times the kernel alone.
   launch_clear_grads(p, ws, consts(*cfg, *g), s);
   for (int j = 0; j <= GSR_STAGE_RASTER; ++j) prof_mark(ctx, s, j);
-  launch_render_backward(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), g_rgb, g_depth, g_T, s);
+  launch_render_backward(p, ws, ctx->views_dev, ctx->tile_view_dev, consts(*cfg, *g), g_rgb, g_depth, g_T, s);
   prof_mark(ctx, s, GSR_STAGE_RASTER_BWD);
   launch_preprocess_backward(p, *g, cams, *cfg, ws, *grads, nullptr, s);
   prof_end(ctx, s, GSR_STAGE_PREGRAD);
@@ -761,7 +765,7 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
       if (t.lpt_order) launch_queue_order(ws, p.total_tiles, s);
       launch_clear_grads(p, ws, consts(*cfg, *g), s);
       (void)hipEventRecord(e0, s);
-      launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), target_rgb, target_depth,
+      launch_render_fused(p, ws, ctx->views_dev, ctx->tile_view_dev, consts(*cfg, *g), target_rgb, target_depth,
                           pixel_mask, w_rgb, w_depth, nullptr, nullptr, t, ctx->num_cus, s);
       (void)hipEventRecord(e1, s);
       st = hip_check(ctx, hipEventSynchronize(e1), "hipEventSynchronize");
@@ -925,7 +929,7 @@ gsr_status gsr_work_counts(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_confi
   if (g->n != ctx->plan.n) return fail(ctx, GSR_E_INVALID, "Gaussian count differs from the plan");
   hipStream_t s = static_cast<hipStream_t>(stream);
   Workspace ws = make_ws(ctx->plan, workspace);
-  launch_work_counts(ctx->plan, ws, ctx->views_dev, ctx->tile_view_dev, *g, consts(*cfg, *g), s);
+  launch_work_counts(ctx->plan, ws, ctx->views_dev, ctx->tile_view_dev, consts(*cfg, *g), s);
   unsigned long long host[4];
   gsr_status st = hip_check(ctx, hipMemcpyAsync(host, ws.counts, sizeof(host), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
   if (st == GSR_OK) st = hip_check(ctx, hipStreamSynchronize(s), "hipStreamSynchronize");

@@ -49,7 +49,6 @@ enum HeaderWord {
   HDR_REQUIRED = 2,    // u64 (words 2-3): largest pair count seen that overflowed
   HDR_OVERFLOW = 4,    // u32: set when a forward overflowed the pair buffer
   HDR_QUEUE = 5,       // u32: persistent rasteriser work counter
-  HDR_FWD_DONE = 6,    // u32: marker that a forward filled this workspace
   HDR_MAGIC = 8,       // u32 x 2 (words 8-9): set once the header has been initialised
   HDR_NLISTED = 12,    // u64 (words 12-13): pairs inside the alpha support (the tile lists)
   HDR_COSTS = 14,      // u32: a fused step has recorded every tile's duration (sticky)
@@ -75,7 +74,6 @@ constexpr int ENTRY_COUNT_BITS = 44;
 constexpr unsigned long long ENTRY_COUNT_MASK = (1ull << ENTRY_COUNT_BITS) - 1ull;
 constexpr unsigned long long ENTRY_TAG = 0xA53C7ull << ENTRY_COUNT_BITS;
 
-// Device pointers into the caller's workspace (computed on the host).
 // ------------------------------------------------------- alpha support
 //
 // Tiles of a Gaussian's rectangle that it can reach with alpha >= alpha_min.
@@ -139,6 +137,7 @@ constexpr uint32_t NO_BASE = 0xFFFFFFFFu;
 constexpr int PAIRS_BITS = 48;
 constexpr unsigned long long PAIRS_MASK = (1ull << PAIRS_BITS) - 1ull;
 
+// Device pointers into the caller's workspace (computed on the host).
 struct Workspace {
   uint32_t *hdr;
   // [n_rec][REC_ROW]: (u_hi, u_lo, v_hi, v_lo), (conic a, b, c, opacity),
@@ -250,7 +249,6 @@ __device__ __forceinline__ void reset_header_words(uint32_t *hdr) {
   hdr[HDR_NLISTED] = 0u;
   hdr[HDR_NLISTED + 1] = 0u;
   hdr[HDR_QUEUE] = 0u;
-  hdr[HDR_FWD_DONE] = 1u;
 }
 
 __device__ __forceinline__ unsigned long long *entry_cursor(uint32_t *hdr) {
@@ -399,8 +397,8 @@ void launch_preprocess(const Plan &p, const gsr_gaussians &g, const gsr_camera *
 void launch_select_reliable(const gsr_gaussians &g, const gsr_camera *cam, const float *depth, int W, int H,
                             float eps, float z_near, uint8_t *out, hipStream_t s);
 
-// Start of a call (before the projection), and the tile lists from the bin
-// entries.  With order_total > 0 the lists kernel also writes the rasteriser's
+// Start of a call without Gaussians (in any other the projection does it), and
+// the tile lists from the bin entries.  With order_total > 0 the lists kernel also writes the rasteriser's
 // longest-first work order of that many tiles (from the durations the last
 // fused step recorded).
 void launch_lists_begin(const Workspace &ws, hipStream_t s);
@@ -415,20 +413,20 @@ void launch_queue_order(const Workspace &ws, int total_tiles, hipStream_t s);
 
 // Rasterisation.
 void launch_render_forward(const Plan &p, const Workspace &ws, const ViewInfo *views,
-                           const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
+                           const int32_t *tile_view, const RenderConsts &rc,
                            const gsr_images *out, hipStream_t s);
 void launch_render_backward(const Plan &p, const Workspace &ws, const ViewInfo *views,
-                            const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
+                            const int32_t *tile_view, const RenderConsts &rc,
                             const float *g_rgb, const float *g_depth, const float *g_T,
                             hipStream_t s);
 void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *views,
-                         const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
+                         const int32_t *tile_view, const RenderConsts &rc,
                          const float *t_rgb, const float *t_depth, const uint8_t *pmask,
                          float w_rgb, float w_depth, const float *loss_cap, const gsr_images *out, const Tuning &tun, int num_cus, hipStream_t s);
-// Work totals of the last forward (re-walks its lists; needs the Gaussians'
-// colours and the constants of that call).
+// Work totals of the last forward (re-walks its lists; needs the constants of
+// that call).
 void launch_work_counts(const Plan &p, const Workspace &ws, const ViewInfo *views, const int32_t *tile_view,
-                        const gsr_gaussians &g, const RenderConsts &rc, hipStream_t s);
+                        const RenderConsts &rc, hipStream_t s);
 void launch_l1(const Plan &p, const ViewInfo *views, const float *rgb, const float *depth,
                const float *t_rgb, const float *t_depth, const uint8_t *pmask, float w_rgb,
                float w_depth, const float *loss_cap, float *g_rgb, float *g_depth, float *loss, hipStream_t s);

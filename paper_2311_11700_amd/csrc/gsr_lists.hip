@@ -7,8 +7,8 @@
 // bin it reaches: a few entries instead of one pair per tile.  The projection
 // writes each block's entries grouped by bin, with the offsets of the groups;
 // one block per bin then collects its groups, sorts them by depth in LDS and
-// writes the lists of all its tiles from the masks.  So the lists take two
-// kernels beside the projection whatever the sizes, with no global sort.
+// writes the lists of all its tiles from the masks.  So the lists take one
+// kernel beside the projection whatever the sizes, with no global sort.
 // Every grid is fixed by the plan and every count is read on the device, so
 // the sequence can be captured in a HIP graph.
 //

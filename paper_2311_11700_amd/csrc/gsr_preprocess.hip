@@ -3,10 +3,11 @@
 // (GS-SLAM Eq. 2-3, supplement eq. q2R).
 //
 // Forward geometry runs in FP64: gfx950 executes FP64 vector arithmetic at
-// the FP32 non-packed rate, and computing the binning quantities (depth sort
-// key, tile rectangle) in FP64 with contraction disabled makes them agree bit
-// for bit with an FP64 reference evaluated in the same order.  The values the
-// rasteriser consumes are rounded to FP32 once, at the end.
+// the FP32 non-packed rate.  The camera-frame centre, and so the depth sort key,
+// agrees bit for bit with an FP64 reference evaluated in the same order
+// (contraction is off); the covariance and the tile rectangle, formed without
+// the 3x3 covariance and with reciprocals, agree up to FP64 rounding.  The
+// values the rasteriser consumes are rounded to FP32 once, at the end.
 #pragma clang fp contract(off)
 
 #include <math.h>

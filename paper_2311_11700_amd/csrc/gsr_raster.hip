@@ -168,7 +168,7 @@ __device__ __forceinline__ float entry_depth(int pos, int lo, const Staged *s_re
 // entry that stopped a pixel), counts[2] += entries blended.  The render
 // kernels do not count; gsr_work_counts re-walks the lists with counting on.
 template <bool COUNT, int NB = BATCH>
-__device__ __forceinline__ void tile_forward(const TileInfo &ti, int64_t n, const float4 *__restrict__ rec,
+__device__ __forceinline__ void tile_forward(const TileInfo &ti, const float4 *__restrict__ rec,
                                              const uint32_t *__restrict__ ids, const RenderConsts &rc,
                                              Staged *s_rec, FwdState &st, unsigned long long *counts,
                                              uint32_t *s_id = nullptr, int *staged_lo = nullptr) {
@@ -535,7 +535,7 @@ __device__ __forceinline__ void spoil_sums(uint32_t bad, float *sum) {
 // gradient) they are in.gC / in.gD themselves, split into high and low bf16
 // halves like the A values.
 template <bool BLO>
-__device__ __forceinline__ void tile_backward(const TileInfo &ti, int64_t n, const float4 *__restrict__ rec,
+__device__ __forceinline__ void tile_backward(const TileInfo &ti, const float4 *__restrict__ rec,
                                               const uint32_t *__restrict__ ids, const RenderConsts &rc,
                                               const BwdIn &in, double *__restrict__ grad2d, double *__restrict__ grad_col,
                                               Staged *s_rec, float *s_part, uint32_t *s_id, int *s_max,
@@ -750,13 +750,12 @@ struct RasterArgs {
   const int2 *ranges;
   const ViewInfo *views;
   const int32_t *tile_view;
-  int64_t n;
   RenderConsts rc;
 };
 
 static RasterArgs raster_args(const Workspace &ws, const ViewInfo *views, const int32_t *tile_view,
-                              const gsr_gaussians &g, const RenderConsts &rc) {
-  return RasterArgs{ws.rec, ws.ids, ws.ranges, views, tile_view, g.n, rc};
+                              const RenderConsts &rc) {
+  return RasterArgs{ws.rec, ws.ids, ws.ranges, views, tile_view, rc};
 }
 
 // Per-pixel forward state that a separate backward reads (the unfused
@@ -777,7 +776,7 @@ __global__ __launch_bounds__(BLOCK) void k_render_fwd(RasterArgs a, PixelState p
   __shared__ Staged s_rec[BATCH];
   const TileInfo ti = tile_info(blockIdx.x, a.views, a.tile_view, a.ranges);
   FwdState st;
-  tile_forward<false>(ti, a.n, a.rec, a.ids, a.rc, s_rec, st, nullptr);
+  tile_forward<false>(ti, a.rec, a.ids, a.rc, s_rec, st, nullptr);
   if (!ti.inside) return;
   save_state(ps, ti.pix, st);
   const int64_t loc = ti.pix - ti.pix_off;
@@ -819,7 +818,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     in.gD = g_depth ? g_depth[ti.pix] : 0.f;
     in.gT = g_T ? g_T[ti.pix] : 0.f;
   }
-  tile_backward<true>(ti, a.n, a.rec, a.ids, a.rc, in, grad2d, grad_col, s_rec, s_part, s_id, s_max, s_mA);
+  tile_backward<true>(ti, a.rec, a.ids, a.rc, in, grad2d, grad_col, s_rec, s_part, s_id, s_max, s_mA);
 }
 
 __device__ __forceinline__ float sgnf(float x) { return (float)((x > 0.f) - (x < 0.f)); }
@@ -888,7 +887,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       FwdState st;
       int staged_lo;
-      tile_forward<false, NB>(ti, a.n, a.rec, a.ids, a.rc, s_rec, st, nullptr, s_id,
+      tile_forward<false, NB>(ti, a.rec, a.ids, a.rc, s_rec, st, nullptr, s_id,
                           &staged_lo);
       BwdIn in{st.T, ti.inside ? st.last : 0, st.zr, 0.f, 0.f, 0.f, 0.f, 0.f};
       float lpx = 0.f;
@@ -928,7 +927,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       const float ls = wave_sum(lpx);
       if ((threadIdx.x & 63) == 0) s_loss[threadIdx.x >> 6] = ls;
-      tile_backward<false>(ti, a.n, a.rec, a.ids, a.rc, in, grad2d, grad_col, s_rec, s_part, s_id, s_max,
+      tile_backward<false>(ti, a.rec, a.ids, a.rc, in, grad2d, grad_col, s_rec, s_part, s_id, s_max,
                            s_mA, staged_lo, w_rgb, w_depth);
       if (threadIdx.x == 0) {
         tile_loss[tile] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
@@ -995,9 +994,9 @@ void launch_l1(const Plan &p, const ViewInfo *views, const float *rgb, const flo
 }
 
 void launch_render_forward(const Plan &p, const Workspace &ws, const ViewInfo *views,
-                           const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
+                           const int32_t *tile_view, const RenderConsts &rc,
                            const gsr_images *out, hipStream_t s) {
-  const RasterArgs a = raster_args(ws, views, tile_view, g, rc);
+  const RasterArgs a = raster_args(ws, views, tile_view, rc);
   gsr_images o{nullptr, nullptr, nullptr, nullptr, nullptr};
   if (out) o = *out;
   PixelState ps{ws.T_final, ws.last, ws.zr};
@@ -1005,19 +1004,19 @@ void launch_render_forward(const Plan &p, const Workspace &ws, const ViewInfo *v
 }
 
 void launch_render_backward(const Plan &p, const Workspace &ws, const ViewInfo *views,
-                            const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
+                            const int32_t *tile_view, const RenderConsts &rc,
                             const float *g_rgb, const float *g_depth, const float *g_T, hipStream_t s) {
-  const RasterArgs a = raster_args(ws, views, tile_view, g, rc);
+  const RasterArgs a = raster_args(ws, views, tile_view, rc);
   hipLaunchKernelGGL(k_render_bwd, dim3(p.total_tiles), dim3(BLOCK), 0, s, a, ws.T_final, ws.last, ws.zr, g_rgb,
                      g_depth, g_T, ws.grad2d, ws.grad_col);
 }
 
 void launch_render_fused(const Plan &p, const Workspace &ws, const ViewInfo *views,
-                         const int32_t *tile_view, const gsr_gaussians &g, const RenderConsts &rc,
+                         const int32_t *tile_view, const RenderConsts &rc,
                          const float *t_rgb, const float *t_depth, const uint8_t *pmask, float w_rgb,
                          float w_depth, const float *loss_cap, const gsr_images *out,
                          const Tuning &tun, int num_cus, hipStream_t s) {
-  const RasterArgs a = raster_args(ws, views, tile_view, g, rc);
+  const RasterArgs a = raster_args(ws, views, tile_view, rc);
   gsr_images o{nullptr, nullptr, nullptr, nullptr, nullptr};
   if (out) o = *out;
   int grid = tun.blocks_per_cu * num_cus;
@@ -1051,7 +1050,7 @@ __global__ __launch_bounds__(BLOCK) void k_count_walk(RasterArgs a, const uint32
   __shared__ Staged s_rec[BATCH];
   const TileInfo ti = tile_info(blockIdx.x, a.views, a.tile_view, a.ranges);
   FwdState st;
-  tile_forward<true>(ti, a.n, a.rec, a.ids, a.rc, s_rec, st, counts);
+  tile_forward<true>(ti, a.rec, a.ids, a.rc, s_rec, st, counts);
   unsigned long long c = ti.inside ? (unsigned long long)st.last : 0ull;
   for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(counts + 3, c);
@@ -1060,9 +1059,9 @@ __global__ __launch_bounds__(BLOCK) void k_count_walk(RasterArgs a, const uint32
 }
 
 void launch_work_counts(const Plan &p, const Workspace &ws, const ViewInfo *views, const int32_t *tile_view,
-                        const gsr_gaussians &g, const RenderConsts &rc, hipStream_t s) {
+                        const RenderConsts &rc, hipStream_t s) {
   launch_fill_u32(reinterpret_cast<uint32_t *>(ws.counts), 0u, 8, s);
-  const RasterArgs a = raster_args(ws, views, tile_view, g, rc);
+  const RasterArgs a = raster_args(ws, views, tile_view, rc);
   if (p.total_tiles > 0)
     hipLaunchKernelGGL(k_count_walk, dim3(p.total_tiles), dim3(BLOCK), 0, s, a, ws.hdr, ws.counts);
 }
