@@ -337,7 +337,8 @@ gsr_status gsr_autotune(gsr_ctx *ctx, const gsr_gaussians *g, const gsr_camera *
  * the next step.  Asynchronous; calls on several streams of one context take
  * turns where a view has more than 32768 pixels (they share counters of the
  * context, which a captured call does not use: there, and on the null stream
- * while another stream is captured, one block counts a view of any size). */
+ * while another stream is captured, one block counts a view of any size, 130 us
+ * at 640x480 where many blocks take 22). */
 gsr_status gsr_loss_median(gsr_ctx *ctx, const float *px_loss, const uint8_t *pixel_mask, float factor,
                            float *cap_out, gsr_stream stream);
 
