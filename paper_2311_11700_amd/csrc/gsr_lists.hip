@@ -204,7 +204,7 @@ __device__ __forceinline__ void order_slot(const ListsArrays &a, uint16_t *from,
 #pragma unroll
     for (int i = 0; i < N; ++i) f[i] = i < n ? from[first + i] : 0u;
 #pragma unroll
-    for (int i = 0; i < N; ++i) k[i] = i < n ? a.key[f[i]] : 0xFFFFFFFFu;  // (keys are below 2^31)
+    for (int i = 0; i < N; ++i) k[i] = i < n ? a.key[f[i]] : 0xFFFFFFFFu;  // (no key: neither a depth nor an id)
     auto order = [&](int i, int j) {
       const bool swap = k[j] < k[i];
       const uint32_t ki = k[i], fi = f[i];

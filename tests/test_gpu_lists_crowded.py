@@ -109,6 +109,16 @@ def test_crowded_views_beside_others(gsr_lib):
     _check(gsr, sc, cams, lambda rng: _longest(2)(rng) + [1], largest=20_000)
 
 
+@pytest.mark.parametrize("n", [9_000, 30_000])
+def test_single_depths_in_several_views(gsr_lib, n):
+    """Bins and rounds of one depth are sorted by index: in views whose record
+    ids do not start at 0."""
+    gsr = gsr_lib
+    sc = _cloud(n, 10, 0.3, lambda g, k: np.full(k, 2.0))
+    cam = W.camera_small()
+    _check(gsr, sc, [cam.with_size(20.0 + v, 20.0, 15.5, 15.5, 32, 32) for v in range(3)], _longest(1), largest=n // 6)
+
+
 def test_every_bin_crowded(gsr_lib):
     gsr = gsr_lib
     sc = _cloud(14_000, 8, 0.6, lambda g, n: g.uniform(2.0, 4.0, n), log_scale=0.3)
