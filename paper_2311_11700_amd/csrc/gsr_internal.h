@@ -133,7 +133,7 @@ struct Entry {
   uint32_t key, id, mask;
 };
 constexpr uint32_t NO_BASE = 0xFFFFFFFFu;
-// (a block has at most 2 048 records of 2^24 tiles, and 512 entries of a batch in a bin)
+// (a block has at most 2 048 records of 2^24 tiles, and as many entries in a bin)
 constexpr int PAIRS_BITS = 48;
 constexpr unsigned long long PAIRS_MASK = (1ull << PAIRS_BITS) - 1ull;
 
@@ -150,7 +150,7 @@ struct Workspace {
   uint32_t *group_off;
   uint32_t *block_base;    // [projection batches] (NO_BASE: none, or past the capacity)
   unsigned long long *block_pairs;  // [projection blocks] pairs (rectangle tiles) of the block's records, and from
-                                    // PAIRS_BITS on the entries of its largest group
+                                    // PAIRS_BITS on a bound of its entries in any bin
   uint32_t *ids;           // [capacity] record ids of the tile lists
   unsigned long long *shared_place;  // [total_bins] place of a bin's lists that several blocks write (0: none yet)
   int2 *ranges;            // [total_tiles]

@@ -665,7 +665,7 @@ __device__ __forceinline__ unsigned long long shared_wait(const Workspace &ws, i
 __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ views,
                                                   const int32_t *__restrict__ bin_view, Workspace ws, int64_t n_gauss,
                                                   int id_bits, int groups, int pre_blocks, unsigned long long cap_pairs,
-                                                  int cap, int order_total, int total_bins, int helpers) {
+                                                  int cap, int order_total, int n_views, int total_bins, int helpers) {
   extern __shared__ uint32_t dyn[];
   __shared__ ListsLds s;
   if (blockIdx.x == 0) {
@@ -713,10 +713,21 @@ __global__ __launch_bounds__(LB) void k_bin_lists(const ViewInfo *__restrict__ v
   int bin = (int)blockIdx.x - 2, part = 0, parts = 1;
   const bool helper = bin >= total_bins;
   if (helper) {
-    // No bin has more entries than its view's groups times the largest of them.
-    uint32_t most = 0u;
-    for (int j = threadIdx.x; j < pre_blocks; j += LB) most = max(most, (uint32_t)(ws.block_pairs[j] >> PAIRS_BITS));
-    if (!__syncthreads_or((uint64_t)most * (uint32_t)groups > (uint32_t)cap)) return;
+    // No bin has more entries than the blocks of its view together allow: most
+    // calls end here, and their helpers on the CUs that no bin needs (the ones of
+    // 1200x680 are gone in half the time of its bins; those that went on to the
+    // estimate, on a bound of the largest group alone, made its lists 1.5 us
+    // longer).
+    const int bpv = pre_blocks / n_views;
+    bool crowd = false;
+    for (int v = threadIdx.x >> 6; v < n_views; v += LW) {
+      uint32_t sum = 0u;
+      for (int j = threadIdx.x & 63; j < bpv; j += 64) sum += (uint32_t)(ws.block_pairs[(size_t)v * bpv + j] >> PAIRS_BITS);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+      crowd = crowd || sum > (uint32_t)cap;
+    }
+    if (!__syncthreads_or(crowd)) return;
     bin = crowd_share(s, dyn, ws, views, bin_view, total_bins, groups, cap, helpers, -1, bin - total_bins, part, parts);
     if (bin < 0) return;
   }
@@ -961,7 +972,7 @@ void launch_bin_lists(const Plan &p, const Workspace &ws, const ViewInfo *views,
   while ((1ll << id_bits) < p.n) ++id_bits;
   hipLaunchKernelGGL(k_bin_lists, dim3((unsigned)(p.total_bins + p.lists_helpers) + 2u), dim3(LB), (size_t)p.lists_cap * LISTS_ENTRY_BYTES,
                      s, views, bin_view, ws, p.n, id_bits, p.blocks_per_view * p.pre_rounds, p.blocks_per_view * p.n_views,
-                     (unsigned long long)p.capacity, p.lists_cap, order_total, p.total_bins, p.lists_helpers);
+                     (unsigned long long)p.capacity, p.lists_cap, order_total, p.n_views, p.total_bins, p.lists_helpers);
 }
 
 // ------------------------------------------------------- lists for inspection

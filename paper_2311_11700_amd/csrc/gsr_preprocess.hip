@@ -413,7 +413,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
   const int nleft = (int)s_nleft;
   const int shift = vi.bin_shift, S = 1 << shift, nb = vi.BX * vi.BY;
   unsigned long long pairs = 0ull;
-  uint32_t largest = 0u;  // entries of a group
+  uint32_t largest = 0u;  // the batches' largest groups among this thread's bins, summed
   for (int batch = 0; batch < rounds; ++batch) {
     const int group = blockIdx.x * rounds + batch;
     if (batch * PRE_BLOCK >= nleft) {
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     // The supports are needed no more, unless rows are to be found again.
     const bool listing = tile_rows <= (uint32_t)ROW_CACHE && nb <= lds_bins;
     uint32_t *row = ws.group_off + vi.mat_off + ((int64_t)blk * rounds + batch) * (nb + 1);
-    uint32_t carry = 0u;
+    uint32_t carry = 0u, most = 0u;
     // Sweep 0 over all bins (counts and offsets), then sweep 1 (entries).
     for (int sweep = 0; sweep < 2; ++sweep) {
       for (int c0 = 0; c0 < nb; c0 += lds_bins) {
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
             const int b = b0 + (int)threadIdx.x;
             uint32_t total;
             const uint32_t count = b < cn ? s_cur[b] : 0u;
-            largest = max(largest, count);
+            most = max(most, count);
             const uint32_t pre = block_exclusive_scan<PRE_BLOCK>(count, s_w, total) + carry;
             if (b < cn) {
               s_cur[b] = pre;
@@ -515,6 +515,7 @@ __global__ __launch_bounds__(PRE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
         }
       }
       if (sweep == 0) {
+        largest += most;
         if (threadIdx.x == 0) {
           row[nb] = carry;
           uint32_t base = NO_BASE;
