@@ -447,10 +447,11 @@ gsr_status gsr_plan(gsr_ctx *ctx, int64_t n, int n_views, const int32_t *wh_host
     const size_t bytes = median_scratch_bytes(n_views);
     st = hip_check(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->median_dev), bytes), "hipMalloc(median)");
     if (st == GSR_OK) st = hip_check(ctx, hipMemset(ctx->median_dev, 0, bytes), "hipMemset(median)");
-    // (a stream created non-blocking does not wait for the null stream's work)
-    if (st == GSR_OK) st = hip_check(ctx, hipStreamSynchronize(nullptr), "hipStreamSynchronize");
     if (st == GSR_OK && !ctx->median_done)
       st = hip_check(ctx, hipEventCreateWithFlags(&ctx->median_done, hipEventDisableTiming), "hipEventCreate");
+    // The first call waits for the clearing as for a call before it: a stream
+    // created non-blocking does not wait for the null stream's work by itself.
+    if (st == GSR_OK) st = hip_check(ctx, hipEventRecord(ctx->median_done, nullptr), "hipEventRecord");
   }
   if (st != GSR_OK) return st;
   ctx->largest_view = largest_view;
